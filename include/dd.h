@@ -229,7 +229,9 @@ dd_status dd_tune_load(const char *cache_path);
  * series of degree M: 13 + 2 max(M, 1) for M <= 3 and 17 + 2M above in
  * mixed precision, 4 fewer in the arrival rows of small exponents that skip
  * the exponent's rounding correction, 9 in all in those that fold the
- * series' linear term into the exponent; 29 + 2M in FP64).  Kernel names: "arrival_far",
+ * series' linear term into the exponent; 29 + 2M in FP64; FP64 maps, sums of
+ * Gaussians on the matrix cores, 2 per pair and Gaussian, counted with two
+ * Gaussians per pair).  Kernel names: "arrival_far",
  * "arrival_near", "map", "batch", "lag_rows", "reduce".                   */
 typedef struct {
   double ms;         /* summed event time of the launches                   */

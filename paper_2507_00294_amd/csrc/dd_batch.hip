@@ -53,9 +53,9 @@ __global__ void __launch_bounds__(256) k_batch_arrival_near(const BatchScan* __r
   }
 }
 
-// Map items; NEAR selects the near-band items (per-pair regimes) or the
-// far-region items (degree segments).
-template <int RM, bool MIXED, bool NEAR>
+// Map items (mixed precision); NEAR selects the near-band items (per-pair
+// regimes) or the far-region items (degree segments).
+template <int RM, bool NEAR>
 __global__ void __launch_bounds__(256) k_batch_map(const BatchScan* __restrict__ scans,
                                                    const BatchItem* __restrict__ items,
                                                    int n_items, int* __restrict__ counter) {
@@ -68,9 +68,9 @@ __global__ void __launch_bounds__(256) k_batch_map(const BatchScan* __restrict__
     const BatchItem bi = items[it];
     const BatchScan& S = scans[bi.scan];
     const MapItem mi{bi.tile, 0, bi.n_lo, bi.n_hi, bi.slot_flags & kSlotMask, NEAR ? 1 : 0, 0, 0};
-    do_map<RM, MIXED>(mi, S.map_time, S.pos, S.pos4, S.rows64, S.rows32, (double)S.map_x0,
-                      (double)S.map_y0, (double)S.map_step, (double)S.map_step, S.map_w, S.map_h,
-                      true, S.map_partial);
+    do_map<RM>(mi, S.map_time, (const float2*)S.pos, S.pos4, S.rows64, S.rows32, (double)S.map_x0,
+               (double)S.map_y0, (double)S.map_step, (double)S.map_step, S.map_w, S.map_h,
+               S.map_partial);
   }
 }
 
@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(256) k_reduce_batch(const BatchReduce* __restr
     const double v = Rd.pref * s;
     Rd.out[j] = v;
     flag_nonfinite(Rd.scan_flag, v, j);
-    flag_nonfinite(fl, v, e);
+    flag_nonfinite(fl, v, Rd.flag_off + j);
   }
 }
 
@@ -156,34 +156,25 @@ hipError_t launch_batch_near(const BatchScan* scans, const BatchItem* items, int
 }
 
 hipError_t launch_batch_map(const BatchScan* scans, const BatchItem* items, int32_t n_items,
-                            int* counter, int RM, bool mixed, bool near, hipStream_t st) {
+                            int* counter, int RM, bool near, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, st, counter);
   const unsigned blocks = persistent_blocks(n_items);
-#define DD_LAUNCH_ONE(C, MX, NR)                                                                 \
-  hipLaunchKernelGGL((k_batch_map<C, MX, NR>), dim3(blocks), dim3(256), 0, st, scans, items,     \
-                     n_items, counter)
-#define DD_LAUNCH_BATCH_MAP(C)                                                                   \
-  if (RM == C) {                                                                                 \
-    if (mixed) {                                                                                 \
-      if (near)                                                                                  \
-        DD_LAUNCH_ONE(C, true, true);                                                            \
-      else                                                                                       \
-        DD_LAUNCH_ONE(C, true, false);                                                           \
-    } else {                                                                                     \
-      if (near)                                                                                  \
-        DD_LAUNCH_ONE(C, false, true);                                                           \
-      else                                                                                       \
-        DD_LAUNCH_ONE(C, false, false);                                                          \
-    }                                                                                            \
-    return hipGetLastError();                                                                    \
+#define DD_LAUNCH_BATCH_MAP(C)                                                                  \
+  if (RM == C) {                                                                                \
+    if (near)                                                                                   \
+      hipLaunchKernelGGL((k_batch_map<C, true>), dim3(blocks), dim3(256), 0, st, scans, items,  \
+                         n_items, counter);                                                     \
+    else                                                                                        \
+      hipLaunchKernelGGL((k_batch_map<C, false>), dim3(blocks), dim3(256), 0, st, scans, items, \
+                         n_items, counter);                                                     \
+    return hipGetLastError();                                                                   \
   }
   // every tile shape the autotuner may choose: RM in {1, 2, 4}
   DD_LAUNCH_BATCH_MAP(4)
   DD_LAUNCH_BATCH_MAP(2)
   DD_LAUNCH_BATCH_MAP(1)
 #undef DD_LAUNCH_BATCH_MAP
-#undef DD_LAUNCH_ONE
   return hipErrorInvalidValue;
 }
 

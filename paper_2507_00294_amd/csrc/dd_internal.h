@@ -158,14 +158,16 @@ struct OutFlag {
   int64_t base;
 };
 
-// Reduction work of a batch: one entry per (scan, query).
+// Reduction work of a batch: one entry per (scan, query), FP64 maps apart
+// (dd_gauss.h).
 struct BatchReduce {
   const double* partial;
   const int32_t* tile_slots;  // arrival: slots per tile; map: nullptr
   int32_t n_slots;            // map: slots of the single time
   int32_t tile;               // arrival tile width
   int64_t n;                  // outputs
-  int64_t out_off;            // first output in the flat index space
+  int64_t out_off;            // first of its outputs among the reductions'
+  int64_t flag_off;           // first output in the call's flat output index
   double* out;
   double pref;
   OutFlag scan_flag;          // the scan's own word (index: its output index)

@@ -533,20 +533,18 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
 }
 
 // ---------------------------------------------------------------------------
-// Map query.  Pixel pix = tile * 64 R + R lane + r at (X0 + u DX, Y0 + v DY),
-// u = pix % W, v = pix / W, all at the item's time; visit v = K - n.
-// LAT: pixel and probe coordinates are exact small dyadic numbers, so the
-// three-operation a = |e|^2 + |p|^2 - 2 e.p is exact; otherwise a is formed
-// from the differences (relative error ~1e-7, no cancellation).
-template <bool LAT, int R>
+// Map query, mixed precision (FP64 maps: dd_gauss.hip).  Pixel pix = tile * 64 R
+// + R lane + r at (X0 + u DX, Y0 + v DY), u = pix % W, v = pix / W, all at the
+// item's time; visit v = K - n.  Pixel and probe coordinates are exact small
+// dyadic numbers (other grids run in FP64), so the three-operation a = |e|^2 +
+// |p|^2 - 2 e.p is exact.
+template <int R>
 __device__ __forceinline__ float map_a32(const float4& p, const float (&ex)[R], const float (&ey)[R],
                                          const float (&ee)[R], int r) {
-  if (LAT) return __builtin_fmaf(ex[r], p.x, __builtin_fmaf(ey[r], p.y, ee[r] + p.z));
-  const float dx = __builtin_fmaf(0.5f, p.x, ex[r]), dy = __builtin_fmaf(0.5f, p.y, ey[r]);
-  return __builtin_fmaf(dy, dy, dx * dx);
+  return __builtin_fmaf(ex[r], p.x, __builtin_fmaf(ey[r], p.y, ee[r] + p.z));
 }
 
-template <int M, int R, int U, bool LAT>
+template <int M, int R, int U>
 __device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const float4* __restrict__ pos,
                                           const float* __restrict__ rows, const float (&ex)[R],
                                           const float (&ey)[R], const float (&ee)[R],
@@ -575,7 +573,7 @@ __device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const float
       for (int s = 0; s < U; ++s) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
-          qv[r][s] = series_row32_q<M>(map_a32<LAT, R>(pc[s], ex, ey, ee, r), cur[s], t[r][s]);
+          qv[r][s] = series_row32_q<M>(map_a32<R>(pc[s], ex, ey, ee, r), cur[s], t[r][s]);
       }
       // Groups of four lags in lag order, each summed by an explicit chain
       // of fused multiply-adds: the arithmetic of a pixel is then the same
@@ -602,7 +600,7 @@ __device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const float
     const Row row = fetch_row<M>(rows, n);
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      acc[r] += (double)series_row32<M>(map_a32<LAT, R>(p, ex, ey, ee, r), row);
+      acc[r] += (double)series_row32<M>(map_a32<R>(p, ex, ey, ee, r), row);
   }
 }
 
@@ -618,7 +616,7 @@ __device__ __forceinline__ float4* map_r1_stage() {
   return stage;
 }
 
-template <int M, bool LAT>
+template <int M>
 __device__ __forceinline__ void map_far32_r1(int lo, int hi, int64_t K, const float4* __restrict__ pos,
                                              const float* __restrict__ rows, const float (&ex)[1],
                                              const float (&ey)[1], const float (&ee)[1],
@@ -645,7 +643,7 @@ __device__ __forceinline__ void map_far32_r1(int lo, int hi, int64_t K, const fl
     const float4* d = st + (buf * 64 + j) * 3;
     const float4 u = d[0], v = d[1], p = d[2];
     const RowA row{u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-    return series_f32a_q<M>(map_a32<LAT, 1>(p, ex, ey, ee, 0), row, t);
+    return series_f32a_q<M>(map_a32<1>(p, ex, ey, ee, 0), row, t);
   };
   float4 r0, r1, pp;
   fetch(lo, r0, r1, pp);
@@ -680,41 +678,24 @@ __device__ __forceinline__ void map_far32_r1(int lo, int hi, int64_t K, const fl
   }
 }
 
-template <int M, int R>
-__device__ __forceinline__ void map_far64(int lo, int hi, int64_t K, const double2* __restrict__ pos,
-                                          const double* __restrict__ rows, const double (&ex)[R],
-                                          const double (&ey)[R], double (&acc)[R]) {
-  for (int n = lo; n < hi; ++n) {
-    const double2 p = ldc(pos + (K - n));
-    const double* row = rows + (int64_t)n * kRow64;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const double dx = ex[r] - p.x, dy = ey[r] - p.y;
-      double t;
-      const double q = series_f64_q<M>(fma(dy, dy, dx * dx), row, t);
-      acc[r] = fma(t, q, acc[r]);  // explicit: the same for every tile width
-    }
-  }
-}
-
-template <int R, int U, bool LAT>
+template <int R, int U>
 __device__ __forceinline__ void map_far32_u(int M, int lo, int hi, int64_t K,
                                             const float4* __restrict__ pos,
                                             const float* __restrict__ rows, const float (&ex)[R],
                                             const float (&ey)[R], const float (&ee)[R],
                                             double (&acc)[R]) {
   switch (M) {
-    case 0: map_far32<0, R, U, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 1: map_far32<1, R, U, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 2: map_far32<2, R, U, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 3: map_far32<3, R, U, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 4: map_far32<4, R, U, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 5: map_far32<5, R, U, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    default: map_far32<6, R, U, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    case 0: map_far32<0, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    case 1: map_far32<1, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    case 2: map_far32<2, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    case 3: map_far32<3, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    case 4: map_far32<4, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    case 5: map_far32<5, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    default: map_far32<6, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
   }
 }
 
-template <int R, bool LAT>
+template <int R>
 __device__ __forceinline__ void map_far32_seg(int M, int lo, int hi, int64_t K,
                                               const float4* __restrict__ pos,
                                               const float* __restrict__ rows, const float (&ex)[R],
@@ -726,109 +707,62 @@ __device__ __forceinline__ void map_far32_seg(int M, int lo, int hi, int64_t K,
   // tile width.
   if constexpr (R == 1) {
     switch (M) {
-      case 0: map_far32_r1<0, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
-      case 1: map_far32_r1<1, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
-      case 2: map_far32_r1<2, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
-      case 3: map_far32_r1<3, LAT>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
+      case 0: map_far32_r1<0>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
+      case 1: map_far32_r1<1>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
+      case 2: map_far32_r1<2>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
+      case 3: map_far32_r1<3>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
       default: break;
     }
     const int mid = lo + ((hi - lo) & ~7);
-    map_far32_u<R, 8, LAT>(M, lo, mid, K, pos, rows, ex, ey, ee, acc);
+    map_far32_u<R, 8>(M, lo, mid, K, pos, rows, ex, ey, ee, acc);
     lo = mid;
   }
-  map_far32_u<R, 4, LAT>(M, lo, hi, K, pos, rows, ex, ey, ee, acc);
+  map_far32_u<R, 4>(M, lo, hi, K, pos, rows, ex, ey, ee, acc);
 }
 
 template <int R>
-__device__ __forceinline__ void map_far64_seg(int M, int lo, int hi, int64_t K,
-                                              const double2* __restrict__ pos,
-                                              const double* __restrict__ rows, const double (&ex)[R],
-                                              const double (&ey)[R], double (&acc)[R]) {
-#define DD_CASE(k) \
-  case k: map_far64<k, R>(lo, hi, K, pos, rows, ex, ey, acc); break;
-  switch (M) {
-    DD_CASE(0) DD_CASE(1) DD_CASE(2) DD_CASE(3) DD_CASE(4) DD_CASE(5) DD_CASE(6) DD_CASE(7)
-    DD_CASE(8) DD_CASE(9) DD_CASE(10) DD_CASE(11) DD_CASE(12) DD_CASE(13) DD_CASE(14)
-    DD_CASE(15) DD_CASE(16)
-    default: map_far64<17, R>(lo, hi, K, pos, rows, ex, ey, acc); break;
-  }
-#undef DD_CASE
-}
-
-template <int R, bool MIXED>
 __device__ __forceinline__ void do_map(const MapItem& item, const MapTime& tm,
-                                       const void* __restrict__ pos_v,
+                                       const float2* __restrict__ pos,
                                        const float4* __restrict__ pos4,
                                        const double* __restrict__ rows64,
                                        const float* __restrict__ rows32, double X0, double Y0,
-                                       double DX, double DY, int W, int H, bool lattice,
+                                       double DX, double DY, int W, int H,
                                        double* __restrict__ partial) {
   const int lane = threadIdx.x & 63;
   const int64_t npix = (int64_t)W * H;
   const int64_t p0 = (int64_t)item.tile * (64 * R) + (int64_t)R * lane;
-  double pxd[R], pyd[R], acc[R];
+  double acc[R];
+  float ex[R], ey[R], ee[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int64_t pix = min(p0 + r, npix - 1);
-    pxd[r] = X0 + (double)(pix % W) * DX;
-    pyd[r] = Y0 + (double)(pix / W) * DY;
+    ex[r] = (float)(X0 + (double)(pix % W) * DX);
+    ey[r] = (float)(Y0 + (double)(pix / W) * DY);
+    ee[r] = __builtin_fmaf(ey[r], ey[r], ex[r] * ex[r]);
     acc[r] = 0.0;
   }
   const double* r64b = rows64 + tm.row_base * kRow64;
   const float* r32b = rows32 + tm.row_base * kRow32;
-  if (MIXED) {
-    const float2* pos = (const float2*)pos_v;
-    float ex[R], ey[R], ee[R];
+  if (item.near) {
+    for (int n = item.n_lo; n < item.n_hi; ++n) {
+      const float2 p = ldc(pos + (tm.K - n));
+      const float* r32 = r32b + (int64_t)n * kRow32;
+      const double* r64 = r64b + (int64_t)n * kRow64;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      ex[r] = (float)pxd[r];
-      ey[r] = (float)pyd[r];
-      ee[r] = __builtin_fmaf(ey[r], ey[r], ex[r] * ex[r]);
-    }
-    if (item.near) {
-      for (int n = item.n_lo; n < item.n_hi; ++n) {
-        const float2 p = ldc(pos + (tm.K - n));
-        const float* r32 = r32b + (int64_t)n * kRow32;
-        const double* r64 = r64b + (int64_t)n * kRow64;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const float dx = ex[r] - p.x, dy = ey[r] - p.y;
-          const float a = __builtin_fmaf(dy, dy, dx * dx);
-          if (a * ldc(r32 + kR32_C) <= kThr32)
-            acc[r] += (double)series_f32<kMNear32>(a, r32);
-          else if (a * ldc(r32 + kR32_RHI) <= kCull32Log2)
-            acc[r] += phi_general_mixed(a, r64, r32);
-        }
-      }
-    } else {
-      for (int M = tm.bounds.m_max; M >= 0; --M) {
-        int lo, hi;
-        seg_range(tm.bounds, M, item.n_lo, item.n_hi, lo, hi);
-        if (lo >= hi) continue;
-        if (lattice)
-          map_far32_seg<R, true>(M, lo, hi, tm.K, pos4, r32b, ex, ey, ee, acc);
-        else
-          map_far32_seg<R, false>(M, lo, hi, tm.K, pos4, r32b, ex, ey, ee, acc);
+      for (int r = 0; r < R; ++r) {
+        const float dx = ex[r] - p.x, dy = ey[r] - p.y;
+        const float a = __builtin_fmaf(dy, dy, dx * dx);
+        if (a * ldc(r32 + kR32_C) <= kThr32)
+          acc[r] += (double)series_f32<kMNear32>(a, r32);
+        else if (a * ldc(r32 + kR32_RHI) <= kCull32Log2)
+          acc[r] += phi_general_mixed(a, r64, r32);
       }
     }
   } else {
-    const double2* pos = (const double2*)pos_v;
-    if (item.near) {
-      for (int n = item.n_lo; n < item.n_hi; ++n) {
-        const double2 p = ldc(pos + (tm.K - n));
-        const double* r64 = r64b + (int64_t)n * kRow64;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const double dx = pxd[r] - p.x, dy = pyd[r] - p.y;
-          acc[r] += phi_general_f64(fma(dy, dy, dx * dx), r64);
-        }
-      }
-    } else {
-      for (int M = tm.bounds.m_max; M >= 0; --M) {
-        int lo, hi;
-        seg_range(tm.bounds, M, item.n_lo, item.n_hi, lo, hi);
-        if (lo < hi) map_far64_seg<R>(M, lo, hi, tm.K, pos, r64b, pxd, pyd, acc);
-      }
+    for (int M = tm.bounds.m_max; M >= 0; --M) {
+      int lo, hi;
+      seg_range(tm.bounds, M, item.n_lo, item.n_hi, lo, hi);
+      if (lo < hi) map_far32_seg<R>(M, lo, hi, tm.K, pos4, r32b, ex, ey, ee, acc);
     }
   }
   double* out = partial + (tm.slot_base + item.slot) * npix;

@@ -34,10 +34,10 @@ struct ArrivalLaunch {
 };
 hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st);
 
+// A mixed-precision map call (FP64: dd_gauss.h).
 struct MapLaunch {
-  const void* pos;          // float2 / double2 probe positions by visit
+  const float2* pos;        // probe positions by visit
   const float4* pos4;       // (-2x, -2y, x^2+y^2, 0) by visit
-  bool lattice;             // pixel/probe coordinates exact small dyadics
   const double* rows64;
   const float* rows32;
   const MapItem* items;
@@ -47,7 +47,6 @@ struct MapLaunch {
   int32_t W, H;
   double* partial;          // [slots][W*H]
   int R;
-  bool mixed;
 };
 hipError_t launch_map(const MapLaunch& L, hipStream_t st);
 
@@ -65,14 +64,14 @@ hipError_t launch_reduce_map(const double* partial, const MapTime* times, int32_
                              int64_t npix, double pref, double* out, OutFlag fl, hipStream_t st);
 
 // Persistent batched launches (arrival far-region items; arrival near-band
-// items; map far-region or near-band items); `counter` is zeroed on the
-// stream first.
+// items; mixed-precision map far-region or near-band items); `counter` is
+// zeroed on the stream first.
 hipError_t launch_batch(const BatchScan* scans, const BatchItem* items, int32_t n_items,
                         int* counter, int R, bool mixed, hipStream_t st);
 hipError_t launch_batch_near(const BatchScan* scans, const BatchItem* items, int32_t n_items,
                              int* counter, int RN, bool mixed, hipStream_t st);
 hipError_t launch_batch_map(const BatchScan* scans, const BatchItem* items, int32_t n_items,
-                            int* counter, int RM, bool mixed, bool near, hipStream_t st);
+                            int* counter, int RM, bool near, hipStream_t st);
 // Also marks each non-finite result in its scan's word and in `fl` (index:
 // the flat output index of the call).
 hipError_t launch_reduce_batch(const BatchReduce* reds, int32_t n_red, int64_t total, OutFlag fl,

@@ -2,8 +2,8 @@
 //
 // The hot path is the all-pairs sum of Eq. 6 (Sec. II): every evaluation
 // point adds the pair term of Eqs. 1-4 for every visit that started before it.
-// It is a transcendental pair sum, not a contraction, so it runs on the vector
-// ALUs (no MFMA).  The design keeps everything that depends only on the lag
+// At scattered points and in FP32 it is a transcendental pair sum, not a
+// contraction, so it runs on the vector ALUs (no MFMA).  The design keeps everything that depends only on the lag
 // (time since a visit started) uniform across a wavefront:
 //
 //  * arrival query (evaluation point = visit j at its start time): a wave owns
@@ -11,9 +11,10 @@
 //    pair (j, n) is visit j - n, so all 64 R pairs of one step share one lag
 //    row (read into SGPRs) and each lane slides a window of 2R - 1 probe
 //    positions (R loads per R^2 pairs);
-//  * map query (evaluation points = pixels at one time): a wave owns 64 R
-//    pixels and walks the visits; probe position and lag row are both
-//    uniform (SGPR operands), only the pixel coordinates live in VGPRs.
+//  * map query in mixed precision (evaluation points = pixels at one time): a
+//    wave owns 64 R pixels and walks the visits; probe position and lag row are
+//    both uniform (SGPR operands), only the pixel coordinates live in VGPRs.
+//    FP64 maps are matrix products (dd_gauss.hip).
 //
 // Lags split into a near band (per-pair choice between the series and the
 // direct E1 difference) and a far region where every pair of the tile is in
@@ -76,20 +77,19 @@ __global__ void __launch_bounds__(256) k_arrival_near(const void* __restrict__ p
   do_arrival_near<R, MIXED>(items[it], pos_v, rows64, rows32, V, partial, pstride, pj0);
 }
 
-template <int R, bool MIXED>
-__global__ void __launch_bounds__(256) k_map(const void* __restrict__ pos_v,
+template <int R>
+__global__ void __launch_bounds__(256) k_map(const float2* __restrict__ pos,
                                              const float4* __restrict__ pos4,
                                              const double* __restrict__ rows64,
                                              const float* __restrict__ rows32,
                                              const MapItem* __restrict__ items, int n_items,
                                              const MapTime* __restrict__ times, double X0, double Y0,
-                                             double DX, double DY, int W, int H, int lattice,
+                                             double DX, double DY, int W, int H,
                                              double* __restrict__ partial) {
   const int it = blockIdx.x * 4 + wave_id();
   if (it >= n_items) return;
   const MapItem item = items[it];
-  do_map<R, MIXED>(item, times[item.m], pos_v, pos4, rows64, rows32, X0, Y0, DX, DY, W, H,
-                   lattice != 0, partial);
+  do_map<R>(item, times[item.m], pos, pos4, rows64, rows32, X0, Y0, DX, DY, W, H, partial);
 }
 
 // ---------------------------------------------------------------------------
@@ -243,15 +243,10 @@ hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st) {
 hipError_t launch_map(const MapLaunch& L, hipStream_t st) {
   if (L.n_items <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)((L.n_items + 3) / 4);
-#define DD_LAUNCH_MAP(RR)                                                                       \
-  if (L.mixed)                                                                                  \
-    hipLaunchKernelGGL((k_map<RR, true>), dim3(blocks), dim3(256), 0, st, L.pos, L.pos4,       \
-                       L.rows64, L.rows32, L.items, L.n_items, L.times, L.X0, L.Y0, L.DX, L.DY, \
-                       L.W, L.H, L.lattice ? 1 : 0, L.partial);                                 \
-  else                                                                                          \
-    hipLaunchKernelGGL((k_map<RR, false>), dim3(blocks), dim3(256), 0, st, L.pos, L.pos4,      \
-                       L.rows64, L.rows32, L.items, L.n_items, L.times, L.X0, L.Y0, L.DX, L.DY, \
-                       L.W, L.H, L.lattice ? 1 : 0, L.partial);
+#define DD_LAUNCH_MAP(RR)                                                                        \
+  hipLaunchKernelGGL((k_map<RR>), dim3(blocks), dim3(256), 0, st, L.pos, L.pos4, L.rows64,       \
+                     L.rows32, L.items, L.n_items, L.times, L.X0, L.Y0, L.DX, L.DY, L.W, L.H,    \
+                     L.partial);
   switch (L.R) {
     case 1: DD_LAUNCH_MAP(1) break;
     case 2: DD_LAUNCH_MAP(2) break;

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/dd.h"
+#include "dd_gauss.h"
 #include "dd_internal.h"
 #include "dd_kernels.h"
 #include "dd_runtime.h"
@@ -518,7 +519,41 @@ dd_status run_arrival_range(dd_scan* s, bool mixed, int64_t j0, int64_t j1, doub
                       s->partial.as<double>(), out_dev, fl, st, true);
 }
 
-// Map query.  Times are snapped to a dwell boundary when within 8 ulp.
+// A time in dwells, snapped to a dwell boundary when within 8 ulp of it.
+double time_in_dwells(const dd_scan* s, double t) {
+  const double th = t / s->tau_v, r = std::rint(th);
+  return std::fabs(th - r) <= 8.0 * 2.220446049250313e-16 * std::max(1.0, std::fabs(th)) ? r : th;
+}
+
+// The FP64 map of scan s on pixels (X0 + u DX, Y0 + v DY), pitch units, at th
+// dwells (see dd_gauss.h); its split, buffers and flags are the caller's.
+GaussJob gauss_job(const dd_scan* s, double th, double X0, double Y0, double DX, double DY,
+                   int32_t w, int32_t h) {
+  GaussJob j{};
+  j.pos = s->pos64.as<double2>() + kPosPad;
+  j.K = std::floor(th);
+  j.f = th - j.K;
+  // visit K has just started, or starts at this time (no contribution yet)
+  const double last = std::min((double)(s->V - 1), j.f > 0.0 ? j.K : j.K - 1.0);
+  j.i_last = (int64_t)last;
+  j.n = j.i_last + 1;
+  // rounded once: a Gaussian's relative error is its exponent, up to 745,
+  // times that of its width
+  const long double sh = (long double)s->desc.sigma_m / s->desc.pitch_m;
+  j.s2 = (double)(2.0L * sh * sh);
+  j.k4 = 4.0 * s->kappa;
+  j.is2 = 1.0;
+  j.X0 = X0;
+  j.Y0 = Y0;
+  j.DX = DX;
+  j.DY = DY;
+  j.W = w;
+  j.H = h;
+  j.pref = s->pref;
+  return j;
+}
+
+// Mixed-precision map query.
 struct MapGroup {
   double f;
   int64_t n_first, n_last;  // rows needed
@@ -540,7 +575,6 @@ struct MapPlan {
   double X0 = 0, Y0 = 0, DX = 0, DY = 0;
   double pairs = 0, flops = 0;
   int R = 1;
-  bool lattice = false;
 };
 
 // Pixel coordinates (pitch units) are multiples of 2^-q for some q <= 8 and
@@ -560,12 +594,11 @@ bool grid_is_lattice(double X0, double Y0, double DX, double DY, int w, int h, i
   return false;
 }
 
-// Plans a map query.  With int_rows, every time must lie on a dwell boundary
+// Plans a mixed-precision map query.  With int_rows, every time must lie on a dwell boundary
 // at or before the end of the scan, and rows are taken from the scan's
 // integer-lag table (row n at offset n) instead of a per-call table.
-void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, bool mixed,
-              int R, int64_t Kmap, bool int_rows, MapPlan& P, bool sort_items = true,
-              bool count = true) {
+void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, int R,
+              int64_t Kmap, bool int_rows, MapPlan& P, bool sort_items = true, bool count = true) {
   const int64_t npix = (int64_t)g->w * g->h;
   const double p = s->desc.pitch_m;
   P.X0 = g->x0_m / p;
@@ -583,8 +616,6 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
   const double my = std::max({std::fabs(ya), std::fabs(yb), std::fabs(ya - (s->desc.ny - 1)),
                               std::fabs(yb - (s->desc.ny - 1))});
   const double a_max = mx * mx + my * my;
-  const double thr = mixed ? (double)kThr32 : kThr64;
-  P.lattice = grid_is_lattice(P.X0, P.Y0, P.DX, P.DY, g->w, g->h, s->desc.nx, s->desc.ny);
 
   std::vector<MapTime>& times = P.times;
   times.assign(n_t, MapTime{});
@@ -593,9 +624,7 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
   std::map<double, int> gid;
   std::vector<int64_t> nlo(n_t);
   for (int m = 0; m < n_t; ++m) {
-    double th = t_s[m] / s->tau_v;
-    const double r = std::rint(th);
-    if (std::fabs(th - r) <= 8.0 * 2.220446049250313e-16 * std::max(1.0, std::fabs(th))) th = r;
+    const double th = time_in_dwells(s, t_s[m]);
     const double K = std::floor(th);
     const double f = th - K;
     times[m].K = (int64_t)K;
@@ -618,9 +647,9 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
   P.total_rows = 0;
   P.jobs.clear();
   for (auto& G : groups) {
-    G.kf = first_row_below(thr, a_max, mixed ? kCullX32 : kCullX64, G.f, s->kappa, s->s2, 1,
+    G.kf = first_row_below((double)kThr32, a_max, kCullX32, G.f, s->kappa, s->s2, 1,
                            std::max<int64_t>(G.n_last, 1));
-    G.bounds = degree_bounds(a_max, G.f, s->kappa, s->s2, G.kf, 1, mixed);
+    G.bounds = degree_bounds(a_max, G.f, s->kappa, s->s2, G.kf, 1, true);
     const int64_t span = std::max<int64_t>(0, G.n_last - G.n_first + 1);
     if (int_rows) {
       G.alloc_off = 0;
@@ -685,14 +714,14 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
     if (count) {
       P.pairs += (double)npix * (double)(near_hi - nlo[m]);
       P.flops += (double)npix * (double)(near_hi - nlo[m]) *
-                 series_flops(mixed ? kMNear32 : kM64, mixed);
+                 series_flops(kMNear32, true);
     }
     for (int64_t lo = std::max(kf, nlo[m]); lo <= K; lo += Kc, ++c) {
       const int64_t hi = std::min<int64_t>(lo + Kc, K + 1);
       for (int64_t t = 0; t < n_tiles; ++t)
         far.push_back(MapItem{(int32_t)t, m, (int32_t)lo, (int32_t)hi, (int32_t)np + c, 0, 0, 0});
       if (count)
-        count_segments(times[m].bounds, lo, hi, mixed,
+        count_segments(times[m].bounds, lo, hi, true,
                        [&](int64_t a, int64_t e) { return (double)npix * (double)(e - a); },
                        P.pairs, P.flops);
     }
@@ -712,6 +741,55 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
   P.items.insert(P.items.end(), far.begin(), far.end());
 }
 
+// FP64 maps: one job per time.  The jobs go up in the thread's pinned buffer,
+// asynchronously; the next call on the thread waits for that copy.
+dd_status run_map64(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, double* out_dev,
+                    const OutFlag& fl, hipStream_t st) {
+  const double p = s->desc.pitch_m;
+  const int64_t npix = (int64_t)g->w * g->h;
+  const GaussShape shape = gauss_shape(g->w, g->h, s->V, n_t);
+  RangeStage& G = g_range;
+  const size_t bytes = sizeof(GaussJob) * (size_t)n_t;
+  DD_HIP(s->aux2.ensure(bytes), "device allocation");
+  if (G.pending) DD_HIP(hipEventSynchronize(G.copied), "event synchronize");
+  G.pending = false;
+  DD_HIP(G.host.ensure(bytes), "pinned host allocation");
+  GaussJob* jobs = static_cast<GaussJob*>(G.host.p);
+  int64_t slots = 0, items = 0;
+  double pairs = 0;
+  for (int32_t m = 0; m < n_t; ++m) {
+    GaussJob& j = jobs[m];
+    j = gauss_job(s, time_in_dwells(s, t_s[m]), g->x0_m / p, g->y0_m / p, g->dx_m / p,
+                  g->dy_m / p, g->w, g->h);
+    gauss_split(j, shape);
+    j.partial = nullptr;
+    j.out = out_dev + m * npix;
+    j.fl = fl;
+    j.fl.base += m * npix;
+    slots += j.n_chunks;
+    items = std::max(items, (int64_t)j.tiles * j.n_chunks);
+    pairs += (double)npix * (double)j.n;
+  }
+  DD_HIP(s->partial.ensure(sizeof(double) * (size_t)slots * (size_t)npix), "device allocation");
+  double* part = s->partial.as<double>();
+  for (int32_t m = 0; m < n_t; ++m) {
+    jobs[m].partial = part;
+    part += jobs[m].n_chunks * npix;
+  }
+  if (!G.copied) DD_HIP(hipEventCreateWithFlags(&G.copied, hipEventDisableTiming), "event creation");
+  DD_HIP(hipMemcpyAsync(s->aux2.p, jobs, bytes, hipMemcpyHostToDevice, st), "host-to-device copy");
+  DD_HIP(hipEventRecord(G.copied, st), "event record");
+  G.pending = true;
+  const GaussJob* d_jobs = s->aux2.as<GaussJob>();
+  ProfToken tm = prof_begin("map", st);
+  DD_HIP(launch_gauss_map(d_jobs, n_t, items, shape.F, false, st), "map launch");
+  prof_end(tm, st, pairs, pairs * kGaussFlops);
+  ProfToken tq = prof_begin("reduce", st);
+  DD_HIP(launch_gauss_reduce(d_jobs, n_t, npix, st), "map reduce launch");
+  prof_end(tq, st, 0, 0);
+  return DD_OK;
+}
+
 dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, bool mixed,
                   double* out_dev, const OutFlag& fl, hipStream_t st) {
   dd_status rc = s->prepare(st);
@@ -719,16 +797,14 @@ dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, 
   // The FP32 bulk takes the squared distance a exactly only when pixels and
   // probes share a dyadic lattice.  Off it, a rounded a costs a term about
   // x1 * 1e-7 of relative accuracy, above the mixed bound where distant
-  // probes (large x1) dominate a pixel, so such grids run on the FP64 kernels.
-  if (mixed) {
-    const double p = s->desc.pitch_m;
-    if (!grid_is_lattice(g->x0_m / p, g->y0_m / p, g->dx_m / p, g->dy_m / p, g->w, g->h,
-                         s->desc.nx, s->desc.ny))
-      mixed = false;
-  }
-  const int R = mixed ? tune().map_R_mixed : tune().map_R_f64;
+  // probes (large x1) dominate a pixel, so such grids run in FP64.
+  const double p = s->desc.pitch_m;
+  if (!mixed || !grid_is_lattice(g->x0_m / p, g->y0_m / p, g->dx_m / p, g->dy_m / p, g->w, g->h,
+                                 s->desc.nx, s->desc.ny))
+    return run_map64(s, g, t_s, n_t, out_dev, fl, st);
+  const int R = tune().map_R_mixed;
   MapPlan P;
-  plan_map(s, g, t_s, n_t, mixed, R, tune().map_K, false, P);
+  plan_map(s, g, t_s, n_t, R, tune().map_K, false, P);
   DD_HIP(s->maprows64.ensure(sizeof(double) * kRow64 * std::max<int64_t>(P.total_rows, 1)),
          "device allocation");
   DD_HIP(s->maprows32.ensure(sizeof(float) * kRow32 * std::max<int64_t>(P.total_rows, 1)),
@@ -747,10 +823,8 @@ dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, 
   DD_HIP(s->partial.ensure(sizeof(double) * (size_t)P.slots * (size_t)P.npix),
          "device allocation");
   MapLaunch L{};
-  L.pos = mixed ? (const void*)(s->pos32.as<float2>() + kPosPad)
-                : (const void*)(s->pos64.as<double2>() + kPosPad);
+  L.pos = s->pos32.as<float2>() + kPosPad;
   L.pos4 = s->pos4.as<float4>() + kPosPad;
-  L.lattice = P.lattice;
   L.rows64 = s->maprows64.as<double>();
   L.rows32 = s->maprows32.as<float>();
   L.items = s->aux2.as<MapItem>();
@@ -760,7 +834,6 @@ dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, 
   L.W = g->w; L.H = g->h;
   L.partial = s->partial.as<double>();
   L.R = R;
-  L.mixed = mixed;
   ProfToken tm = prof_begin("map", st);
   DD_HIP(launch_map(L, st), "map launch");
   prof_end(tm, st, P.pairs, P.flops);
@@ -830,6 +903,7 @@ struct BatchScratch {
   std::vector<BatchScan> h_scans;
   std::vector<BatchItem> h_items, h_near_items, h_map_items, h_map_near_items, h_tmp;
   std::vector<BatchReduce> h_reds;
+  std::vector<GaussJob> h_gauss;  // FP64 final maps, in scan order
   std::vector<int32_t> h_slots;
   std::vector<uint64_t> h_ka, h_kb;
   hipEvent_t done = nullptr, copied = nullptr;  // kept until the process ends
@@ -907,10 +981,10 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
   const int R = mixed ? tune().arr_R_mixed : tune().arr_R_f64;
   const int RN = mixed ? tune().arr_RN_mixed : tune().arr_RN_f64;
   const bool want_arr = (mask & DD_Q_ARRIVAL) != 0, want_map = (mask & DD_Q_FINAL_AT_PROBES) != 0;
-  // map tile width: the tuned one, narrowed while a narrower tile still covers
+  // mixed map tile width: the tuned one, narrowed while a narrower tile still covers
   // the largest map of the call (a one-row map fills one 64-pixel tile)
-  int RM = mixed ? tune().map_R_mixed : tune().map_R_f64;
-  if (want_map) {
+  int RM = tune().map_R_mixed;
+  if (want_map && mixed) {
     int64_t most = 0;
     for (int32_t k = 0; k < n; ++k) {
       const MapSel q = resolve_sel(scans[k], sel);
@@ -956,8 +1030,9 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
   map_near_items.clear();
   reds.clear();
   all_slots.clear();
+  W.h_gauss.clear();
   std::vector<int64_t> arr_off(n, 0), map_off(n, 0), slot_off(n, 0), out_off(n, 0);
-  int64_t partial_total = 0, out_total = 0;
+  int64_t partial_total = 0, out_total = 0, reds_total = 0;
   double pairs = 0, flops = 0;
   ProfToken trw = prof_begin("lag_rows", st);
   std::vector<OutFlag> scan_flag(n);
@@ -1038,20 +1113,36 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
       };
       add(near_items, an, kBatchArrNear, 64.0 * RN * near_w);
       add(items, af, kBatchArrFar, 64.0 * R);
-      reds.push_back(BatchReduce{nullptr, nullptr, 0, 64 * R, s->V, out_total, nullptr, s->pref,
+      reds.push_back(BatchReduce{nullptr, nullptr, 0, 64 * R, s->V, reds_total, out_total,
+                                 nullptr, s->pref,
                                  scan_flag[k]});
+      reds_total += s->V;
       out_total += s->V;
       pairs += C.pairs;
       flops += C.flops;
     }
-    if (want_map) {
+    if (want_map && !mixed) {  // the final map as in run_map64
+      GaussJob j = gauss_job(s, (double)s->V, q.x0, q.y0, q.step, q.step, q.w, q.h);
+      gauss_split(j, gauss_shape(q.w, q.h, s->V, 1));
+      const int64_t npix = (int64_t)q.w * q.h;
+      map_off[k] = partial_total;
+      partial_total += j.n_chunks * npix;
+      j.fl = scan_flag[k];
+      j.fl.base = want_arr ? s->V : 0;
+      j.fl2 = call_flag;
+      j.fl2.base = out_total;
+      W.h_gauss.push_back(j);
+      out_total += npix;
+      pairs += (double)npix * (double)s->V;
+      flops += (double)npix * (double)s->V * kGaussFlops;
+    } else if (want_map) {
       const double pm = s->desc.pitch_m;
       dd_grid g{q.x0 * pm, q.y0 * pm, q.step * pm, q.step * pm, q.w, q.h};
       const double t_end = (double)s->V * s->tau_v;
       const int64_t Kmap = tune().map_K;
       dd_scan::BatchMapPlan* C = nullptr;
       for (dd_scan::BatchMapPlan& c : s->bmap)
-        if (c.ok && c.mixed == mixed && c.R == RM && c.sel.x0 == q.x0 && c.sel.y0 == q.y0 &&
+        if (c.ok && c.R == RM && c.sel.x0 == q.x0 && c.sel.y0 == q.y0 &&
             c.sel.step == q.step && c.sel.w == q.w && c.sel.h == q.h && c.K == Kmap &&
             (c.counted || !count))
           C = &c;
@@ -1059,8 +1150,7 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
         C = s->bmap[0].used <= s->bmap[1].used ? &s->bmap[0] : &s->bmap[1];
         MapPlan MP;
         C->ok = false;
-        plan_map(s, &g, &t_end, 1, mixed, RM, Kmap, true, MP, false, count);
-        C->mixed = mixed;
+        plan_map(s, &g, &t_end, 1, RM, Kmap, true, MP, false, count);
         C->R = RM;
         C->sel = q;
         C->K = Kmap;
@@ -1077,7 +1167,7 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
       B.map_time = C->time;
       map_off[k] = partial_total;
       partial_total += C->slots * C->npix;
-      const double near_w = mixed ? 6.0 : 3.0;
+      const double near_w = 6.0;
       for (const MapItem& m : C->items) {
         const int64_t tile_pix = std::min<int64_t>(64 * RM, C->npix - (int64_t)m.tile * 64 * RM);
         const double cost = (double)(m.n_hi - m.n_lo) * tile_pix * (m.near ? near_w : 1.0);
@@ -1088,8 +1178,9 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
       }
       OutFlag mf = scan_flag[k];
       mf.base = want_arr ? s->V : 0;  // index into the scan's output
-      reds.push_back(BatchReduce{nullptr, nullptr, C->time.n_slots, 0, C->npix, out_total,
-                                 nullptr, s->pref, mf});
+      reds.push_back(BatchReduce{nullptr, nullptr, C->time.n_slots, 0, C->npix, reds_total,
+                                 out_total, nullptr, s->pref, mf});
+      reds_total += C->npix;
       out_total += C->npix;
       pairs += C->pairs;
       flops += C->flops;
@@ -1098,18 +1189,20 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
   if (W.pending) DD_HIP(hipStreamWaitEvent(st, W.done, 0), "stream wait");
   for (std::vector<BatchItem>* v : {&items, &near_items, &map_items, &map_near_items})
     sort_longest_first(*v, W.h_tmp, W.h_ka, W.h_kb);
-  // tables: scans, far/near arrival items, far/near map items, reductions, slots
+  // tables: scans, far/near arrival items, far/near map items, reductions,
+  // slots, FP64 maps
   struct Table {
     const void* src;
     size_t bytes, off;
   };
-  Table tab[7] = {{bs.data(), sizeof(BatchScan) * bs.size(), 0},
+  Table tab[8] = {{bs.data(), sizeof(BatchScan) * bs.size(), 0},
                   {items.data(), sizeof(BatchItem) * items.size(), 0},
                   {near_items.data(), sizeof(BatchItem) * near_items.size(), 0},
                   {map_items.data(), sizeof(BatchItem) * map_items.size(), 0},
                   {map_near_items.data(), sizeof(BatchItem) * map_near_items.size(), 0},
                   {reds.data(), sizeof(BatchReduce) * reds.size(), 0},
-                  {all_slots.data(), sizeof(int32_t) * all_slots.size(), 0}};
+                  {all_slots.data(), sizeof(int32_t) * all_slots.size(), 0},
+                  {W.h_gauss.data(), sizeof(GaussJob) * W.h_gauss.size(), 0}};
   size_t block_bytes = 0;
   for (Table& t : tab) {
     t.off = block_bytes;
@@ -1135,7 +1228,10 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
         o += scans[k]->V;
         ++r;
       }
-      if (want_map) {
+      if (want_map && !mixed) {
+        W.h_gauss[k].partial = part + map_off[k];
+        W.h_gauss[k].out = o;
+      } else if (want_map) {
         bs[k].map_partial = part + map_off[k];
         reds[r].partial = bs[k].map_partial;
         reds[r].out = o;
@@ -1143,6 +1239,9 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
       }
     }
   }
+  // FP64 maps by tile factor (each map writes its own partial sums and output)
+  std::stable_sort(W.h_gauss.begin(), W.h_gauss.end(),
+                   [](const GaussJob& a, const GaussJob& b) { return a.F > b.F; });
   if (W.copy_pending) DD_HIP(hipEventSynchronize(W.copied), "event synchronize");
   W.copy_pending = false;
   DD_HIP(W.host_block.ensure(block_bytes), "pinned host allocation");
@@ -1164,17 +1263,30 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
                            (int32_t)near_items.size(), W.counter.as<int>() + 1, RN, mixed, st),
          "batched near-band launch");
   DD_HIP(launch_batch_map(d_scans, (const BatchItem*)(blk + tab[3].off), (int32_t)map_items.size(),
-                          W.counter.as<int>() + 2, RM, mixed, false, st),
+                          W.counter.as<int>() + 2, RM, false, st),
          "batched map launch");
   DD_HIP(launch_batch_map(d_scans, (const BatchItem*)(blk + tab[4].off),
-                          (int32_t)map_near_items.size(), W.counter.as<int>() + 3, RM, mixed, true,
-                          st),
+                          (int32_t)map_near_items.size(), W.counter.as<int>() + 3, RM, true, st),
          "batched map near-band launch");
+  const GaussJob* d_gauss = (const GaussJob*)(blk + tab[7].off);
+  int64_t max_pixels = 0;
+  for (size_t k = 0, e; k < W.h_gauss.size(); k = e) {
+    int64_t most = 0;
+    for (e = k; e < W.h_gauss.size() && W.h_gauss[e].F == W.h_gauss[k].F; ++e) {
+      const GaussJob& j = W.h_gauss[e];
+      most = std::max(most, (int64_t)j.tiles * j.n_chunks);
+      max_pixels = std::max(max_pixels, (int64_t)j.W * j.H);
+    }
+    DD_HIP(launch_gauss_map(d_gauss + k, (int32_t)(e - k), most, W.h_gauss[k].F, false, st),
+           "batched map launch");
+  }
   prof_end(tb, st, pairs, flops);
   ProfToken tq = prof_begin("reduce", st);
   DD_HIP(launch_reduce_batch((const BatchReduce*)(blk + tab[5].off), (int32_t)reds.size(),
-                             out_total, call_flag, st),
+                             reds_total, call_flag, st),
          "batched reduce launch");
+  DD_HIP(launch_gauss_reduce(d_gauss, (int32_t)W.h_gauss.size(), max_pixels, st),
+         "batched map reduce launch");
   prof_end(tq, st, 0, 0);
   if (!W.done) DD_HIP(hipEventCreateWithFlags(&W.done, hipEventDisableTiming), "event creation");
   DD_HIP(hipEventRecord(W.done, st), "event record");

@@ -60,6 +60,9 @@ inline double series_flops(int M, bool mixed) {
 // fused multiply-add into the partial sum: 9).
 inline double plain_flops(int M) { return series_flops(M, true) - 4.0; }
 constexpr double kFoldFlops = 9.0;
+// FP64 maps: one multiply-add per pair and Gaussian (dd_gauss.hip); records
+// count the two Gaussians that most pairs take.
+constexpr double kGaussFlops = 4.0;
 
 // A grow-only device buffer.
 struct DevBuf {
@@ -93,7 +96,8 @@ struct TuneParams {
   int arr_R_mixed = 4, arr_R_f64 = 2;      // far-region tile: 64 R visits
   int arr_RN_mixed = 2, arr_RN_f64 = 2;    // near-band tile
   int arr_K_mixed = 2048, arr_K_f64 = 1024;   // lags per far work item
-  int map_R_mixed = 4, map_R_f64 = 1;
+  int map_R_mixed = 4;
+  int map_R_f64 = 1;  // kept for the cache file's format: FP64 maps take no tuned shape
   int map_K = 4096;
 };
 TuneParams& tune();
@@ -175,9 +179,9 @@ struct dd_scan {
   dd::DevBuf sur;
   int sur_state = 0;
   // Plans of the batched solve, kept on the handle: they depend only on the
-  // scan, the precision and the tile shape (and, for the map, its probe
-  // sub-grid), so a scan solved again skips the host planning.  Two map
-  // plans are kept (the whole final map and one sub-grid, as the
+  // scan, the precision and the tile shape (for the map, mixed precision
+  // only: the tile shape and its probe sub-grid), so a scan solved again
+  // skips the host planning.  Two map plans are kept (the whole final map and one sub-grid, as the
   // surrogate's judge uses).
   struct BatchArrPlan {
     bool ok = false, mixed = false, counted = false;
@@ -188,7 +192,7 @@ struct dd_scan {
     double pairs = 0, flops = 0;
   } barr;
   struct BatchMapPlan {
-    bool ok = false, mixed = false, counted = false;
+    bool ok = false, counted = false;
     int R = 0;
     dd::MapSel sel{};
     int64_t K = 0, slots = 0, npix = 0;

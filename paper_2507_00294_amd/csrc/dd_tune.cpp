@@ -222,29 +222,33 @@ dd_status dd_autotune(const char* cache_path) {
     return fail(DD_ENOMEM, "device allocation failed");
   }
   FreeGuard fg2{mout};
-  for (int mixed = 1; mixed >= 0; --mixed) {
-    double bms = 1e30;
-    for (int R : {1, 2, 4})
-      for (int K : {1024, 4096, 16384}) {
-        TuneParams t = best;
-        (mixed ? t.map_R_mixed : t.map_R_f64) = R;
-        if (mixed) t.map_K = K;
-        if (!mixed && K != best.map_K) continue;
-        tune() = t;
-        double ms = 0;
-        rc = time_ms([&] { return dd_damage_map(mid.s, &g, &t_end, 1, mixed ? DD_MIXED : DD_FP64,
-                                                mout, 1, st); },
-                     st, 3, ms);
-        if (rc != DD_OK) {
-          tune() = saved;
-          return rc;
-        }
-        if (ms < bms) {
-          bms = ms;
-          best = t;
-        }
+  auto time_map = [&](dd_precision p, double& ms) {
+    return time_ms([&] { return dd_damage_map(mid.s, &g, &t_end, 1, p, mout, 1, st); }, st, 3, ms);
+  };
+  double bms = 1e30;
+  for (int R : {1, 2, 4})
+    for (int K : {1024, 4096, 16384}) {
+      TuneParams t = best;
+      t.map_R_mixed = R;
+      t.map_K = K;
+      tune() = t;
+      double ms = 0;
+      rc = time_map(DD_MIXED, ms);
+      if (rc != DD_OK) {
+        tune() = saved;
+        return rc;
       }
-    best_ms[mixed ? 2 : 3] = bms;
+      if (ms < bms) {
+        bms = ms;
+        best = t;
+      }
+    }
+  best_ms[2] = bms;
+  // FP64 maps have no tuned shape; their time is recorded beside the others
+  rc = time_map(DD_FP64, best_ms[3]);
+  if (rc != DD_OK) {
+    tune() = saved;
+    return rc;
   }
   tune() = best;
   if (!write_cache(path.c_str(), best, best_ms))

@@ -1,5 +1,5 @@
-// dd_visit_rows.h -- the series of the per-visit rows that the map query over
-// a general visit list builds on the device (see k_visit_map).
+// dd_visit_rows.h -- the series of the per-visit rows that the mixed map query
+// over a general visit list builds on the device (see k_visit_map).
 //
 // At one query time a visit has fixed b0 (its b of Eqs. 1-2 over sigma^2 at
 // the end of the beam-on time seen from t), db and b1 = b0 + db, so its pair
@@ -76,8 +76,8 @@ __host__ __device__ inline int series_degree(double dx, double target) {
   return M;
 }
 
-// Per-term truncation targets of the map rows: FP64 kTrunc64; mixed 2e-8,
-// below the FP32 evaluation's own ~1e-7.
+// Per-term truncation target of the map rows, below the FP32 evaluation's own
+// ~1e-7.
 constexpr double kTrunc32 = 2e-8;
 
 }  // namespace dd

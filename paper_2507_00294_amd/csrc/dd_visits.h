@@ -63,8 +63,8 @@ struct VisItem {
   int64_t nv;
 };
 
-// Partial sums of every item: arrival (map = false) or map points, in FP64
-// or with the FP32 near form (mixed).
+// Partial sums of every item: arrival (map = false) in FP64 or with the FP32
+// near form (mixed), or map points (mixed only; FP64 maps: dd_gauss.h).
 hipError_t launch_visit_pairs(bool map, bool mixed, const VisList* lists, const VisTile* tiles,
                               const VisItem* items, int64_t n_items, double* partial,
                               hipStream_t st);

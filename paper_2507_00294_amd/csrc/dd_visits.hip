@@ -7,13 +7,14 @@
 //   E1(x1) - E1(x0) = integral of e^-u / u over [x1, x0]
 // and, at a = 0, ln(b1/b0) (Eqs. 3-4).
 //
-// Maps (k_visit_map): every pixel of a map shares its time, so each visit
-// has one b0 and db for the whole map and its term is a series in dx with
-// coefficients of the visit alone (dd_visit_rows.h), built once per visit
-// and tile, as the scan's lag rows are once per lag.
+// Maps in mixed precision (k_visit_map): every pixel of a map shares its time,
+// so each visit has one b0 and db for the whole map and its term is a series in
+// dx with coefficients of the visit alone (dd_visit_rows.h), built once per
+// visit and tile, as the scan's lag rows are once per lag.  FP64 maps are sums
+// of separable Gaussians (dd_gauss.hip).
 //
 // Arrival (k_visit_arrival): every pair has its own b0 and db; the bulk of
-// a long list takes a short polynomial (see bulk_term), the rest the
+// a long list takes a short polynomial (see bulk_f), the rest the
 // general form, one of four per pair:
 //   * x1 > 745: zero (both E1 values below the double range);
 //   * dx > 1: the difference of the two E1 values (series or continued
@@ -33,7 +34,6 @@
 
 #include <algorithm>
 #include <cstdint>
-#include <type_traits>
 
 #include "dd_device.h"
 #include "dd_visit_rows.h"
@@ -198,7 +198,7 @@ __device__ __forceinline__ double pair_term(bool active, double x1, double dx, d
 }
 
 // ---------------------------------------------------------------------------
-// Map query: per-visit series rows.
+// Map query, mixed precision: per-visit series rows (FP64 maps: dd_gauss.hip).
 //
 // All pixels of a map share its time, so a visit's b0, db and b1 are the
 // same for every pixel and its pair term is the series of dd_visit_rows.h
@@ -214,11 +214,10 @@ __device__ __forceinline__ double pair_term(bool active, double x1, double dx, d
 // dx_max = min(a_max c, cull q) (a_max over the tile's bounding box; a pair
 // beyond the cull, x1 > cull, has dx = x1 q > cull q), gives the degree by
 // series_degree at min(dx_max, threshold).  A row with dx_max above the
-// series threshold (1 in FP64, 0.25 mixed) is general: a wave with a
-// contributing pair above the threshold takes the general form (pair_term)
-// for that visit.  Pairs beyond the cull stay in the series with dx clamped
-// to the row's bound, where exp(-x1) makes them vanish (below 2^-1074 in
-// FP64, e^-100 in FP32).  A visit beyond the cull for the whole box of the
+// series threshold (0.25) is careful: its contributing pairs above the
+// threshold take the difference of the two E1 values.  Pairs beyond the cull
+// stay in the series with dx clamped to the row's bound, where exp(-x1) makes
+// them vanish (below e^-100).  A visit beyond the cull for the whole box of the
 // tile is skipped.
 
 constexpr int kMapWaves = 4;            // waves per block, one item each
@@ -228,12 +227,11 @@ constexpr int kMapPix = kVisTile / 64;   // pixels per lane
 constexpr int kRowNotStarted = -1;  // the visit starts at or after t
 constexpr int kRowCulled = -2;      // x1 > cull for the whole tile
 constexpr int kRowCareful = 32;     // clamps, and the per-pair far form
-constexpr int kRowP0 = 64;          // mixed: exponent correction through P_0
+constexpr int kRowP0 = 64;          // exponent correction through P_0
 // A lean row: every pixel of the tile has dx <= threshold and
-// x1 log2(e) <= kLeanY (FP64: 2^-y by exp2_lean without a clamp; mixed: y
-// converts to a finite FP32 value), so its pairs need no clamp.
-template <bool MIXED>
-constexpr double kLeanY = MIXED ? 1e30 : 1000.0;
+// x1 log2(e) <= kLeanY (y converts to a finite FP32 value), so its pairs need
+// no clamp.
+constexpr double kLeanY = 1e30;
 
 // 1/k (k = 1 .. 63) and (-1)^m / m! (m = 0 .. 23), in constant memory.
 struct RowConst {
@@ -252,29 +250,23 @@ __constant__ RowConst kRowConst = [] {
 }();
 
 // A visit's row for one tile, in the wave's LDS block.
-template <bool MIXED>
 struct MapRow {
-  using T = typename std::conditional<MIXED, float, double>::type;
   double vx, vy;  // visit position (m)
   double R;       // log2(e) / (b1 sigma^2): x1 log2(e) = a_m R
   double rb1s;    // 1 / (b1 sigma^2): x1 = a_m rb1s
-  T c2;           // db / (b0 b1 sigma^2): dx = a_m c2
-  T zmax;         // dx bound of the series, min(dx_max, threshold)
-  T p0n;          // -ln2 P_0 (mixed)
+  float c2;       // db / (b0 b1 sigma^2): dx = a_m c2
+  float zmax;     // dx bound of the series, min(dx_max, threshold)
+  float p0n;      // -ln2 P_0
   int32_t kind;
-  T P[(MIXED ? kM32 : kM64) + 1];
+  float P[kM32 + 1];
 };
 
 // Row of visit v for the tile with bounding box (xlo, xhi, ylo, yhi) at
 // time t, written into `row` (LDS) field by field; returns its kind.
-template <bool MIXED>
 __device__ __forceinline__ int build_map_row(const double4 v, double t, double th4, double is2,
-                                             const double4 box, MapRow<MIXED>* row) {
-  constexpr int MM = MIXED ? kM32 : kM64;
-  constexpr double thr = MIXED ? (double)kThr32 : kThr64;
-  constexpr double target = MIXED ? kTrunc32 : kTrunc64;
-  constexpr double cull = MIXED ? kCullX32 : kCullX64;
-  using T = typename MapRow<MIXED>::T;
+                                             const double4 box, MapRow* row) {
+  constexpr int MM = kM32;
+  constexpr double thr = (double)kThr32, cull = kCullX32;
   row->vx = v.x;
   row->vy = v.y;
   const double dt = t - v.z;
@@ -294,8 +286,8 @@ __device__ __forceinline__ int build_map_row(const double4 v, double t, double t
   const double R = rb1s * kLog2e;
   row->R = R;
   row->rb1s = rb1s;
-  row->c2 = (T)c2;
-  row->zmax = (T)zmax;
+  row->c2 = (float)c2;
+  row->zmax = (float)zmax;
   // P_m = (-1)^m q J_m / m! with J_m by the regime of q (dd_visit_rows.h)
   if (q <= 0.25) {
     // downwards from J_N = 1/(N+1), constants from the table (a loop, not
@@ -306,7 +298,7 @@ __device__ __forceinline__ int build_map_row(const double4 v, double t, double t
 #pragma unroll 1
     for (int m = N - 1; m >= 0; --m) {
       j = fma(-q, j, kRowConst.inv[m + 1]);
-      if (m <= MM) row->P[m] = (T)(kRowConst.sfac[m] * q * j);
+      if (m <= MM) row->P[m] = (float)(kRowConst.sfac[m] * q * j);
     }
   } else if (q <= 1.0) {
     // 24-node Gauss-Legendre rule on [0, 1], one coefficient at a time
@@ -321,7 +313,7 @@ __device__ __forceinline__ int build_map_row(const double4 v, double t, double t
         for (int i = 0; i < m; ++i) um *= u;
         J = fma(g.w[k] / fma(q, u, 1.0), um, J);
       }
-      row->P[m] = (T)(kRowConst.sfac[m] * q * J);
+      row->P[m] = (float)(kRowConst.sfac[m] * q * J);
     }
   } else {
     // upwards from J_0 = ln(1 + q)/q
@@ -329,34 +321,20 @@ __device__ __forceinline__ int build_map_row(const double4 v, double t, double t
     double j = log1p(q) * rq;
 #pragma unroll 1
     for (int m = 0; m <= MM; ++m) {
-      row->P[m] = (T)(kRowConst.sfac[m] * q * j);
+      row->P[m] = (float)(kRowConst.sfac[m] * q * j);
       j = (kRowConst.inv[m + 1] - j) * rq;
     }
   }
   int kind;
-  if (!(amax * c2 <= thr && amax * R <= kLeanY<MIXED>)) {
+  if (!(amax * c2 <= thr && amax * R <= kLeanY)) {
     kind = kRowCareful | MM;
   } else {
-    kind = series_degree<MM>(zmax, target);
-    // mixed: the P_0 form of the exponent correction (as in the scan's
-    // bulk) where dx <= 0.01: its neglected part is below |eps| dx / 2 < 1e-8
-    if (MIXED && kind <= 3 && zmax <= 0.01) kind |= kRowP0;
+    kind = series_degree<MM>(zmax, kTrunc32);
+    // the P_0 form of the exponent correction (as in the scan's bulk) where dx <= 0.01: its neglected part is below |eps| dx / 2 < 1e-8
+    if (kind <= 3 && zmax <= 0.01) kind |= kRowP0;
   }
-  row->p0n = (T)(-kLn2 * (double)row->P[0]);
+  row->p0n = (float)(-kLn2 * (double)row->P[0]);
   return row->kind = kind;
-}
-
-// 2^-y for 0 <= y <= 1000 in double precision: -y = m + h, m = rint(-y), 2^h
-// by the degree-9 Chebyshev interpolant of exp2_neg9 (relative error below
-// 1.9e-14), without exp2_neg9's clamp.
-__device__ __forceinline__ double exp2_lean(double y) {
-  constexpr Exp2Cheb<9> e{};
-  const double m = __builtin_rint(-y);
-  const double h = -y - m;
-  double p = e.c[9];
-#pragma unroll
-  for (int k = 8; k >= 0; --k) p = fma(p, h, e.c[k]);
-  return __builtin_ldexp(p, (int)m);
 }
 
 __device__ __forceinline__ void map_am(const double (&px)[kMapPix], const double (&py)[kMapPix],
@@ -369,47 +347,38 @@ __device__ __forceinline__ void map_am(const double (&px)[kMapPix], const double
 }
 
 // The lean rows of a stage (bit j of `mask`: row j), all at degree M (the
-// stage's highest; a higher degree is as accurate), the terms added to acc
-// (mixed: each term in FP32, converted).
-template <int M, bool MIXED, bool P0C>
-__device__ __forceinline__ void map_lean_rows(const MapRow<MIXED>* __restrict__ rows,
+// stage's highest; a higher degree is as accurate), each term in FP32, converted
+// and added to acc.
+template <int M, bool P0C>
+__device__ __forceinline__ void map_lean_rows(const MapRow* __restrict__ rows,
                                               uint64_t mask, const double (&px)[kMapPix],
                                               const double (&py)[kMapPix],
                                               double (&acc)[kMapPix]) {
-  using T = typename MapRow<MIXED>::T;
   while (mask) {
     const int j = __builtin_ctzll(mask);
     mask &= mask - 1;
-    const MapRow<MIXED>* r = rows + j;
+    const MapRow* r = rows + j;
     double am[kMapPix];
     map_am(px, py, r->vx, r->vy, am);
     const double R = r->R;
-    const T c2 = r->c2;
-    T P[M + 1];
+    const float c2 = r->c2;
+    float P[M + 1];
 #pragma unroll
     for (int m = 0; m <= M; ++m) P[m] = r->P[m];
 #pragma unroll
     for (int k = 0; k < kMapPix; ++k) {
-      if constexpr (MIXED) {
-        const double y = am[k] * R;
-        const float yh = (float)y;
-        const float yl = (float)(y - (double)yh);
-        const float z = (float)am[k] * c2;
-        float s = P[M];
+      const double y = am[k] * R;
+      const float yh = (float)y;
+      const float yl = (float)(y - (double)yh);
+      const float z = (float)am[k] * c2;
+      float s = P[M];
 #pragma unroll
-        for (int m = M - 1; m >= 0; --m) s = __builtin_fmaf(s, z, P[m]);
-        if constexpr (P0C)
-          s = __builtin_fmaf(r->p0n, yl, s);
-        else
-          s = __builtin_fmaf(s, yl * (float)(-kLn2), s);
-        acc[k] += (double)(__builtin_amdgcn_exp2f(-yh) * s);
-      } else {
-        const double z = am[k] * c2;
-        double s = P[M];
-#pragma unroll
-        for (int m = M - 1; m >= 0; --m) s = fma(s, z, P[m]);
-        acc[k] = fma(exp2_lean(am[k] * R), s, acc[k]);
-      }
+      for (int m = M - 1; m >= 0; --m) s = __builtin_fmaf(s, z, P[m]);
+      if constexpr (P0C)
+        s = __builtin_fmaf(r->p0n, yl, s);
+      else
+        s = __builtin_fmaf(s, yl * (float)(-kLn2), s);
+      acc[k] += (double)(__builtin_amdgcn_exp2f(-yh) * s);
     }
   }
 }
@@ -420,19 +389,17 @@ __device__ __forceinline__ void map_lean_rows(const MapRow<MIXED>* __restrict__ 
 // those lanes: the two E1 values differ by more than a factor e^thr there,
 // so the difference keeps its digits (the general form of the scan's lag
 // rows, phi_general_*).
-template <bool MIXED>
-__device__ __forceinline__ void map_careful_rows(const MapRow<MIXED>* __restrict__ rows,
+__device__ __forceinline__ void map_careful_rows(const MapRow* __restrict__ rows,
                                                  uint64_t mask, const double (&px)[kMapPix],
                                                  const double (&py)[kMapPix],
                                                  const bool (&live)[kMapPix],
                                                  double (&acc)[kMapPix]) {
-  constexpr int MM = MIXED ? kM32 : kM64;
-  constexpr double thr = MIXED ? (double)kThr32 : kThr64;
-  constexpr double cull = MIXED ? kCullX32 : kCullX64;
+  constexpr int MM = kM32;
+  constexpr double thr = (double)kThr32, cull = kCullX32;
   while (mask) {
     const int j = __builtin_ctzll(mask);
     mask &= mask - 1;
-    const MapRow<MIXED>* r = rows + j;
+    const MapRow* r = rows + j;
     double am[kMapPix];
     map_am(px, py, r->vx, r->vy, am);
     // pixel slot by slot, not unrolled (rare rows, long code)
@@ -448,30 +415,18 @@ __device__ __forceinline__ void map_careful_rows(const MapRow<MIXED>* __restrict
         }
       const double x1 = a * r->rb1s, dx = a * (double)r->c2;
       const bool far = l && dx > thr && x1 <= cull;
-      double term;
-      if constexpr (MIXED) {
-        const double y = fmin(a * r->R, 4096.0);
-        const float yh = (float)y;
-        const float yl = (float)(y - (double)yh);
-        const float z = fminf((float)a * r->c2, r->zmax);
-        float s = r->P[MM];
+      const double y = fmin(a * r->R, 4096.0);
+      const float yh = (float)y;
+      const float yl = (float)(y - (double)yh);
+      const float z = fminf((float)a * r->c2, r->zmax);
+      float s = r->P[MM];
 #pragma unroll
-        for (int m = MM - 1; m >= 0; --m) s = __builtin_fmaf(s, z, r->P[m]);
-        s = __builtin_fmaf(s, yl * (float)(-kLn2), s);
-        term = (double)(__builtin_amdgcn_exp2f(-yh) * s);
-      } else {
-        const double z = fmin(dx, r->zmax);
-        double s = r->P[MM];
-#pragma unroll
-        for (int m = MM - 1; m >= 0; --m) s = fma(s, z, r->P[m]);
-        term = exp2_neg<11>(a * r->R) * s;
-      }
+      for (int m = MM - 1; m >= 0; --m) s = __builtin_fmaf(s, z, r->P[m]);
+      s = __builtin_fmaf(s, yl * (float)(-kLn2), s);
+      double term = (double)(__builtin_amdgcn_exp2f(-yh) * s);
       if (__ballot(far) && far) {
         const double x0 = x1 + dx;
-        if constexpr (MIXED)
-          term = e1_mixed(x1) - (x0 > 745.0 ? 0.0 : e1_mixed(x0));
-        else
-          term = e1_f64(x1) - (x0 > 745.0 ? 0.0 : e1_f64(x0));
+        term = e1_mixed(x1) - (x0 > 745.0 ? 0.0 : e1_mixed(x0));
       }
 #pragma unroll
       for (int i = 0; i < kMapPix; ++i)
@@ -482,53 +437,30 @@ __device__ __forceinline__ void map_careful_rows(const MapRow<MIXED>* __restrict
 
 #define DD_LEAN(MV, P0) \
   case MV:              \
-    map_lean_rows<(MV), MIXED, P0>(rows, lean, px, py, acc); \
+    map_lean_rows<(MV), P0>(rows, lean, px, py, acc); \
     break;
 
 // One stage of rows: the lean rows (bits of `lean`) at degree M with the
 // P_0 correction form if every one allows it (p0), then the careful rows.
-template <bool MIXED>
-__device__ __forceinline__ void map_stage(const MapRow<MIXED>* __restrict__ rows, uint64_t lean,
-                                          int M, bool p0, uint64_t careful,
-                                          const double (&px)[kMapPix],
-                                          const double (&py)[kMapPix],
-                                          const bool (&live)[kMapPix], double (&acc)[kMapPix]) {
+__device__ __forceinline__ void map_stage(const MapRow* __restrict__ rows, uint64_t lean, int M,
+                                          bool p0, uint64_t careful, const double (&px)[kMapPix],
+                                          const double (&py)[kMapPix], const bool (&live)[kMapPix],
+                                          double (&acc)[kMapPix]) {
   if (lean) {
-    if constexpr (MIXED) {
-      if (p0) {
-        switch (M) {
-          DD_LEAN(0, true) DD_LEAN(1, true) DD_LEAN(2, true)
-          default: map_lean_rows<3, MIXED, true>(rows, lean, px, py, acc);
-        }
-      } else {
-        switch (M) {
-          DD_LEAN(0, false) DD_LEAN(1, false) DD_LEAN(2, false)
-          DD_LEAN(3, false) DD_LEAN(4, false) DD_LEAN(5, false)
-          default: map_lean_rows<6, MIXED, false>(rows, lean, px, py, acc);
-        }
+    if (p0) {
+      switch (M) {
+        DD_LEAN(0, true) DD_LEAN(1, true) DD_LEAN(2, true)
+        default: map_lean_rows<3, true>(rows, lean, px, py, acc);
       }
     } else {
-      // degrees rounded up to 1, 2, 3, 4, 6, 8, 11, 14, 17 (fewer variants
-      // keep the code small)
-      if (M <= 4) {
-        switch (M) {
-          DD_LEAN(0, false) DD_LEAN(1, false) DD_LEAN(2, false) DD_LEAN(3, false)
-          default: map_lean_rows<4, MIXED, false>(rows, lean, px, py, acc);
-        }
-      } else if (M <= 6) {
-        map_lean_rows<6, MIXED, false>(rows, lean, px, py, acc);
-      } else if (M <= 8) {
-        map_lean_rows<8, MIXED, false>(rows, lean, px, py, acc);
-      } else if (M <= 11) {
-        map_lean_rows<11, MIXED, false>(rows, lean, px, py, acc);
-      } else if (M <= 14) {
-        map_lean_rows<14, MIXED, false>(rows, lean, px, py, acc);
-      } else {
-        map_lean_rows<17, MIXED, false>(rows, lean, px, py, acc);
+      switch (M) {
+        DD_LEAN(0, false) DD_LEAN(1, false) DD_LEAN(2, false)
+        DD_LEAN(3, false) DD_LEAN(4, false) DD_LEAN(5, false)
+        default: map_lean_rows<6, false>(rows, lean, px, py, acc);
       }
     }
   }
-  if (careful) map_careful_rows<MIXED>(rows, careful, px, py, live, acc);
+  if (careful) map_careful_rows(rows, careful, px, py, live, acc);
 }
 #undef DD_LEAN
 
@@ -544,18 +476,16 @@ __device__ __forceinline__ void wave_lds_sync() {
 // Wave w of block b takes items 4 b + w, 4 b + w + 4 gridDim.x, ...  The
 // item's visits go 64 at a time: lane j builds visit j's row in the wave's
 // LDS block; then the stage's lean rows are taken by one loop at their
-// highest degree and its careful rows by another.  Mixed: held to 168 VGPRs
-// (3 waves per SIMD instead of 2; the few spilled values are outside the
+// highest degree and its careful rows by another.  Held to 168 VGPRs (3 waves per SIMD instead of 2; the few spilled values are outside the
 // lean loop).
-template <bool MIXED>
 __global__ __launch_bounds__(64 * kMapWaves)
-__attribute__((amdgpu_waves_per_eu(MIXED ? 3 : 1, 8))) void k_visit_map(
+__attribute__((amdgpu_waves_per_eu(3, 8))) void k_visit_map(
     const VisList* __restrict__ lists, const VisTile* __restrict__ tiles,
     const VisItem* __restrict__ items, int64_t n_items, double* __restrict__ partial) {
-  __shared__ MapRow<MIXED> s_rows[kMapWaves][64];
+  __shared__ MapRow s_rows[kMapWaves][64];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  MapRow<MIXED>* rows = s_rows[w];
+  MapRow* rows = s_rows[w];
   for (int64_t it = (int64_t)blockIdx.x * kMapWaves + w; it < n_items;
        it += (int64_t)gridDim.x * kMapWaves) {
     const VisItem item = items[it];
@@ -591,7 +521,7 @@ __attribute__((amdgpu_waves_per_eu(MIXED ? 3 : 1, 8))) void k_visit_map(
       const int nk = left < 64 ? (int)left : 64;
       wave_lds_sync();  // the previous stage's rows are no longer read
       int mykind = kRowNotStarted;
-      if (lane < nk) mykind = build_map_row<MIXED>(L.vis[v0 + lane], t, th4, is2, box, rows + lane);
+      if (lane < nk) mykind = build_map_row(L.vis[v0 + lane], t, th4, is2, box, rows + lane);
       // visits are in start order: the started ones are a prefix
       const int ns = __popcll(__ballot(mykind != kRowNotStarted));
       if (ns < nk) done = true;
@@ -602,7 +532,7 @@ __attribute__((amdgpu_waves_per_eu(MIXED ? 3 : 1, 8))) void k_visit_map(
       const uint64_t careful = __ballot(mykind >= 0 && (mykind & kRowCareful));
       int M = 0;
       if (lean) {
-        constexpr int MM = MIXED ? kM32 : kM64;
+        constexpr int MM = kM32;
         const int mine = is_lean ? (mykind & 31) : 0;
         for (int m = MM; m > 0; --m)
           if (__ballot(mine >= m)) {
@@ -610,8 +540,8 @@ __attribute__((amdgpu_waves_per_eu(MIXED ? 3 : 1, 8))) void k_visit_map(
             break;
           }
       }
-      const bool p0 = MIXED && !__ballot(is_lean && !(mykind & kRowP0));
-      map_stage<MIXED>(rows, lean, M, p0, careful, px, py, live, acc);
+      const bool p0 = !__ballot(is_lean && !(mykind & kRowP0));
+      map_stage(rows, lean, M, p0, careful, px, py, live, acc);
     }
     const int64_t pb = tile.pbase + (int64_t)item.slot * kVisTile;
 #pragma unroll
@@ -700,7 +630,7 @@ __device__ __forceinline__ double bulk_term64_lds(double x1, double u, double v,
     for (int n = deg[m] - 1; n >= 0; --n) cm = cm * u + bc[m * kBulkStride + n];
     g = (m == 6) ? cm : g * v + cm;
   }
-  // exp2_lean with the interpolant's coefficients from bc
+  // 2^-y, y <= 1000 log2(e), by exp2_neg9's interpolant without its clamp
   const double y = x1 * kLog2e;
   const double mm = __builtin_rint(-y);
   const double h = -y - mm;
@@ -710,21 +640,15 @@ __device__ __forceinline__ double bulk_term64_lds(double x1, double u, double v,
   return __builtin_ldexp(p, (int)mm) * (u * g);
 }
 
-// The bulk term e^{-x1} u F(u, v) (x1 <= cull).
-template <bool MIXED>
-__device__ __forceinline__ double bulk_term(double x1, double u, double v) {
-  if constexpr (MIXED) {
-    const double y = x1 * kLog2e;
-    const float yh = (float)y;
-    const float yl = (float)(y - (double)yh);
-    const float uf = (float)u, vf = (float)v;
-    float g = bulk_f<float, 4, 4, 3, 3, 1>(uf, vf);
-    g = __builtin_fmaf(g, yl * (float)(-kLn2), g);
-    return (double)(__builtin_amdgcn_exp2f(-yh) * (uf * g));
-  } else {
-    const double g = bulk_f<double, 7, 5, 5, 5, 4, 3, 2, 1>(u, v);
-    return exp2_lean(x1 * kLog2e) * (u * g);
-  }
+// The mixed bulk term e^{-x1} u F(u, v) (x1 <= cull).
+__device__ __forceinline__ double bulk_term32(double x1, double u, double v) {
+  const double y = x1 * kLog2e;
+  const float yh = (float)y;
+  const float yl = (float)(y - (double)yh);
+  const float uf = (float)u, vf = (float)v;
+  float g = bulk_f<float, 4, 4, 3, 3, 1>(uf, vf);
+  g = __builtin_fmaf(g, yl * (float)(-kLn2), g);
+  return (double)(__builtin_amdgcn_exp2f(-yh) * (uf * g));
 }
 
 // One arrival pair (point at (px, py) at time pt, visit v): the quantities
@@ -757,7 +681,7 @@ struct ArrPair {
   __device__ __forceinline__ double bulk_value(const double* __restrict__ bc) const {
     double t;
     if constexpr (MIXED)
-      t = bulk_term<MIXED>(x1, u, w);
+      t = bulk_term32(x1, u, w);
     else
       t = bulk_term64_lds(x1, u, w, bc);
     return act ? t : 0.0;
@@ -788,7 +712,6 @@ __global__ __launch_bounds__(kVisTile)
 __attribute__((amdgpu_waves_per_eu(MIXED ? 1 : 3, 8))) void k_visit_arrival(
     const VisList* __restrict__ lists, const VisTile* __restrict__ tiles,
     const VisItem* __restrict__ items, int64_t n_items, double* __restrict__ partial) {
-  constexpr double cull = MIXED ? kCullX32 : kCullX64;
   __shared__ double4 s_v[kVisStage];
   __shared__ double s_bc[MIXED ? 1 : kBulkLds];
   const int lane = threadIdx.x;
@@ -875,10 +798,8 @@ hipError_t launch_visit_pairs(bool map, bool mixed, const VisList* lists, const 
   if (map) {
     const unsigned mb =
         (unsigned)std::min<int64_t>((n_items + kMapWaves - 1) / kMapWaves, 1 << 20);
-    if (mixed)
-      k_visit_map<true><<<mb, 64 * kMapWaves, 0, st>>>(lists, tiles, items, n_items, partial);
-    else
-      k_visit_map<false><<<mb, 64 * kMapWaves, 0, st>>>(lists, tiles, items, n_items, partial);
+    if (!mixed) return hipErrorInvalidValue;
+    k_visit_map<<<mb, 64 * kMapWaves, 0, st>>>(lists, tiles, items, n_items, partial);
     return hipGetLastError();
   }
   const unsigned blocks = (unsigned)std::min<int64_t>(n_items, 1 << 20);

@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "../../include/dd.h"
+#include "dd_gauss.h"
 #include "dd_runtime.h"
 #include "dd_visits.h"
 
@@ -118,6 +119,28 @@ struct dd_visits {
                    inv_sigma, th4, pref, fl};
   }
 
+  // The FP64 map on grid g at time t (split, buffers and flag: the caller's).
+  GaussJob map_job(const dd_grid& g, double t) const {
+    GaussJob j{};
+    j.pos = d_vis.as<double4>();
+    // the visits started before t are a prefix of the start order
+    j.n = std::lower_bound(vis.begin(), vis.end(), t,
+                           [](const double4& v, double x) { return v.z < x; }) - vis.begin();
+    j.i_last = j.n - 1;
+    j.t = t;
+    j.s2 = 2.0;
+    j.k4 = th4;
+    j.is2 = (double)(1.0L / ((long double)sigma * sigma));  // rounded once, as a scan's s2
+    j.X0 = g.x0_m;
+    j.Y0 = g.y0_m;
+    j.DX = g.dx_m;
+    j.DY = g.dy_m;
+    j.W = g.w;
+    j.H = g.h;
+    j.pref = pref;
+    return j;
+  }
+
   // Tiles of the arrival query (visits in start order), appended for list `list`.
   void arrival_tiles(int32_t list, std::vector<VisTile>& tiles) const {
     for (int64_t p0 = 0; p0 < n; p0 += kVisTile) {
@@ -165,7 +188,8 @@ struct VisScratch {
   std::vector<VisTile> h_tiles;
   std::vector<VisItem> h_items;
   std::vector<VisList> h_lists;
-  std::vector<const double*> h_times;  // maps: each list's times (host) and count
+  std::vector<GaussJob> h_gauss;       // FP64 maps
+  std::vector<const double*> h_times;  // mixed maps: each list's times (host) and count
   std::vector<int32_t> h_nt;
   HostStage stage;
   DevBuf d_stage, d_partial;
@@ -353,12 +377,100 @@ struct MapTiling {
   }
 };
 
-// Maps of lists[k] on grids[k] at times t_s[k][0 .. n_t[k]) into outs[k]
-// (device), all in the same launch groups; each list's tiles and items are
+// FP64 maps (dd_gauss.h) of lists[k], as run_maps: one job per list and time,
+// in launch groups of at most 2^25 partial sums (256 MiB) or one map.  A map's
+// split depends on its list and grid alone, so results depend neither on the
+// other times of a call nor on the other lists.
+dd_status launch_maps64(hipStream_t st) {
+  VisScratch& W = g_vis;
+  std::vector<GaussJob>& jobs = W.h_gauss;
+  if (W.inflight) {
+    VIS_HIP(hipEventSynchronize(W.done), "event synchronize");
+    W.inflight = false;
+  }
+  if (!W.done) VIS_HIP(hipEventCreateWithFlags(&W.done, hipEventDisableTiming), "event creation");
+  const size_t bytes = sizeof(GaussJob) * jobs.size();
+  int64_t sums = 0, max_pixels = 0;
+  double pairs = 0;
+  for (const GaussJob& j : jobs) {
+    const int64_t npix = (int64_t)j.W * j.H;
+    sums += j.n_chunks * npix;
+    max_pixels = std::max(max_pixels, npix);
+    pairs += (double)npix * (double)j.n;
+  }
+  VIS_HIP(W.stage.ensure(bytes), "pinned host allocation");
+  VIS_HIP(W.d_stage.ensure(bytes), "device allocation");
+  VIS_HIP(W.d_partial.ensure(sizeof(double) * sums), "device allocation");
+  double* part = W.d_partial.as<double>();
+  for (GaussJob& j : jobs) {
+    j.partial = part;
+    part += (int64_t)j.n_chunks * j.W * j.H;
+  }
+  std::stable_sort(jobs.begin(), jobs.end(),
+                   [](const GaussJob& a, const GaussJob& b) { return a.F > b.F; });
+  std::copy(jobs.begin(), jobs.end(), static_cast<GaussJob*>(W.stage.p));
+  W.inflight = true;
+  VIS_HIP(hipMemcpyAsync(W.d_stage.p, W.stage.p, bytes, hipMemcpyHostToDevice, st),
+          "host-to-device copy");
+  VIS_HIP(hipEventRecord(W.done, st), "event record");  // the stage is read; again after the launches
+  const GaussJob* d = W.d_stage.as<GaussJob>();
+  const ProfToken tok = prof_begin("k_visit_pairs", st);
+  for (size_t k = 0, e; k < jobs.size(); k = e) {
+    int64_t most = 0;
+    for (e = k; e < jobs.size() && jobs[e].F == jobs[k].F; ++e)
+      most = std::max(most, (int64_t)jobs[e].tiles * jobs[e].n_chunks);
+    VIS_HIP(launch_gauss_map(d + k, (int32_t)(e - k), most, jobs[k].F, true, st),
+            "visit map launch");
+  }
+  prof_end(tok, st, pairs, pairs * kGaussFlops);
+  VIS_HIP(launch_gauss_reduce(d, (int32_t)jobs.size(), max_pixels, st), "visit map reduce launch");
+  VIS_HIP(hipEventRecord(W.done, st), "event record");
+  return DD_OK;
+}
+
+dd_status run_maps64(dd_visits* const* lists, int32_t n, const dd_grid* grids,
+                     const double* const* t_s, const int32_t* n_t, double* const* outs,
+                     hipStream_t st) {
+  VisScratch& W = g_vis;
+  OutFlag fl;
+  dd_status rc = call_flag(st, fl);
+  if (rc != DD_OK) return rc;
+  std::vector<int64_t> off(n, 0);
+  W.h_gauss.clear();
+  int64_t sums = 0;
+  for (int32_t k = 0; k < n; ++k) {
+    const dd_grid& g = grids[k];
+    const dd_visits* v = lists[k];
+    const int64_t npix = (int64_t)g.w * g.h;
+    if (k > 0) off[k] = off[k - 1] + (int64_t)n_t[k - 1] * grids[k - 1].w * grids[k - 1].h;
+    const GaussShape shape = gauss_shape(g.w, g.h, v->n, 1);
+    for (int32_t m = 0; m < n_t[k]; ++m) {
+      GaussJob j = v->map_job(g, t_s[k][m]);
+      gauss_split(j, shape);
+      j.out = outs[k] + m * npix;
+      j.fl = fl;
+      j.fl.base = off[k] + m * npix;
+      if (!W.h_gauss.empty() && sums + j.n_chunks * npix > ((int64_t)1 << 25)) {
+        rc = launch_maps64(st);
+        if (rc != DD_OK) return rc;
+        W.h_gauss.clear();
+        sums = 0;
+      }
+      sums += j.n_chunks * npix;
+      W.h_gauss.push_back(j);
+    }
+  }
+  rc = launch_maps64(st);
+  if (rc != DD_OK) return rc;
+  return check_call_flag(fl, off, st);
+}
+
+// Mixed-precision maps of lists[k] on grids[k] at times t_s[k][0 .. n_t[k]) into
+// outs[k] (device), all in the same launch groups; each list's tiles and items are
 // planned exactly as for a call of its own (tiles time by time, blocks in
 // order), so the results do not depend on the batch.
 dd_status run_maps(dd_visits* const* lists, int32_t n, const dd_grid* grids,
-                   const double* const* t_s, const int32_t* n_t, bool mixed, double* const* outs,
+                   const double* const* t_s, const int32_t* n_t, double* const* outs,
                    hipStream_t st) {
   VisScratch& W = g_vis;
   std::vector<int64_t> npix(n), per(n), off(n, 0);
@@ -414,7 +526,7 @@ dd_status run_maps(dd_visits* const* lists, int32_t n, const dd_grid* grids,
       }
     }
     order_items(lists);
-    rc = launch_group(true, mixed, st);
+    rc = launch_group(true, true, st);
     if (rc != DD_OK) return rc;
   }
   return check_call_flag(fl, off, st);
@@ -543,7 +655,11 @@ dd_status dd_visits_batch_map(dd_visits* const* lists, int32_t n, const dd_grid*
     dd_status rc = lists[k]->prepare(st);
     if (rc != DD_OK) return rc;
   }
-  if (out_on_device) return run_maps(lists, n, grids, t_s, n_t, mixed, outs, st);
+  auto maps = [&](double* const* o) {
+    return mixed ? run_maps(lists, n, grids, t_s, n_t, o, st)
+                 : run_maps64(lists, n, grids, t_s, n_t, o, st);
+  };
+  if (out_on_device) return maps(outs);
   // host outputs: one device buffer for all maps, then a copy per list
   std::vector<int64_t> off(n + 1, 0);
   for (int32_t k = 0; k < n; ++k)
@@ -552,7 +668,7 @@ dd_status dd_visits_batch_map(dd_visits* const* lists, int32_t n, const dd_grid*
   VIS_HIP(tmp.ensure(sizeof(double) * off[n]), "device allocation");
   std::vector<double*> douts(n);
   for (int32_t k = 0; k < n; ++k) douts[k] = tmp.as<double>() + off[k];
-  dd_status rc = run_maps(lists, n, grids, t_s, n_t, mixed, douts.data(), st);
+  dd_status rc = maps(douts.data());
   if (rc == DD_OK) {
     for (int32_t k = 0; k < n && rc == DD_OK; ++k) {
       hipError_t e = hipMemcpyAsync(outs[k], douts[k], sizeof(double) * (off[k + 1] - off[k]),
