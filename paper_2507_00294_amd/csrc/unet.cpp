@@ -14,9 +14,9 @@
 // Kernels: 3x3 convolutions on BF16 MFMA over LDS halo tiles (unet_conv.hip)
 // for the forward pass and the data gradient -- the decoder's upsampling and
 // skip concatenation are read directly by its first convolution, and the
-// output head is reduced in the last convolution's epilogue -- im2col +
-// split-K MFMA GEMM for the weight gradient, FP32 elementwise kernels and Adam
-// (unet_kernels.hip).
+// output head is reduced in the last convolution's epilogue --, for the weight
+// gradient MFMA products over the same tiles (unet_wgrad.hip), FP32
+// elementwise kernels and Adam (unet_kernels.hip).
 // Predictions are judged by the exact kernels (an exact 8 x 8 probe sub-grid
 // per map) and replaced by the exact map when the judge rejects them or the
 // scan lies outside the training range.
@@ -40,7 +40,7 @@ namespace {
 constexpr int S = 64;        // input side
 constexpr int NPX = S * S;   // pixels per map
 constexpr int CIN = DD_SURROGATE_CHANNELS;
-constexpr int KPAD0 = 64;    // row length of the first layer's im2col (9 CIN padded)
+constexpr int KPAD0 = 64;    // row length of the first layer's weights (9 CIN padded)
 constexpr int kPredictChunk = 2048;  // maps per inference forward pass (per-map rate measured
                                      // 427k/s at 512, 492k/s at 1024, 511k/s at 2000 maps)
 // Probes the exact judge evaluates per predicted map: the 8 x 8 sub-grid of
@@ -69,9 +69,11 @@ struct dd_unet {
   int64_t step = 0;
   int capB = 0, capB_train = 0, B = 0;
   bool last_train = false;
-  DevBuf p1, p2, p3, y, col0;
-  DevBuf col, dA0, dA1, dZ, dZb, ds1, ds2, ds3, part, loss_map, norm_part, scale_norm;
-  size_t part_elems = 0;
+  DevBuf p1, p2, p3, y;
+  // backward pass: data gradients (two in turn, and those of the three
+  // concatenations, which the skip maps read again), dZ of the current layer,
+  // partial sums of every weight and bias gradient
+  DevBuf dA0, dA1, dcat1, dcat2, dcat3, dZb, part, loss_map, norm_part, scale_norm;
   // second stream (default priority, non-blocking) on which predict runs the
   // exact judge while the network runs on the caller's stream
   hipStream_t judge_stream = nullptr;
@@ -123,10 +125,33 @@ void build_layers(dd_unet& u) {
 
 int64_t M_of(const dd_unet& u, const Conv& c) { return (int64_t)u.B * c.H * c.H; }
 
-int wgrad_splits(const Conv& c, int64_t M) {
-  const int tiles = ((9 * c.ci + 63) / 64) * ((c.co + 63) / 64);
-  int64_t s = std::max<int64_t>(1, std::min<int64_t>(M / 256, 2048 / std::max(tiles, 1)));
-  return (int)std::min<int64_t>(s, 512);
+// Partial sums of all weight, bias and head gradients of a batch of B maps, in
+// the order of the layers: where each part starts (floats) and the sums to
+// form, with `part` their base.
+size_t grad_parts(const dd_unet& u, int B, float* part, nn::PartTable& tab,
+                  std::vector<size_t>& w_at, std::vector<size_t>& b_at) {
+  size_t at = 0;
+  tab.n = 0;
+  w_at.clear();
+  b_at.clear();
+  float* g = u.g.as<float>();
+  for (size_t l = 0; l < u.L.size(); ++l) {
+    const Conv& c = u.L[l];
+    const int64_t M = (int64_t)B * c.H * c.H, n = 9LL * c.ci * c.co;
+    const int sp = nn::wgrad_splits(M, c.ci, c.co);
+    w_at.push_back(at);
+    tab.l[tab.n++] = nn::PartDesc{part + at, n, n, sp, g + c.w_off};
+    at += (size_t)sp * n;
+    // the last layer's blocks also hold the head's sums: bias, then head
+    const bool head = l + 1 == u.L.size();
+    const int64_t len = head ? 2 * c.co + 1 : c.co;
+    b_at.push_back(at);
+    tab.l[tab.n++] = nn::PartDesc{part + at, len, c.co, nn::kActBlocks, g + c.b_off};
+    if (head)
+      tab.l[tab.n++] = nn::PartDesc{part + at + c.co, len, c.co + 1, nn::kActBlocks, g + u.head_w};
+    at += (size_t)nn::kActBlocks * len;
+  }
+  return at;
 }
 
 // Buffers of a forward pass over B maps; with `train`, also what the backward
@@ -147,30 +172,29 @@ dd_status ensure_capacity(dd_unet& u, int B, bool train) {
     u.capB = B;
   }
   if (train && B > u.capB_train) {
-    size_t max_mco = 0, max_mci = 0, max_col = 0, max_part = 0;
+    size_t max_mco = 0, max_mci = 0;
     UN_HIP(u.L[nL - 1].A.ensure(sizeof(__bf16) * M64 * u.L[nL - 1].co), "device allocation");
-    UN_HIP(u.col0.ensure(sizeof(__bf16) * M64 * KPAD0), "device allocation");
-    for (Conv& c : u.L) {
+    for (size_t l = 0; l < nL; ++l) {
+      Conv& c = u.L[l];
       const int64_t M = (int64_t)B * c.H * c.H;
       UN_HIP(c.Z.ensure(sizeof(float) * M * c.co), "device allocation");
       max_mco = std::max(max_mco, (size_t)(M * c.co));
-      max_mci = std::max(max_mci, (size_t)(M * c.ci));
-      if (c.ci % 32 == 0) max_col = std::max(max_col, (size_t)(M * 9 * c.ci));
-      const int sp = nn::gemm_splits(9 * c.ci, (int)M, wgrad_splits(c, M));
-      max_part = std::max(max_part, (size_t)sp * 9 * c.ci * c.co);
+      const bool cat = l == 8 || l == 10 || l == 12;  // their data gradients are dcat*
+      if (l > 0 && !cat) max_mci = std::max(max_mci, (size_t)(M * c.ci));
     }
-    const size_t dmax = std::max(max_mco, max_mci);
-    UN_HIP(u.col.ensure(sizeof(__bf16) * max_col), "device allocation");
-    UN_HIP(u.dA0.ensure(sizeof(float) * dmax), "device allocation");
-    UN_HIP(u.dA1.ensure(sizeof(float) * dmax), "device allocation");
-    UN_HIP(u.dZ.ensure(sizeof(float) * max_mco), "device allocation");
+    UN_HIP(u.dA0.ensure(sizeof(float) * max_mci), "device allocation");
+    UN_HIP(u.dA1.ensure(sizeof(float) * max_mci), "device allocation");
+    UN_HIP(u.dcat1.ensure(sizeof(float) * M64 * 96), "device allocation");
+    UN_HIP(u.dcat2.ensure(sizeof(float) * M32 * 192), "device allocation");
+    UN_HIP(u.dcat3.ensure(sizeof(float) * M16 * 384), "device allocation");
     UN_HIP(u.dZb.ensure(sizeof(__bf16) * max_mco), "device allocation");
-    UN_HIP(u.ds1.ensure(sizeof(float) * M64 * 32), "device allocation");
-    UN_HIP(u.ds2.ensure(sizeof(float) * M32 * 64), "device allocation");
-    UN_HIP(u.ds3.ensure(sizeof(float) * M16 * 128), "device allocation");
-    UN_HIP(u.part.ensure(sizeof(float) * max_part), "device allocation");
-    u.part_elems = max_part;
     u.capB_train = B;
+  }
+  if (train) {  // a smaller batch may take more partial sums (its layers' splits)
+    nn::PartTable tab;
+    std::vector<size_t> w_at, b_at;
+    UN_HIP(u.part.ensure(sizeof(float) * grad_parts(u, B, nullptr, tab, w_at, b_at)),
+           "device allocation");
   }
   return DD_OK;
 }
@@ -206,41 +230,6 @@ dd_status conv_fwd(dd_unet& u, size_t l, In in, bool train, hipStream_t st,
     UN_HIP(nn::conv3_silu(in.x, u.B, c.lg, c.ci, wt, bias, c.A.as<__bf16>(), z, c.co, pool, st),
            "conv");
   }
-  return DD_OK;
-}
-
-// Backward of one convolution: from dA (gradient of its activation) and its
-// input, the gradients of its weights and bias, and dX (the gradient of its
-// input, of the concatenation for a decoder input) when requested.
-dd_status conv_bwd(dd_unet& u, Conv& c, In in, const float* dA, float* dX, hipStream_t st) {
-  const int64_t M = M_of(u, c);
-  UN_HIP(nn::silu_bwd(dA, c.Z.as<float>(), M * c.co, u.dZ.as<float>(), u.dZb.as<__bf16>(), st),
-         "SiLU backward");
-  UN_HIP(nn::colsum_add(u.dZ.as<float>(), (int)M, c.co, u.g.as<float>() + c.b_off, st),
-         "bias gradient");
-  const __bf16* col = u.col.as<__bf16>();
-  int ld = 9 * c.ci;
-  if (c.ci % 32 != 0) {
-    UN_HIP(nn::im2col(in.x0, u.B, c.H, c.H, c.ci, KPAD0, u.col0.as<__bf16>(), st), "im2col");
-    col = u.col0.as<__bf16>();
-    ld = KPAD0;
-  } else if (in.coarse) {
-    UN_HIP(nn::im2col_upcat(in.coarse, in.c1, in.x, c.ci - in.c1, u.B, c.H, u.col.as<__bf16>(), st),
-           "im2col");
-  } else {
-    UN_HIP(nn::im2col(in.x, u.B, c.H, c.H, c.ci, ld, u.col.as<__bf16>(), st), "im2col");
-  }
-  const int want = wgrad_splits(c, M);
-  const int sp = nn::gemm_splits(9 * c.ci, (int)M, want);
-  UN_HIP(nn::gemm(col, ld, true, u.dZb.as<__bf16>(), c.co, false, u.part.as<float>(), c.co,
-                  9 * c.ci, c.co, (int)M, want, st),
-         "weight-gradient GEMM");
-  UN_HIP(nn::sum_splits(u.part.as<float>(), sp, 9LL * c.ci * c.co, u.g.as<float>() + c.w_off, st),
-         "weight-gradient reduction");
-  if (dX)
-    UN_HIP(nn::conv3_plain(u.dZ.as<float>(), u.B, c.lg, c.co, u.wd.as<__bf16>() + c.wd_off, dX,
-                           c.ci, st),
-           "data-gradient convolution");
   return DD_OK;
 }
 
@@ -284,40 +273,54 @@ dd_status forward(dd_unet& u, const float* x, bool train, hipStream_t st) {
   return DD_OK;
 }
 
+// Backward pass: per layer, from the last, dZ and its channel sums (act_bwd*,
+// which gathers dA from wherever it lies), the weight gradient's partial sums
+// and the data gradient; then the sums of all partials in one launch.
 dd_status backward(dd_unet& u, const float* x, const float* dy, hipStream_t st) {
-  auto& L = u.L;
   const int B = u.B;
-  const int64_t M64 = (int64_t)B * NPX, M32 = M64 / 4, M16 = M64 / 16;
-  float* a0 = u.dA0.as<float>();
-  float* a1 = u.dA1.as<float>();
-  dd_status rc;
   const std::vector<In> in = layer_inputs(u, x);
-  UN_HIP(nn::fill(u.ds1.as<float>(), M64 * 32, 0.f, st), "fill");
-  UN_HIP(nn::fill(u.ds2.as<float>(), M32 * 64, 0.f, st), "fill");
-  UN_HIP(nn::fill(u.ds3.as<float>(), M16 * 128, 0.f, st), "fill");
-  UN_HIP(nn::head_bwd(dy, L[13].A.as<__bf16>(), M64, 32, u.w.as<float>() + u.head_w, a0,
-                      u.g.as<float>() + u.head_w, st),
-         "head backward");
-  STEP(conv_bwd(u, L[13], in[13], a0, a1, st));
-  STEP(conv_bwd(u, L[12], in[12], a1, a0, st));  // a0 = d[up, skip] at 64^2 x 96
-  UN_HIP(nn::up_concat_bwd(a0, B, 32, 32, 64, 32, a1, u.ds1.as<float>(), st), "upsample backward");
-  STEP(conv_bwd(u, L[11], in[11], a1, a0, st));
-  STEP(conv_bwd(u, L[10], in[10], a0, a1, st));  // a1 = d[up, skip] at 32^2 x 192
-  UN_HIP(nn::up_concat_bwd(a1, B, 16, 16, 128, 64, a0, u.ds2.as<float>(), st), "upsample backward");
-  STEP(conv_bwd(u, L[9], in[9], a0, a1, st));
-  STEP(conv_bwd(u, L[8], in[8], a1, a0, st));  // a0 = d[up, skip] at 16^2 x 384
-  UN_HIP(nn::up_concat_bwd(a0, B, 8, 8, 256, 128, a1, u.ds3.as<float>(), st), "upsample backward");
-  STEP(conv_bwd(u, L[7], in[7], a1, a0, st));
-  STEP(conv_bwd(u, L[6], in[6], a0, a1, st));  // a1 = d p3 [8^2][128]
-  UN_HIP(nn::pool_bwd_add(a1, B, 16, 16, 128, u.ds3.as<float>(), st), "pool backward");
-  STEP(conv_bwd(u, L[5], in[5], u.ds3.as<float>(), a0, st));
-  STEP(conv_bwd(u, L[4], in[4], a0, a1, st));  // a1 = d p2 [16^2][64]
-  UN_HIP(nn::pool_bwd_add(a1, B, 32, 32, 64, u.ds2.as<float>(), st), "pool backward");
-  STEP(conv_bwd(u, L[3], in[3], u.ds2.as<float>(), a0, st));
-  STEP(conv_bwd(u, L[2], in[2], a0, a1, st));  // a1 = d p1 [32^2][32]
-  UN_HIP(nn::pool_bwd_add(a1, B, 64, 64, 32, u.ds1.as<float>(), st), "pool backward");
-  STEP(conv_bwd(u, L[1], in[1], u.ds1.as<float>(), a0, st));
-  STEP(conv_bwd(u, L[0], in[0], a0, nullptr, st));
+  nn::PartTable tab;
+  std::vector<size_t> w_at, b_at;
+  float* part = u.part.as<float>();
+  grad_parts(u, B, part, tab, w_at, b_at);
+  __bf16* dz = u.dZb.as<__bf16>();
+  float *a0 = u.dA0.as<float>(), *a1 = u.dA1.as<float>();
+  float* dcat[3] = {u.dcat1.as<float>(), u.dcat2.as<float>(), u.dcat3.as<float>()};
+  const float* da = nullptr;  // the data gradient just formed
+  for (int l = 13; l >= 0; --l) {
+    Conv& c = u.L[l];
+    const int64_t M = M_of(u, c);
+    const float* z = c.Z.as<float>();
+    float* bp = part + b_at[l];
+    hipError_t e;
+    switch (l) {
+      case 13:
+        e = nn::act_bwd_head(dy, u.w.as<float>() + u.head_w, c.A.as<__bf16>(), z, M, c.co, dz, bp,
+                             st);
+        break;
+      // the coarse inputs of the concatenations of layers 12, 10 and 8
+      case 11: e = nn::act_bwd_up(dcat[0], 96, z, B, c.lg, c.co, dz, bp, st); break;
+      case 9: e = nn::act_bwd_up(dcat[1], 192, z, B, c.lg, c.co, dz, bp, st); break;
+      case 7: e = nn::act_bwd_up(dcat[2], 384, z, B, c.lg, c.co, dz, bp, st); break;
+      // their skip inputs, which also feed the pooling to the next level
+      case 5: e = nn::act_bwd_pool(dcat[2], 384, da, z, B, c.lg, c.co, dz, bp, st); break;
+      case 3: e = nn::act_bwd_pool(dcat[1], 192, da, z, B, c.lg, c.co, dz, bp, st); break;
+      case 1: e = nn::act_bwd_pool(dcat[0], 96, da, z, B, c.lg, c.co, dz, bp, st); break;
+      default: e = nn::act_bwd(da, z, M, c.co, dz, bp, st); break;
+    }
+    UN_HIP(e, "activation backward");
+    if (l == 0) {
+      UN_HIP(nn::wgrad_first(in[0].x0, dz, B, c.ci, part + w_at[0], st), "weight gradient");
+      break;
+    }
+    UN_HIP(nn::wgrad(in[l].x, in[l].coarse, in[l].c1, dz, B, c.lg, c.ci, c.co, part + w_at[l], st),
+           "weight gradient");
+    float* dx = l == 12 ? dcat[0] : l == 10 ? dcat[1] : l == 8 ? dcat[2] : da == a0 ? a1 : a0;
+    UN_HIP(nn::conv3_plain(dz, B, c.lg, c.co, u.wd.as<__bf16>() + c.wd_off, dx, c.ci, st),
+           "data-gradient convolution");
+    da = dx;
+  }
+  UN_HIP(nn::sum_parts(tab, st), "gradient sums");
   return DD_OK;
 }
 #undef STEP
@@ -461,9 +464,8 @@ dd_status dd_unet_create(uint64_t seed, dd_unet** out) {
 
 void dd_unet_destroy(dd_unet* u) {
   if (!u) return;
-  for (DevBuf* b : {&u->w, &u->wf, &u->wd, &u->g, &u->m, &u->v, &u->col0, &u->p1, &u->p2, &u->p3,
-                    &u->y, &u->col, &u->dA0, &u->dA1, &u->dZ, &u->dZb,
-                    &u->ds1, &u->ds2, &u->ds3, &u->part, &u->loss_map, &u->norm_part,
+  for (DevBuf* b : {&u->w, &u->wf, &u->wd, &u->g, &u->m, &u->v, &u->p1, &u->p2, &u->p3, &u->y,
+                    &u->dA0, &u->dA1, &u->dcat1, &u->dcat2, &u->dcat3, &u->dZb, &u->part, &u->loss_map, &u->norm_part,
                     &u->scale_norm, &u->px, &u->pown, &u->pfeat, &u->pout, &u->ppref, &u->pspot,
                     &u->prel})
     b->release();

@@ -19,7 +19,8 @@
 // from its two sources.  Epilogues: plain (the data gradient), bias + SiLU,
 // and bias + SiLU followed by the 32 -> 1 output head reduced across lanes.
 // Activations are stored in BF16 (the MFMA operand precision; every consumer
-// rounds its input to BF16 anyway); pre-activations and gradients are FP32.
+// rounds its input to BF16 anyway), and so is dZ, the data gradient's input;
+// pre-activations and the data gradient are FP32.
 //
 // k_conv_first (the 5-channel input layer): K = 45 padded to 64; the input
 // halo tile is staged in LDS (FP32), each thread assembles its pixel's row of
@@ -62,11 +63,10 @@ __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) {
   return bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
 }
 
-// Activations (inputs of IN_PLAIN / IN_UPCAT with TIn = __bf16, outputs of
-// EPI_SILU / EPI_HEAD) are BF16; the data gradient reads and writes FP32.
+// Inputs and activations are BF16; the data gradient is written in FP32.
 struct ConvArgs {
-  const void* x;     // IN_PLAIN: input [M][ci]; IN_UPCAT: skip map [M][ci - c1]
-  const void* xc;    // IN_UPCAT: coarse map [M / 4][c1]
+  const __bf16* x;   // IN_PLAIN: input [M][ci]; IN_UPCAT: skip map [M][ci - c1]
+  const __bf16* xc;  // IN_UPCAT: coarse map [M / 4][c1]
   int c1;            // IN_UPCAT: channels taken from the coarse map
   int M, lg, ci;     // output pixels, log2 side, input channels
   const __bf16* wt;  // [N][9 ci]
@@ -204,15 +204,8 @@ __device__ __forceinline__ void epilogue(const ConvArgs& p, f32x4 (&acc)[4][NB],
   }
 }
 
-// Input element type as a template integer (kernel names in traces then
-// demangle plainly): TIN_BF16 for activations, TIN_F32 for gradients.
-enum { TIN_BF16 = 0, TIN_F32 = 1 };
-template <int TIN>
-using InType = typename std::conditional<TIN == TIN_BF16, __bf16, float>::type;
-
-template <int TIN, int IN, int BN, int EPI, int LG>
+template <int IN, int BN, int EPI, int LG>
 __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
-  using TIn = InType<TIN>;
   // weights staged in LDS for BN = 64; for BN = 32 (the one-chunk layers at
   // 64^2, which depend on occupancy) each wave reads them from L2, one tap ahead
   constexpr bool BLDS = BN >= 64;
@@ -233,17 +226,14 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
   constexpr int HW2 = W + 2, slice = (R + 2) * HW2;
   constexpr int G = CBM >> lgRW, HP = G * slice;
   const int img0 = m0 >> (2 * lg), y0 = (m0 >> lg) & (W - 1);
-  // staging: 16-byte slots of CPQ channels, QPP slots per pixel and chunk
-  constexpr int CPQ = 16 / (int)sizeof(TIn), LGQ = CPQ == 8 ? 2 : 3, QPP = 1 << LGQ;
-  constexpr int NSLOT = (HPMAX * QPP + 255) / 256;
-  const TIn* xin = static_cast<const TIn*>(p.x);
-  const TIn* xco = static_cast<const TIn*>(p.xc);
+  // staging: 16-byte slots of 8 channels, 4 slots per pixel and chunk
+  constexpr int NSLOT = (HPMAX * 4 + 255) / 256;
 
   // source pixel of every staging slot (fixed over the channel chunks)
   int src[NSLOT];
 #pragma unroll
   for (int i = 0; i < NSLOT; ++i) {
-    const int idx = tid + 256 * i, px = idx >> LGQ;
+    const int idx = tid + 256 * i, px = idx >> 2;
     int s = -1;
     if (px < HP) {
       const int g = px / slice, rem = px - g * slice;
@@ -275,12 +265,10 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
   const __bf16* wlane = p.wt + (int64_t)(n0 + (lane & 15)) * K + 8 * (lane >> 4);
   const int chunks = ci >> 5;
   // Staging registers of one chunk: the weights (BN = 64) and the halo tile.
-  // With BF16 activations and BN = 64 the next chunk's loads are issued before the
-  // current chunk's MFMAs and stored to LDS after them (register prefetch);
-  // the FP32 input of the data gradient is loaded and stored in one step.
-  constexpr bool PIPE = CPQ == 8 && BLDS;
-  using AReg = typename std::conditional<CPQ == 8, bf16x8, f32x4>::type;
-  AReg ar[NSLOT];
+  // With BN = 64 the next chunk's loads are issued before the current chunk's
+  // MFMAs and stored to LDS after them (register prefetch).
+  constexpr bool PIPE = BLDS;
+  bf16x8 ar[NSLOT];
   bf16x8 br[BLDS ? BSLOTS : 1];
   auto fetch = [&](int cc) {
 #pragma unroll
@@ -295,21 +283,21 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
     }
 #pragma unroll
     for (int i = 0; i < NSLOT; ++i) {
-      const int idx = tid + 256 * i, px = idx >> LGQ, q = idx & (QPP - 1);
-      ar[i] = AReg{};
+      const int idx = tid + 256 * i, px = idx >> 2, q = idx & 3;
+      ar[i] = bf16x8{};
       const int s = src[i];
       if (px < HP && s >= 0) {
-        const TIn* from;
+        const __bf16* from;
         if (IN == IN_UPCAT && cc * 32 < p.c1) {
           const int im = s >> (2 * lg), yy = (s >> lg) & (W - 1), xx = s & (W - 1);
           const int sc = (((im << (lg - 1)) + (yy >> 1)) << (lg - 1)) + (xx >> 1);
-          from = xco + (int64_t)sc * p.c1 + cc * 32 + CPQ * q;
+          from = p.xc + (int64_t)sc * p.c1 + cc * 32 + 8 * q;
         } else if (IN == IN_UPCAT) {
-          from = xin + (int64_t)s * (ci - p.c1) + (cc * 32 - p.c1) + CPQ * q;
+          from = p.x + (int64_t)s * (ci - p.c1) + (cc * 32 - p.c1) + 8 * q;
         } else {
-          from = xin + (int64_t)s * ci + cc * 32 + CPQ * q;
+          from = p.x + (int64_t)s * ci + cc * 32 + 8 * q;
         }
-        ar[i] = *reinterpret_cast<const AReg*>(from);
+        ar[i] = *reinterpret_cast<const bf16x8*>(from);
       }
     }
   };
@@ -325,13 +313,8 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
     }
 #pragma unroll
     for (int i = 0; i < NSLOT; ++i) {
-      const int idx = tid + 256 * i, px = idx >> LGQ, q = idx & (QPP - 1);
-      if (px < HP) {
-        if constexpr (CPQ == 8)
-          *reinterpret_cast<bf16x8*>(&As[px][8 * q]) = ar[i];
-        else
-          *reinterpret_cast<bf16x4*>(&As[px][4 * q]) = to_bf16x4(ar[i]);
-      }
+      const int idx = tid + 256 * i, px = idx >> 2, q = idx & 3;
+      if (px < HP) *reinterpret_cast<bf16x8*>(&As[px][8 * q]) = ar[i];
     }
   };
   if (PIPE) fetch(0);
@@ -386,7 +369,7 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
 // then assembles its pixel's 9 CI values (indices fixed at compile time) and
 // writes its BF16 row of A with 16-byte stores.
 template <int CI, int EPI>
-__global__ void __launch_bounds__(256) k_conv_first(ConvArgs p) {
+__global__ void __launch_bounds__(256) k_conv_first(ConvArgs p, const float* __restrict__ x) {
   static_assert(9 * CI <= 64, "first layer: 9 CI must fit in 64 columns");
   __shared__ float Xs[HPMAX][CI];
   __shared__ __attribute__((aligned(16))) __bf16 As[CBM][72];
@@ -397,7 +380,6 @@ __global__ void __launch_bounds__(256) k_conv_first(ConvArgs p) {
   const int lgR = lg >= 4 ? 8 - lg : lg, R = 1 << lgR, lgRW = lgR + lg;
   const int HW2 = W + 2, slice = (R + 2) * HW2, HP = (CBM >> lgRW) * slice;
   const int img0 = m0 >> (2 * lg), y0 = (m0 >> lg) & (W - 1);
-  const float* x = static_cast<const float*>(p.x);
   // halo tile, one pixel per thread and pass
   for (int px = tid; px < HP; px += 256) {
     const int g = px / slice, rem = px - g * slice;
@@ -464,25 +446,25 @@ __global__ void __launch_bounds__(256) k_conv_first(ConvArgs p) {
   epilogue<2, EPI>(p, acc, m0, 0, wave, lane);
 }
 
-template <int TIN, int IN, int BN, int EPI>
+template <int IN, int BN, int EPI>
 void launch_halo_bn(const ConvArgs& p, dim3 grid, hipStream_t st) {
   switch (p.lg) {
-    case 3: hipLaunchKernelGGL((k_conv_halo<TIN, IN, BN, EPI, 3>), grid, dim3(256), 0, st, p); break;
-    case 4: hipLaunchKernelGGL((k_conv_halo<TIN, IN, BN, EPI, 4>), grid, dim3(256), 0, st, p); break;
-    case 5: hipLaunchKernelGGL((k_conv_halo<TIN, IN, BN, EPI, 5>), grid, dim3(256), 0, st, p); break;
-    default: hipLaunchKernelGGL((k_conv_halo<TIN, IN, BN, EPI, 6>), grid, dim3(256), 0, st, p); break;
+    case 3: hipLaunchKernelGGL((k_conv_halo<IN, BN, EPI, 3>), grid, dim3(256), 0, st, p); break;
+    case 4: hipLaunchKernelGGL((k_conv_halo<IN, BN, EPI, 4>), grid, dim3(256), 0, st, p); break;
+    case 5: hipLaunchKernelGGL((k_conv_halo<IN, BN, EPI, 5>), grid, dim3(256), 0, st, p); break;
+    default: hipLaunchKernelGGL((k_conv_halo<IN, BN, EPI, 6>), grid, dim3(256), 0, st, p); break;
   }
 }
 
 // Callers have checked 3 <= lg <= 6 (halo_ok).
-template <int TIN, int IN, int EPI>
+template <int IN, int EPI>
 hipError_t launch_halo(const ConvArgs& p, hipStream_t st) {
   const int bn = (EPI == EPI_HEAD) ? 32 : (p.N % 64 == 0) ? 64 : 32;
   dim3 grid((p.M + CBM - 1) / CBM, p.N / bn);
   if (bn == 64)
-    launch_halo_bn<TIN, IN, 64, EPI>(p, grid, st);
+    launch_halo_bn<IN, 64, EPI>(p, grid, st);
   else
-    launch_halo_bn<TIN, IN, 32, EPI>(p, grid, st);
+    launch_halo_bn<IN, 32, EPI>(p, grid, st);
   return hipGetLastError();
 }
 
@@ -496,7 +478,7 @@ hipError_t conv3_silu(const __bf16* x, int B, int lg, int ci, const __bf16* wt, 
                       __bf16* act, float* z, int co, __bf16* pool, hipStream_t st) {
   ConvArgs p{x, nullptr, 0, B << (2 * lg), lg, ci, wt, bias, act, z, nullptr, nullptr, co, pool};
   if (!halo_ok(p.M, lg, ci, co) || !act || (pool && lg < 4)) return hipErrorInvalidValue;
-  return launch_halo<TIN_BF16, IN_PLAIN, EPI_SILU>(p, st);
+  return launch_halo<IN_PLAIN, EPI_SILU>(p, st);
 }
 
 hipError_t conv3_upcat_silu(const __bf16* coarse, int c1, const __bf16* skip, int c2, int B,
@@ -504,7 +486,7 @@ hipError_t conv3_upcat_silu(const __bf16* coarse, int c1, const __bf16* skip, in
                             int co, hipStream_t st) {
   ConvArgs p{skip, coarse, c1, B << (2 * lg), lg, c1 + c2, wt, bias, act, z, nullptr, nullptr, co};
   if (!halo_ok(p.M, lg, p.ci, co) || c1 % 32 != 0 || lg < 4 || !act) return hipErrorInvalidValue;
-  return launch_halo<TIN_BF16, IN_UPCAT, EPI_SILU>(p, st);
+  return launch_halo<IN_UPCAT, EPI_SILU>(p, st);
 }
 
 hipError_t conv3_silu_head(const __bf16* x, int B, int lg, int ci, const __bf16* wt,
@@ -512,24 +494,24 @@ hipError_t conv3_silu_head(const __bf16* x, int B, int lg, int ci, const __bf16*
                            hipStream_t st) {
   ConvArgs p{x, nullptr, 0, B << (2 * lg), lg, ci, wt, bias, act, z, head, y, 32};
   if (!halo_ok(p.M, lg, ci, 32) || !y || !head) return hipErrorInvalidValue;
-  return launch_halo<TIN_BF16, IN_PLAIN, EPI_HEAD>(p, st);
+  return launch_halo<IN_PLAIN, EPI_HEAD>(p, st);
 }
 
-hipError_t conv3_plain(const float* x, int B, int lg, int ci, const __bf16* wt, float* out, int co,
+hipError_t conv3_plain(const __bf16* x, int B, int lg, int ci, const __bf16* wt, float* out, int co,
                        hipStream_t st) {
   ConvArgs p{x, nullptr, 0, B << (2 * lg), lg, ci, wt, nullptr, out, nullptr, nullptr, nullptr, co};
   if (!halo_ok(p.M, lg, ci, co) || !out) return hipErrorInvalidValue;
-  return launch_halo<TIN_F32, IN_PLAIN, EPI_PLAIN>(p, st);
+  return launch_halo<IN_PLAIN, EPI_PLAIN>(p, st);
 }
 
 hipError_t conv3_first_silu(const float* x, int B, int lg, int ci, const __bf16* wt,
                             const float* bias, __bf16* act, float* z, hipStream_t st) {
-  ConvArgs p{x, nullptr, 0, B << (2 * lg), lg, ci, wt, bias, act, z, nullptr, nullptr, 32};
+  ConvArgs p{nullptr, nullptr, 0, B << (2 * lg), lg, ci, wt, bias, act, z, nullptr, nullptr, 32};
   if (p.M <= 0 || lg < 3 || lg > 6 || !act) return hipErrorInvalidValue;
   const dim3 grid((p.M + CBM - 1) / CBM);
   switch (ci) {  // the input channel counts the network uses
-    case 5: hipLaunchKernelGGL((k_conv_first<5, EPI_SILU>), grid, dim3(256), 0, st, p); break;
-    case 3: hipLaunchKernelGGL((k_conv_first<3, EPI_SILU>), grid, dim3(256), 0, st, p); break;
+    case 5: hipLaunchKernelGGL((k_conv_first<5, EPI_SILU>), grid, dim3(256), 0, st, p, x); break;
+    case 3: hipLaunchKernelGGL((k_conv_first<3, EPI_SILU>), grid, dim3(256), 0, st, p, x); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -1,5 +1,5 @@
 // unet_kernels.h -- launchers of the surrogate's HIP kernels (unet_conv.hip,
-// unet_kernels.hip).  All activations are NHWC FP32; GEMM operands BF16.
+// unet_wgrad.hip, unet_kernels.hip).  All activations are NHWC FP32; GEMM operands BF16.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -31,7 +31,7 @@ constexpr int kNormBlocks = 256;  // partial sums of the gradient norm
 //                      [B][side][side][c2]];
 //   conv3_silu_head:   co = 32, then y = SiLU(z) . head[0..31] + head[32]
 //                      (act and z stored when non-NULL);
-//   conv3_plain:       out = conv (the data gradient, with the dgrad layout);
+//   conv3_plain:       out = conv in FP32 (the data gradient, with the dgrad layout);
 //   conv3_first_silu:  ci < 32 with 9 ci <= 64, co = 32, weights [32][64].
 // ci, c1 and co must be multiples of 32 except in conv3_first_silu.
 hipError_t conv3_silu(const __bf16* x, int B, int lg, int ci, const __bf16* wt, const float* bias,
@@ -42,32 +42,47 @@ hipError_t conv3_upcat_silu(const __bf16* coarse, int c1, const __bf16* skip, in
 hipError_t conv3_silu_head(const __bf16* x, int B, int lg, int ci, const __bf16* wt,
                            const float* bias, const float* head, __bf16* act, float* z, float* y,
                            hipStream_t st);
-hipError_t conv3_plain(const float* x, int B, int lg, int ci, const __bf16* wt, float* out, int co,
+hipError_t conv3_plain(const __bf16* x, int B, int lg, int ci, const __bf16* wt, float* out, int co,
                        hipStream_t st);
 hipError_t conv3_first_silu(const float* x, int B, int lg, int ci, const __bf16* wt,
                             const float* bias, __bf16* act, float* z, hipStream_t st);
 
-// C = A B on BF16 MFMA (FP32 accumulation); ta/tb select transposed storage;
-// with ksplit > 1 the partial matrices (gemm_splits() of them) are written at
-// C + s*M*ldc and must be added by sum_splits.
-hipError_t gemm(const __bf16* A, int lda, bool ta, const __bf16* B, int ldb, bool tb, float* C,
-                int ldc, int M, int N, int K, int ksplit, hipStream_t st);
-int gemm_splits(int M, int K, int ksplit);
-hipError_t sum_splits(const float* part, int splits, int64_t n, float* out, hipStream_t st);
-hipError_t im2col(const float* x, int B, int H, int W, int C, int ld, __bf16* col, hipStream_t st);
-hipError_t im2col(const __bf16* x, int B, int H, int W, int C, int ld, __bf16* col,
-                  hipStream_t st);
-// im2col of the virtual concatenation [upsampled coarse (c1), skip (c2)].
-hipError_t im2col_upcat(const __bf16* coarse, int c1, const __bf16* skip, int c2, int B, int H,
-                        __bf16* col, hipStream_t st);
-hipError_t silu_bwd(const float* dA, const float* Z, int64_t n, float* dZ, __bf16* dZb,
-                    hipStream_t st);
-hipError_t colsum_add(const float* dZ, int M, int N, float* db, hipStream_t st);
-hipError_t pool_bwd_add(const float* dy, int B, int H, int W, int C, float* dx, hipStream_t st);
-hipError_t up_concat_bwd(const float* dout, int B, int h, int w, int C1, int C2, float* dx,
-                         float* dskip, hipStream_t st);
-hipError_t head_bwd(const float* dy, const __bf16* a, int64_t M, int C, const float* w, float* da,
-                    float* dw, hipStream_t st);
+// Weight gradient (unet_wgrad.hip) of a 3x3 convolution of x [B][side][side][ci]
+// (or the concatenation of the upsampled coarse map, c1 channels, and the skip
+// map x) for dz [B][side][side][co]: wgrad_splits() partial sums [9 ci][co]
+// each.  wgrad_first: the first layer (ci = 5, co = 32, side 64, x FP32).
+int wgrad_splits(int64_t M, int ci, int co);
+hipError_t wgrad(const __bf16* x, const __bf16* coarse, int c1, const __bf16* dz, int B, int lg,
+                 int ci, int co, float* part, hipStream_t st);
+hipError_t wgrad_first(const float* x, const __bf16* dz, int B, int ci, float* part,
+                       hipStream_t st);
+// dZ = dA SiLU'(z) as BF16 and its kActBlocks partial channel sums (see
+// k_act_bwd): dA the data gradient itself, dy w (head; 2 C + 1 sums per
+// block: bias, head weights, head bias), the upsampling's adjoint on the
+// first channels of dcat, or the skip channels of dcat and the pooling's
+// adjoint of dp.
+constexpr int kActBlocks = 512;
+hipError_t act_bwd(const float* da, const float* z, int64_t M, int C, __bf16* dz, float* part,
+                   hipStream_t st);
+hipError_t act_bwd_head(const float* dy, const float* hw, const __bf16* a, const float* z, int64_t M,
+                        int C, __bf16* dz, float* part, hipStream_t st);
+hipError_t act_bwd_up(const float* dcat, int ct, const float* z, int B, int lg, int C, __bf16* dz,
+                      float* part, hipStream_t st);
+hipError_t act_bwd_pool(const float* dcat, int ct, const float* dp, const float* z, int B, int lg,
+                        int C, __bf16* dz, float* part, hipStream_t st);
+// out[e] = sum over s < splits of part[s stride + e], e < n, for every entry.
+struct PartDesc {
+  const float* part;
+  int64_t stride, n;
+  int splits;
+  float* out;
+  int first = 0;  // set by sum_parts
+};
+struct PartTable {
+  int n;
+  PartDesc l[2 * kMaxConv + 1];
+};
+hipError_t sum_parts(PartTable tab, hipStream_t st);
 // Squared relative L2 error per map (loss_map[b]) of prediction own + exp(y)
 // against t; dy of the mean over maps of that error plus the anchor term
 // (anchor / npx) sum (r/t)^2 (y - ln r)^2, r = max(t - own, 1e-6 t).
