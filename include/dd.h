@@ -231,7 +231,8 @@ dd_status dd_tune_load(const char *cache_path);
  * the exponent's rounding correction, 9 in all in those that fold the
  * series' linear term into the exponent; 29 + 2M in FP64; FP64 maps, sums of
  * Gaussians on the matrix cores, 2 per pair and Gaussian, counted with two
- * Gaussians per pair).  Kernel names: "arrival_far",
+ * Gaussians per pair; FP64 arrival queries of scans made of rasters, sums of
+ * a table of distinct terms, the table's 29 + 2M per term and its sums).  Kernel names: "arrival_far",
  * "arrival_near", "map", "batch", "lag_rows", "reduce".                   */
 typedef struct {
   double ms;         /* summed event time of the launches                   */

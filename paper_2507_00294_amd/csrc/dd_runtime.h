@@ -9,6 +9,7 @@
 
 #include "../../include/dd.h"
 #include "dd_internal.h"
+#include "dd_lattice.h"
 
 struct dd_scan;
 
@@ -112,6 +113,9 @@ struct ArrivalPlan {
   int n_near = 0, n_far = 0, S = 0;
   DegreeBounds bounds{};
   double near_pairs = 0, near_flops = 0, far_pairs = 0, far_flops = 0;
+  // a scan of rasters, FP64: its tables are in `items` instead (n_near = n_far = 0)
+  bool lattice = false;
+  LatJob lat{};
 };
 
 // Plan of an arrival query over the visits [j0, j1) (the streaming range):
@@ -189,6 +193,8 @@ struct dd_scan {
     dd::DegreeBounds bounds{};
     std::vector<dd::ArrItem> near, far;
     std::vector<int32_t> tile_slots;
+    bool lattice = false;  // a scan of rasters, FP64: `lat` instead of items
+    dd::LatPlan lat;
     double pairs = 0, flops = 0;
   } barr;
   struct BatchMapPlan {
