@@ -11,7 +11,7 @@
 // tile's input pixels plus a one-pixel halo (at most 400 pixels) in LDS as
 // BF16, once, and all nine taps then read their A fragments from that tile
 // (the nine-fold reuse of every input value stays on chip).  With BN = 64 the
-// chunk's weights (9 taps x BN columns x 32, from [N][9 ci]) are staged in LDS
+// chunk's weights (9 taps x BN columns x 32) are staged in LDS
 // once per block beside it, so the four waves share them; with BN = 32 each
 // wave reads its weight fragments from L2 one tap ahead, which keeps the LDS
 // footprint (and so the occupancy) of the 64^2 layers low.  Input modes: a plain activation, or the decoder's virtual
@@ -21,6 +21,12 @@
 // Activations are stored in BF16 (the MFMA operand precision; every consumer
 // rounds its input to BF16 anyway), and so is dZ, the data gradient's input;
 // pre-activations and the data gradient are FP32.
+//
+// k_conv_small: the 64-pixel tile of launches that would leave the chip idle.
+//
+// Weights are laid out [ci / 32][tap][N][32]: a tap's weights of a chunk are
+// contiguous (against [N][9 ci], whose chunk is 64-byte pieces: 256 maps' layers
+// 5% shorter, the small tile's 20%).
 //
 // k_conv_first (the 5-channel input layer): K = 45 padded to 64; the input
 // halo tile is staged in LDS (FP32), each thread assembles its pixel's row of
@@ -52,6 +58,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int CBM = 256;    // output pixels per block
+constexpr int CSM = 64;     // output pixels per block of the small tile
 constexpr int CLDK = 40;    // LDS row of the halo tile: 32 channels + 8 padding (BF16)
 constexpr int CLDB = 40;    // LDS row of the staged weights
 constexpr int HPMAX = 400;  // halo-tile pixels: 6 x 66, 10 x 34, 18 x 18 or 4 x 10 x 10
@@ -69,7 +76,7 @@ struct ConvArgs {
   const __bf16* xc;  // IN_UPCAT: coarse map [M / 4][c1]
   int c1;            // IN_UPCAT: channels taken from the coarse map
   int M, lg, ci;     // output pixels, log2 side, input channels
-  const __bf16* wt;  // [N][9 ci]
+  const __bf16* wt;  // [ci / 32][9][N][32] (first layer: [N][64])
   const float* bias;
   void* out;         // [M][N]: BF16 activation (EPI_SILU, EPI_HEAD; may be NULL
                      // with EPI_HEAD) or FP32 (EPI_PLAIN)
@@ -204,6 +211,92 @@ __device__ __forceinline__ void epilogue(const ConvArgs& p, f32x4 (&acc)[4][NB],
   }
 }
 
+// Small tile (k_conv_small): 64 pixels -- 2 or 4 rows of an image, or an 8x8
+// image -- by 64 output channels, a wave taking all 64 pixels for 16 of the
+// channels.  No weight is shared between waves, so each wave reads its nine
+// fragments of a chunk from L2 into registers, the next chunk's (and its share
+// of the next halo tile) while the current one is multiplied.  The chunks,
+// taps and channels are added up in k_conv_halo's order: the same values.
+template <int IN, int EPI, int LG>
+__global__ void __launch_bounds__(256) k_conv_small(ConvArgs p) {
+  static_assert(LG >= 3 && LG <= 5, "64-pixel tiles are whole rows");
+  constexpr int lg = LG, W = 1 << lg, R = CSM >> lg;
+  constexpr int HW2 = W + 2, HP = (R + 2) * HW2;
+  constexpr int NSLOT = (HP * 4 + 255) / 256;
+  __shared__ __attribute__((aligned(16))) __bf16 As[2][HP][CLDK];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.x * CSM, n0 = blockIdx.y * 64 + wave * 16;
+  const int ci = p.ci, chunks = ci >> 5;
+  const int img = m0 >> (2 * lg), y0 = (m0 >> lg) & (W - 1);
+  int src[NSLOT];
+#pragma unroll
+  for (int i = 0; i < NSLOT; ++i) {
+    const int px = (tid + 256 * i) >> 2;
+    const int yy = y0 + px / HW2 - 1, xx = px % HW2 - 1;
+    src[i] = px < HP && yy >= 0 && yy < W && xx >= 0 && xx < W ? ((img << lg) + yy) * W + xx : -1;
+  }
+  const __bf16* wlane = p.wt + (n0 + (lane & 15)) * 32 + 8 * (lane >> 4);
+  bf16x8 ar[NSLOT], wn[9];
+  auto fetch = [&](int cc) {
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap)
+      wn[tap] =
+          *reinterpret_cast<const bf16x8*>(wlane + (int64_t)(cc * 9 + tap) * p.N * 32);
+#pragma unroll
+    for (int i = 0; i < NSLOT; ++i) {
+      const int q = tid & 3, s = src[i];
+      ar[i] = bf16x8{};
+      if (s >= 0) {
+        const __bf16* from;
+        if (IN == IN_UPCAT && cc * 32 < p.c1) {
+          const int im = s >> (2 * lg), yy = (s >> lg) & (W - 1), xx = s & (W - 1);
+          const int sc = (((im << (lg - 1)) + (yy >> 1)) << (lg - 1)) + (xx >> 1);
+          from = p.xc + (int64_t)sc * p.c1 + cc * 32 + 8 * q;
+        } else if (IN == IN_UPCAT) {
+          from = p.x + (int64_t)s * (ci - p.c1) + (cc * 32 - p.c1) + 8 * q;
+        } else {
+          from = p.x + (int64_t)s * ci + cc * 32 + 8 * q;
+        }
+        ar[i] = *reinterpret_cast<const bf16x8*>(from);
+      }
+    }
+  };
+  int hbase[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const int o = a * 16 + (lane & 15);
+    hbase[a] = (o >> lg) * HW2 + (o & (W - 1));
+  }
+  f32x4 acc[4][1];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) acc[a][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+  fetch(0);
+  for (int cc = 0; cc < chunks; ++cc) {
+    bf16x8 w[9];
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) w[tap] = wn[tap];
+    // two tiles: the chunk before may still be read from the other one
+    auto& A = As[cc & 1];
+#pragma unroll
+    for (int i = 0; i < NSLOT; ++i) {
+      const int px = (tid + 256 * i) >> 2;
+      if (px < HP) *reinterpret_cast<bf16x8*>(&A[px][8 * (tid & 3)]) = ar[i];
+    }
+    __syncthreads();
+    if (cc + 1 < chunks) fetch(cc + 1);
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const int toff = (tap / 3) * HW2 + (tap % 3);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const bf16x8 af = *reinterpret_cast<const bf16x8*>(&A[hbase[a] + toff][8 * (lane >> 4)]);
+        acc[a][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[tap], af, acc[a][0], 0, 0, 0);
+      }
+    }
+  }
+  epilogue<1, EPI, false, LG>(p, acc, m0, n0, 0, lane);
+}
+
 template <int IN, int BN, int EPI, int LG>
 __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
   // weights staged in LDS for BN = 64; for BN = 32 (the one-chunk layers at
@@ -219,7 +312,7 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
   // the image side is a template parameter, so that the tile geometry below
   // is constant and its divisions are multiplications
   constexpr int lg = LG, W = 1 << lg;
-  const int ci = p.ci, K = 9 * ci;
+  const int ci = p.ci;
   // tile geometry: G image slices of R rows x W columns, halo (R+2) x (W+2)
   constexpr int lgR = lg >= 4 ? 8 - lg : lg;  // rows per slice: 256 / W, or W for W = 8
   constexpr int R = 1 << lgR, lgRW = lgR + lg;
@@ -262,7 +355,7 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const __bf16* wlane = p.wt + (int64_t)(n0 + (lane & 15)) * K + 8 * (lane >> 4);
+  const __bf16* wlane = p.wt + (n0 + (lane & 15)) * 32 + 8 * (lane >> 4);
   const int chunks = ci >> 5;
   // Staging registers of one chunk: the weights (BN = 64) and the halo tile.
   // With BN = 64 the next chunk's loads are issued before the current chunk's
@@ -277,8 +370,8 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
       if (BLDS && piece < BPIECES) {
         const int tap = piece / (BN * 4), rem = piece - tap * (BN * 4);
         const int n = rem >> 2, part = rem & 3;
-        br[BLDS ? i : 0] = *reinterpret_cast<const bf16x8*>(p.wt + (int64_t)(n0 + n) * K +
-                                                            tap * ci + cc * 32 + part * 8);
+        br[BLDS ? i : 0] = *reinterpret_cast<const bf16x8*>(
+            p.wt + ((int64_t)(cc * 9 + tap) * p.N + n0 + n) * 32 + part * 8);
       }
     }
 #pragma unroll
@@ -325,7 +418,7 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
     if (!BLDS) {
 #pragma unroll
       for (int b = 0; b < NB; ++b)
-        bcur[b] = *reinterpret_cast<const bf16x8*>(wlane + (int64_t)b * 16 * K + cc * 32);
+        bcur[b] = *reinterpret_cast<const bf16x8*>(wlane + ((int64_t)cc * 9 * p.N + b * 16) * 32);
     }
     __syncthreads();
     if (PIPE && cc + 1 < chunks) fetch(cc + 1);
@@ -336,8 +429,8 @@ __global__ void __launch_bounds__(256) k_conv_halo(ConvArgs p) {
       if (!BLDS && tap < 8) {
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-          bnext[b] = *reinterpret_cast<const bf16x8*>(wlane + (int64_t)b * 16 * K + (tap + 1) * ci +
-                                                      cc * 32);
+          bnext[b] = *reinterpret_cast<const bf16x8*>(
+              wlane + ((int64_t)(cc * 9 + tap + 1) * p.N + b * 16) * 32);
       }
       bf16x8 af[4];
 #pragma unroll
@@ -456,11 +549,31 @@ void launch_halo_bn(const ConvArgs& p, dim3 grid, hipStream_t st) {
   }
 }
 
+// Blocks of 256 pixels below which the small tile is taken: the chip has 256
+// CUs, and a block's chunks are a serial chain.  Training batch of 32, large ->
+// small tile: 8x8 levels (32 blocks) 30 -> 12 us a layer, 16x16 (64) 15.5 -> 8,
+// 32x32 (128) 12 -> 8, 16x16 384 -> 128 channels' data gradient (192) 18.6 ->
+// 13.7; 256 maps, 8x8 (256 blocks): 31.5 -> 34, 16x16 (512): 25 -> 35 (the small
+// tile reads four times the weights).
+constexpr int64_t kSmallBelow = 256;
+
 // Callers have checked 3 <= lg <= 6 (halo_ok).
 template <int IN, int EPI>
 hipError_t launch_halo(const ConvArgs& p, hipStream_t st) {
   const int bn = (EPI == EPI_HEAD) ? 32 : (p.N % 64 == 0) ? 64 : 32;
   dim3 grid((p.M + CBM - 1) / CBM, p.N / bn);
+  if constexpr (EPI != EPI_HEAD) {
+    if (bn == 64 && p.lg <= 5 && (int64_t)grid.x * grid.y < kSmallBelow) {
+      const dim3 g(p.M / CSM, p.N / 64);
+      if (p.lg == 3)
+        hipLaunchKernelGGL((k_conv_small<IN, EPI, 3>), g, dim3(256), 0, st, p);
+      else if (p.lg == 4)
+        hipLaunchKernelGGL((k_conv_small<IN, EPI, 4>), g, dim3(256), 0, st, p);
+      else
+        hipLaunchKernelGGL((k_conv_small<IN, EPI, 5>), g, dim3(256), 0, st, p);
+      return hipGetLastError();
+    }
+  }
   if (bn == 64)
     launch_halo_bn<IN, 64, EPI>(p, grid, st);
   else

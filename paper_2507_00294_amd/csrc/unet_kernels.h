@@ -10,8 +10,8 @@ namespace nn {
 
 // One convolution layer for the weight-layout kernel.
 struct ConvDesc {
-  int ci, co, kpad, has_dgrad;  // kpad: row length of the forward layout (>= 9 ci)
-  int64_t w_off, wf_off, wd_off;  // FP32 master, BF16 forward [co][kpad], BF16 dgrad [ci][9 co]
+  int ci, co, kpad, has_dgrad;  // kpad: forward weights per output channel (>= 9 ci)
+  int64_t w_off, wf_off, wd_off;  // FP32 master, BF16 forward and dgrad (k_prep_weights)
 };
 constexpr int kMaxConv = 16;
 struct ConvTable {
@@ -21,7 +21,7 @@ struct ConvTable {
 constexpr int kNormBlocks = 256;  // partial sums of the gradient norm
 
 // 3x3 convolutions (unet_conv.hip) of x [B][side][side][ci], side = 2^lg in
-// 8..64, weights wt [co][9 ci] (k = tap ci + c):
+// 8..64, weights wt [ci / 32][tap][co][32] (k_prep_weights):
 //   conv3_silu:        z = conv + bias, act = SiLU(z) (z stored when non-NULL;
 //                      with pool non-NULL, side >= 16, also the 2x2 average of
 //                      act, [B][side/2][side/2][co]: the four BF16 values in row order, x 0.25,

@@ -124,24 +124,38 @@ __global__ void __launch_bounds__(256) k_adam(float* __restrict__ w, float* __re
 
 // BF16 weight layouts of the convolutions from the FP32 master vector (layer
 // blockIdx.y), whose weights W[k][j] (k = tap ci + c) start at w_off:
-//   forward  wf[j][k], k < kpad (zero for k >= 9 ci);
-//   dgrad    wd[c][t co + j] = W[(8 - t) ci + c][j] (mirrored taps).
+//   forward  wf[c / 32][t][j][c % 32] = W[t ci + c][j] (first layer: [j][k],
+//            k < kpad, zero for k >= 9 ci);
+//   dgrad    wd[j / 32][t][c][j % 32] = W[(8 - t) ci + c][j] (mirrored taps):
+// what a block reads for a chunk of 32 input channels is contiguous per tap.  A
+// thread makes eight consecutive values; neighbours read neighbouring j.
 __global__ void __launch_bounds__(256) k_prep_weights(const float* __restrict__ w, ConvTable tab,
                                                       __bf16* __restrict__ wf,
                                                       __bf16* __restrict__ wd) {
   const ConvDesc L = tab.l[blockIdx.y];
-  const int64_t nf = (int64_t)L.co * L.kpad, nd = L.has_dgrad ? 9LL * L.ci * L.co : 0;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nf + nd;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    if (e < nf) {
-      const int j = (int)(e / L.kpad), k = (int)(e % L.kpad);
-      wf[L.wf_off + e] = k < 9 * L.ci ? (__bf16)w[L.w_off + (int64_t)k * L.co + j] : (__bf16)0.f;
+  const int nf = L.co * L.kpad / 8, nd = L.has_dgrad ? 9 * L.ci * L.co / 8 : 0;
+  const bool first = L.ci % 32 != 0;
+  typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+  const float* W = w + L.w_off;
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < nf + nd; e += gridDim.x * blockDim.x) {
+    bf16x8 v;
+    if (e < nf && first) {
+      const int j = 8 * e / L.kpad, k = 8 * e % L.kpad;
+      for (int i = 0; i < 8; ++i)
+        v[i] = k + i < 9 * L.ci ? (__bf16)W[(int64_t)(k + i) * L.co + j] : (__bf16)0.f;
+      *reinterpret_cast<bf16x8*>(wf + L.wf_off + 8 * (int64_t)e) = v;
+    } else if (e < nf) {
+      const int j = e % L.co, g = e / L.co;  // g = (c / 32 9 + t) 4 + c % 32 / 8
+      const int part = g & 3, t = (g >> 2) % 9, cc = (g >> 2) / 9;
+      const float* from = W + (int64_t)(t * L.ci + cc * 32 + part * 8) * L.co + j;
+      for (int i = 0; i < 8; ++i) v[i] = (__bf16)from[(int64_t)i * L.co];
+      *reinterpret_cast<bf16x8*>(wf + L.wf_off + ((int64_t)(g >> 2) * L.co + j) * 32 + part * 8) = v;
     } else {
-      const int64_t f = e - nf;
-      const int K2 = 9 * L.co;
-      const int c = (int)(f / K2), r = (int)(f % K2);
-      const int t = r / L.co, j = r % L.co;
-      wd[L.wd_off + f] = (__bf16)w[L.w_off + ((int64_t)(8 - t) * L.ci + c) * L.co + j];
+      const int f = e - nf, part = f & 3, c = (f >> 2) % L.ci, g = (f >> 2) / L.ci;
+      const int t = g % 9, jc = g / 9;
+      const float* from = W + (int64_t)((8 - t) * L.ci + c) * L.co + jc * 32 + part * 8;
+      for (int i = 0; i < 8; ++i) v[i] = (__bf16)from[i];
+      *reinterpret_cast<bf16x8*>(wd + L.wd_off + 8 * (int64_t)f) = v;
     }
   }
 }
