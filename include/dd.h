@@ -232,8 +232,10 @@ dd_status dd_tune_load(const char *cache_path);
  * series' linear term into the exponent; 29 + 2M in FP64; FP64 maps, sums of
  * Gaussians on the matrix cores, 2 per pair and Gaussian, counted with two
  * Gaussians per pair; FP64 arrival queries of scans made of rasters, sums of
- * a table of distinct terms, the table's 29 + 2M per term and its sums).  Kernel names: "arrival_far",
- * "arrival_near", "map", "batch", "lag_rows", "reduce".                   */
+ * a table of distinct terms, the table's 29 + 2M per term and its sums; the
+ * mixed arrival query's squared distance, 5 of these, runs on the matrix
+ * cores).  Kernel names: "arrival_far", "arrival_near", "map", "batch",
+ * "lag_rows", "reduce".                                                   */
 typedef struct {
   double ms;         /* summed event time of the launches                   */
   int64_t launches;

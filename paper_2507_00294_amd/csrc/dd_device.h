@@ -49,16 +49,14 @@ __device__ __forceinline__ double2 ldc(const double2* p) {
 }
 #undef DD_CONST_AS
 
-// Per-lane load of the first three fields of a float4 known to be in global
-// memory (a plain vector load, not a flat one, also through a pointer read
-// from memory); the fourth field is returned as 0.
-__device__ __forceinline__ float4 ldg3(const float4* p) {
-  typedef float v3 __attribute__((ext_vector_type(3)));
-  const v3 v =
-      *reinterpret_cast<const __attribute__((address_space(1))) v3*>(reinterpret_cast<uintptr_t>(p));
-  return make_float4(v[0], v[1], v[2], 0.0f);
+// Per-lane load known to be from global memory (a plain vector load, not a
+// flat one, also through a pointer read from memory).
+__device__ __forceinline__ float4 ldg4(const float4* p) {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  const v4 v =
+      *reinterpret_cast<const __attribute__((address_space(1))) v4*>(reinterpret_cast<uintptr_t>(p));
+  return make_float4(v[0], v[1], v[2], v[3]);
 }
-
 
 constexpr double kLog2e = 1.4426950408889634;
 constexpr double kLn2 = 0.6931471805599453;

@@ -129,6 +129,7 @@ enum { kBatchArrNear = 0, kBatchArrFar = 1, kBatchMapNear = 2, kBatchMapFar = 3 
 struct BatchScan {
   const void* pos;         // float2 (mixed) or double2 (FP64), base = visit 0
   const float4* pos4;      // (-2x, -2y, x^2+y^2, 0) by visit
+  const uint2* posh;       // four halves by visit (see arr_far32)
   const double* rows64;    // integer-lag rows of this scan
   const float* rows32;
   int64_t V;

@@ -93,15 +93,19 @@ __device__ __forceinline__ float pairwise_sum(const float (&t)[R]) {
   }
 }
 
+__device__ __forceinline__ void wave_sync() {
+  // a wave's LDS operations complete in order: a compiler barrier at
+  // wavefront scope orders its writes before other lanes' reads
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // ---------------------------------------------------------------------------
-// Arrival query, far region, mixed precision.  Lags [lo, hi) with
-// (hi - lo) % R == 0; window W[q] holds the probe of visit jl - n0 - (R-1) + q
-// as (-2x, -2y, x^2 + y^2), so that a = |e|^2 + |p|^2 - 2 e.p takes three
-// exact FP32 operations (lattice coordinates below 2048).  For degrees <= 3
-// the rows of the next R lags are fetched (scalar loads) while the current R
-// lags are evaluated.
+// Arrival query, far region, mixed precision.
+//
 // Forms of the far series by row range (see DegreeBounds): the full form,
 // the a-form without the exponent's rounding correction, and the folded
 // single exponential P_0 2^{-a RA}.
@@ -161,77 +165,196 @@ __device__ __forceinline__ float series_row32_q(float a, const typename RowSel<M
     return series_f32_q<M>(a, row, t);
 }
 
-// One chunk of R lags n0 .. n0+R-1 against window W (see arr_far32); the R
-// terms of each evaluation point are summed in FP32 by fused multiply-adds
-// (R roundings) and then added to its FP64 accumulator.
-template <int M, int R, bool EDGE, int F>
-__device__ __forceinline__ void arr_chunk32(int n0, int64_t jl, const float4 (&W)[2 * R - 1],
-                                            const float (&ex)[R], const float (&ey)[R],
-                                            const float (&ee)[R],
-                                            const typename RowSel<M, F>::type (&row)[R],
-                                            double (&acc)[R]) {
-  float part[R];
-#pragma unroll
-  for (int s = 0; s < R; ++s) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float4 p = W[r - s + R - 1];
-      const float a = __builtin_fmaf(ex[r], p.x, __builtin_fmaf(ey[r], p.y, ee[r] + p.z));
-      float v = series_row32<M, F>(a, row[s]);
-      if (EDGE) v = (jl + r >= (int64_t)(n0 + s)) ? v : 0.0f;
-      part[r] = (s == 0) ? v : part[r] + v;
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] += (double)part[r];
+// The squared distances of a wave's pairs come from the matrix cores.  A visit
+// is four halves (PosH), (-2x, -2y, sh, sl) with x^2 + y^2 = 4096 sh + sl, and
+//   a = |e|^2 + |p|^2 - 2 e.p = (x_e, y_e, 4096, 1) . (-2x, -2y, sh, sl) + |e|^2
+// is a four-term dot product with a start value: v_mfma_f32_4x4x4_16b_f16, 16
+// independent 4x4 blocks.  It is exact: coordinates are below 2048, so x, y, -2x
+// and -2y (even, below 4096) are half-precision values, sh is at most 2048 and sl
+// in [-2048, 2047], and every partial sum is a whole number below 2^24.
+//
+// Lane l = 4 b + c owns the R visits j = J + 4 R b + R c + t, t < R.  Step D takes,
+// per t, the four earlier visits i = J + 4 R b + t - D - v, v < 4, of block b (the
+// A rows) against the block's four columns c: lane (b, c) gets the pairs of lags
+// D + R c + v, four consecutive lags per lane and step.  The lag now differs
+// between a block's lanes, so the fields of the lag rows that the form needs pass
+// through a ring of 128 lags in LDS, one row per lane and 64 lags at a time
+// (coalesced, prefetched), and are read back by broadcast; lags outside [lo, hi),
+// which the slant adds at both ends, get zero coefficients.  Terms are summed in
+// groups of R consecutive lags from lo in FP32, then in FP64.
+//
+// Bound: VALU issue, in the folded form a product, the exponential (two
+// issues) and a fused multiply-add per pair, and 1/R of a conversion and an FP64
+// addition; the matrix cores run beside it.  512x512 in random order: far region
+// 8.8 ms with a by three FP32 operations per pair from positions in registers,
+// 6.5 ms now, of which the vector ALUs issue for 98% (5.9 instructions per pair).
+template <int M, int F>
+struct FarRow {
+  static constexpr int n = F == kFormFold ? 2 : M <= 1 ? 4 : M <= kMaxA ? 8 : 12;
+};
+constexpr int kRingLags = 128;
+__device__ __forceinline__ float* far_ring() {
+  __shared__ __attribute__((aligned(16))) float ring[4][kRingLags * 12];  // one per wave
+  return ring[threadIdx.x >> 6];
 }
 
-// A visit position of the arrival window (per lane); CAS: through the global
-// address space, for pointers read from memory.
-template <bool CAS>
-__device__ __forceinline__ float4 ldpos(const float4* p) {
-  if constexpr (CAS)
-    return ldg3(p);
-  else
-    return *p;
+// The fields of a lag row, in the order the ring holds them.
+template <int M, int F>
+__device__ __forceinline__ void far_row(const float* __restrict__ row, float (&w)[FarRow<M, F>::n]) {
+  if constexpr (F == kFormFold) {
+    w[0] = row[kR32_RA];
+    w[1] = row[kR32_P0];
+  } else {
+    w[0] = row[kR32_RHI];
+    w[1] = row[kR32_P0];
+    if constexpr (M <= 1) {
+      w[2] = row[M == 0 ? kR32_P0NR : kR32_PA];
+      w[3] = row[kR32_P0N];
+    } else if constexpr (M <= kMaxA) {
+      w[2] = row[kR32_PA];
+      w[3] = row[kR32_P0N];
+      w[4] = row[kR32_PA + 1];
+      w[5] = row[kR32_PA + 2];
+      w[6] = w[7] = 0.0f;
+    } else {
+      w[2] = row[kR32_C];
+      w[3] = row[kR32_RLO];
+#pragma unroll
+      for (int m = 0; m < kM32; ++m) w[4 + m] = row[kR32_P1 + m];
+      w[10] = w[11] = 0.0f;
+    }
+  }
+}
+
+template <int M, int F>
+__device__ __forceinline__ float far_term(float a, const float (&w)[FarRow<M, F>::n]) {
+  if constexpr (F == kFormFold) {
+    return series_row32<M, F>(a, RowF{w[0], w[1]});
+  } else if constexpr (M <= 1) {
+    return series_row32<M, F>(a, RowA{w[0], w[1], w[2], 0.f, 0.f, w[3], w[2], 0.f});
+  } else if constexpr (M <= kMaxA) {
+    return series_row32<M, F>(a, RowA{w[0], w[1], w[2], w[4], w[5], w[3], 0.f, 0.f});
+  } else {
+    float row[kRow32] = {};
+    row[kR32_RHI] = w[0];
+    row[kR32_P0] = w[1];
+    row[kR32_C] = w[2];
+    row[kR32_RLO] = w[3];
+#pragma unroll
+    for (int m = 0; m < kM32; ++m) row[kR32_P1 + m] = w[4 + m];
+    return series_row32<M, F>(a, row);
+  }
+}
+
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Visits p[0] .. p[R - 1] (8-byte alignment); CAS: through the global address
+// space, for pointers read from memory.
+template <int R, bool CAS>
+__device__ __forceinline__ void load_posh(const uint2* p, half4_t (&q)[R]) {
+  static_assert(R == 2 || R == 4, "16-byte loads of two visits");
+  typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(8)));
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < R; i += 2) {
+    u4 v;
+    if constexpr (CAS)
+      v = *reinterpret_cast<const __attribute__((address_space(1))) u4*>(
+          reinterpret_cast<uintptr_t>(p + i));
+    else
+      v = *reinterpret_cast<const u4*>(p + i);
+    q[i] = __builtin_bit_cast(half4_t, u2{v[0], v[1]});
+    q[i + 1] = __builtin_bit_cast(half4_t, u2{v[2], v[3]});
+  }
 }
 
 template <int M, int R, bool EDGE, bool CAS, int F = kFormFull>
-__device__ __forceinline__ void arr_far32(int lo, int hi, const float4* __restrict__ pos, int64_t jl,
-                                          const float (&ex)[R], const float (&ey)[R],
-                                          const float (&ee)[R], const float* __restrict__ rows,
-                                          double (&acc)[R]) {
-  using Row = typename RowSel<M, F>::type;
-  // Two windows alternate: A covers the chunk at n0, B the chunk at n0 + R.
-  // Each shares R - 1 positions with the other, copied in registers; loading
-  // the whole window per chunk instead costs more than those moves.
-  float4 A[2 * R - 1], B[2 * R - 1];
+__device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restrict__ pos, int64_t J,
+                                          const half4_t (&e)[R], const float (&ee)[R],
+                                          const float* __restrict__ rows, double (&acc)[R]) {
+  constexpr int NF = FarRow<M, F>::n;
+  typedef float vec __attribute__((ext_vector_type(NF == 2 ? 2 : 4)));
+  constexpr int NV = NF == 2 ? 1 : NF / 4;
+  const int lane = threadIdx.x & 63, b = lane >> 2, c = lane & 3;
+  vec* const ring = reinterpret_cast<vec*>(far_ring());
+  const int L0 = lo - 3 * R;  // ring entry of lag n: (n - L0) % 128
+  // lane l fetches the row of lag L0 + 64 k + l
+  auto fetch = [&](int k, float(&w)[NF]) {
+    const int n = L0 + 64 * k + lane;
+    far_row<M, F>(rows + (int64_t)max(lo, min(n, hi - 1)) * kRow32, w);
+    const bool in = n >= lo && n < hi;
 #pragma unroll
-  for (int q = 0; q < 2 * R - 1; ++q) A[q] = ldpos<CAS>(pos + (jl - lo - (R - 1) + q));
-  Row cur[R];
+    for (int i = 0; i < NF; ++i) w[i] = in ? w[i] : 0.0f;
+  };
+  auto put = [&](int k, const float(&w)[NF]) {
+    vec* r = ring + ((64 * k + lane) & (kRingLags - 1)) * NV;
 #pragma unroll
-  for (int s = 0; s < R; ++s) cur[s] = fetch_row<M, CAS, F>(rows, lo + s);
-  int n0 = lo;
-  for (; n0 + 2 * R <= hi; n0 += 2 * R) {
-    Row nxt[R];
+    for (int i = 0; i < NV; ++i) {
+      vec x;
 #pragma unroll
-    for (int s = 0; s < R; ++s) nxt[s] = fetch_row<M, CAS, F>(rows, n0 + R + s);
+      for (int q = 0; q < NF / NV; ++q) x[q] = w[i * (NF / NV) + q];
+      r[i] = x;
+    }
+  };
+  const uint2* pa = pos + (J + 4 * R * b - c - L0);  // step s: four visits before per s
+  auto load = [&](int s, half4_t(&q)[R]) { load_posh<R, CAS>(pa - 4 * s, q); };
+  const int i0 = (int)(J + 4 * R * b - L0);
+  auto step = [&](int s, const half4_t(&A)[R]) {
+    f32x4_t a[R];
 #pragma unroll
-    for (int q = R; q < 2 * R - 1; ++q) B[q] = A[q - R];
-    const int64_t b1 = jl - (n0 + R) - (R - 1);
+    for (int t = 0; t < R; ++t)
+      a[t] = __builtin_amdgcn_mfma_f32_4x4x4f16(A[t], e[t], f32x4_t{ee[t], ee[t], ee[t], ee[t]}, 0,
+                                                0, 0);
+    float part[R];
 #pragma unroll
-    for (int q = 0; q < R; ++q) B[q] = ldpos<CAS>(pos + (b1 + q));
-    arr_chunk32<M, R, EDGE, F>(n0, jl, A, ex, ey, ee, cur, acc);
+    for (int v = 0; v < 4; ++v) {
+      // groups of R lags are aligned, so that only they can wrap
+      const int at = ((4 * s + R * c + v / R * R) & (kRingLags - 1)) + v % R;
+      float w[NF];
 #pragma unroll
-    for (int s = 0; s < R; ++s) cur[s] = fetch_row<M, CAS, F>(rows, min(n0 + 2 * R + s, hi - 1));
+      for (int i = 0; i < NV; ++i) {
+        const vec x = ring[at * NV + i];
 #pragma unroll
-    for (int q = R; q < 2 * R - 1; ++q) A[q] = B[q - R];
-    const int64_t b2 = jl - (n0 + 2 * R) - (R - 1);
+        for (int q = 0; q < NF / NV; ++q) w[i * (NF / NV) + q] = x[q];
+      }
 #pragma unroll
-    for (int q = 0; q < R; ++q) A[q] = ldpos<CAS>(pos + (b2 + q));
-    arr_chunk32<M, R, EDGE, F>(n0 + R, jl, B, ex, ey, ee, nxt, acc);
+      for (int t = 0; t < R; ++t) {
+        float x = far_term<M, F>(a[t][v], w);
+        if (EDGE) x = i0 + t - 4 * s - v >= 0 ? x : 0.0f;
+        part[t] = v % R == 0 ? x : part[t] + x;
+        if (v % R == R - 1) acc[t] += (double)part[t];
+      }
+    }
+  };
+  wave_sync();  // the ring's last readers are done
+  {
+    float w0[NF], w1[NF];
+    fetch(0, w0);
+    fetch(1, w1);
+    put(0, w0);
+    put(1, w1);
   }
-  if (n0 < hi) arr_chunk32<M, R, EDGE, F>(n0, jl, A, ex, ey, ee, cur, acc);  // one chunk left
+  wave_sync();
+  const int steps = (hi - L0 + 3) / 4;
+  half4_t A[R], B[R];
+  load(0, A);
+  load(1, B);
+  for (int k = 0; 16 * k < steps; ++k) {
+    float w[NF];
+    fetch(k + 2, w);
+    // an odd count takes one step more, of lags past hi
+    const int s1 = min(16 * k + 16, (steps + 1) & ~1);
+    for (int s = 16 * k; s < s1; s += 2) {
+      step(s, A);
+      load(s + 2, A);
+      step(s + 1, B);
+      load(s + 3, B);
+    }
+    wave_sync();
+    put(k + 2, w);
+    wave_sync();
+  }
 }
 
 template <int M, int R, bool EDGE>
@@ -267,27 +390,26 @@ __device__ __forceinline__ void arr_far64(int lo, int hi, const double2* __restr
 // without the exponent's rounding correction (degrees <= 3 only; the planner
 // starts that range below degree 4).
 template <int R, bool EDGE, bool CAS, bool PLAIN = false>
-__device__ __forceinline__ void arr_far32_seg(int M, int lo, int hi, const float4* __restrict__ pos,
-                                              int64_t jl, const float (&ex)[R], const float (&ey)[R],
-                                              const float (&ee)[R], const float* __restrict__ rows,
+__device__ __forceinline__ void arr_far32_seg(int M, int lo, int hi, const uint2* __restrict__ pos,
+                                              int64_t J, const half4_t (&e)[R], const float (&ee)[R], const float* __restrict__ rows,
                                               double (&acc)[R]) {
   if constexpr (PLAIN) {
     switch (M) {
-      case 0: arr_far32<0, R, EDGE, CAS, kFormPlain>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-      case 1: arr_far32<1, R, EDGE, CAS, kFormPlain>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-      case 2: arr_far32<2, R, EDGE, CAS, kFormPlain>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-      default: arr_far32<3, R, EDGE, CAS, kFormPlain>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
+      case 0: arr_far32<0, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
+      case 1: arr_far32<1, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
+      case 2: arr_far32<2, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
+      default: arr_far32<3, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
     }
     return;
   }
   switch (M) {
-    case 0: arr_far32<0, R, EDGE, CAS>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-    case 1: arr_far32<1, R, EDGE, CAS>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-    case 2: arr_far32<2, R, EDGE, CAS>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-    case 3: arr_far32<3, R, EDGE, CAS>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-    case 4: arr_far32<4, R, EDGE, CAS>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-    case 5: arr_far32<5, R, EDGE, CAS>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
-    default: arr_far32<6, R, EDGE, CAS>(lo, hi, pos, jl, ex, ey, ee, rows, acc); break;
+    case 0: arr_far32<0, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
+    case 1: arr_far32<1, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
+    case 2: arr_far32<2, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
+    case 3: arr_far32<3, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
+    case 4: arr_far32<4, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
+    case 5: arr_far32<5, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
+    default: arr_far32<6, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
   }
 }
 
@@ -317,21 +439,22 @@ __device__ __forceinline__ void seg_range(const DegreeBounds& b, int M, int n_lo
 // visit j go to partial[slot * pstride + j - pj0]: pstride = V and pj0 = 0
 // for a whole-scan query; a visit range keeps only the columns of its tiles.
 template <int R, bool CAS>
-__device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const float4* __restrict__ pos,
+__device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint2* __restrict__ pos,
                                                  const float* __restrict__ rows, int64_t V,
                                                  const DegreeBounds& bnd,
                                                  double* __restrict__ partial, int64_t pstride,
                                                  int64_t pj0) {
   const int lane = threadIdx.x & 63;
-  const int64_t jl = (int64_t)item.tile * (64 * R) + (int64_t)R * lane;
-  float ex[R], ey[R], ee[R];
+  const int64_t J = (int64_t)item.tile * (64 * R), jl = J + (int64_t)R * lane;
+  half4_t e[R];
+  float ee[R];
   double acc[R];
+  load_posh<R, CAS>(pos + jl, e);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const float4 e = pos[jl + r];
-    ex[r] = -0.5f * e.x;
-    ey[r] = -0.5f * e.y;
-    ee[r] = e.z;
+    ee[r] = __builtin_fmaf(4096.0f, (float)e[r][2], (float)e[r][3]);
+    e[r] = half4_t{e[r][0] * (_Float16)-0.5f, e[r][1] * (_Float16)-0.5f, (_Float16)4096.0f,
+                   (_Float16)1.0f};
     acc[r] = 0.0;
   }
   const bool edge = (item.slot_flags & kItemEdge) != 0;
@@ -344,18 +467,18 @@ __device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const floa
     if (lo >= hi) continue;
     const int mid = max(lo, min(hi, bnd.plain));
     if (edge) {
-      if (lo < mid) arr_far32_seg<R, true, CAS>(M, lo, mid, pos, jl, ex, ey, ee, rows, acc);
-      if (mid < hi) arr_far32_seg<R, true, CAS, true>(M, mid, hi, pos, jl, ex, ey, ee, rows, acc);
+      if (lo < mid) arr_far32_seg<R, true, CAS>(M, lo, mid, pos, J, e, ee, rows, acc);
+      if (mid < hi) arr_far32_seg<R, true, CAS, true>(M, mid, hi, pos, J, e, ee, rows, acc);
     } else {
-      if (lo < mid) arr_far32_seg<R, false, CAS>(M, lo, mid, pos, jl, ex, ey, ee, rows, acc);
-      if (mid < hi) arr_far32_seg<R, false, CAS, true>(M, mid, hi, pos, jl, ex, ey, ee, rows, acc);
+      if (lo < mid) arr_far32_seg<R, false, CAS>(M, lo, mid, pos, J, e, ee, rows, acc);
+      if (mid < hi) arr_far32_seg<R, false, CAS, true>(M, mid, hi, pos, J, e, ee, rows, acc);
     }
   }
   if (n_fold < item.n_hi) {
     if (edge)
-      arr_far32<0, R, true, CAS, kFormFold>(n_fold, item.n_hi, pos, jl, ex, ey, ee, rows, acc);
+      arr_far32<0, R, true, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, acc);
     else
-      arr_far32<0, R, false, CAS, kFormFold>(n_fold, item.n_hi, pos, jl, ex, ey, ee, rows, acc);
+      arr_far32<0, R, false, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, acc);
   }
   const int64_t base = (int64_t)(item.slot_flags & kSlotMask) * pstride - pj0;
 #pragma unroll
@@ -414,14 +537,6 @@ struct NearQueue {
   double fv[64 * kNearQ];
 };
 
-__device__ __forceinline__ void near_wave_sync() {
-  // a wave's LDS operations complete in order: a compiler barrier at
-  // wavefront scope orders its writes before other lanes' reads
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int R>
 __device__ __forceinline__ void near_flush(NearQueue& Q, int& cnt, const double* __restrict__ rows64,
                                            const float* __restrict__ rows32, double (&acc)[R]) {
@@ -440,12 +555,12 @@ __device__ __forceinline__ void near_flush(NearQueue& Q, int& cnt, const double*
       Q.fa[base + k] = Q.a[k][lane];
       Q.fn[base + k] = Q.n[k][lane];
     }
-  near_wave_sync();
+  wave_sync();
   for (int e = lane; e < total; e += 64) {
     const int n = Q.fn[e] & 0x1fffffff;
     Q.fv[e] = phi_general_mixed(Q.fa[e], rows64 + (int64_t)n * kRow64, rows32 + (int64_t)n * kRow32);
   }
-  near_wave_sync();
+  wave_sync();
 #pragma unroll
   for (int k = 0; k < kNearQ; ++k)
     if (k < c) {
@@ -454,7 +569,7 @@ __device__ __forceinline__ void near_flush(NearQueue& Q, int& cnt, const double*
 #pragma unroll
       for (int rr = 0; rr < R; ++rr) acc[rr] += (rr == r) ? v : 0.0;  // no indexed registers
     }
-  near_wave_sync();  // the queues and the list are rewritten next
+  wave_sync();  // the queues and the list are rewritten next
   cnt = 0;
 }
 

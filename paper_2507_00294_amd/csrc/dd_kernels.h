@@ -13,12 +13,15 @@ constexpr int kPosPad = 1024;
 // Fills `count` lag rows for lags lambda = f + n, n = n0 .. n0+count-1, into
 // rows64[k * kRow64] and rows32[k * kRow32], k = n - n0 (rows with
 // lambda <= 0 are zero).
+// Visit positions from probe ids, kPosPad zeros before and after each array.
+hipError_t launch_positions(const int32_t* ids, int64_t V, int nx, float2* pos32, double2* pos64,
+                            float4* pos4, uint2* posh, hipStream_t st);
 hipError_t launch_lag_rows(int64_t n0, int64_t count, double f, double kappa, double s2,
                            const GLNodes& gl, double* rows64, float* rows32, hipStream_t st);
 
 struct ArrivalLaunch {
   const void* pos;          // float2 (mixed) or double2 (FP64), base = visit 0
-  const float4* pos4;       // (-2x, -2y, x^2+y^2, 0) by visit, base = visit 0
+  const uint2* posh;        // four halves by visit (see arr_far32), base = visit 0
   const double* rows64;     // integer-lag rows, row n = lag n
   const float* rows32;
   const ArrItem* items;

@@ -2,15 +2,17 @@
 //
 // The hot path is the all-pairs sum of Eq. 6 (Sec. II): every evaluation
 // point adds the pair term of Eqs. 1-4 for every visit that started before it.
-// At scattered points and in FP32 it is a transcendental pair sum, not a
-// contraction, so it runs on the vector ALUs (no MFMA).  The design keeps everything that depends only on the lag
-// (time since a visit started) uniform across a wavefront:
+// At scattered points and in FP32 it is a transcendental pair sum, whose terms
+// run on the vector ALUs:
 //
 //  * arrival query (evaluation point = visit j at its start time): a wave owns
 //    64 R consecutive visits (R per lane) and walks the lag n; the probe of
-//    pair (j, n) is visit j - n, so all 64 R pairs of one step share one lag
-//    row (read into SGPRs) and each lane slides a window of 2R - 1 probe
-//    positions (R loads per R^2 pairs);
+//    pair (j, n) is visit j - n.  In mixed precision the squared distances are
+//    4x4 blocks on the matrix cores and the lag rows pass through LDS
+//    (arr_far32).  In FP64 all 64 R pairs of one step share one lag row (read
+//    into SGPRs) and each lane slides a window of 2R - 1 probe positions (R loads
+//    per R^2 pairs); scans made of rasters take sums of a table instead
+//    (dd_lattice.hip);
 //  * map query in mixed precision (evaluation points = pixels at one time): a
 //    wave owns 64 R pixels and walks the visits; probe position and lag row are
 //    both uniform (SGPR operands), only the pixel coordinates live in VGPRs.
@@ -36,13 +38,35 @@ __global__ void __launch_bounds__(256) k_lag_rows(int64_t n0, int64_t count, dou
   }
 }
 
+// One thread per entry.  Bound: launch latency and the upload of the ids (1 MB
+// for 512x512; three arrays formed on the host and uploaded took 2.3 ms longer).
+__global__ void __launch_bounds__(256) k_positions(const int32_t* __restrict__ ids, int64_t V, int nx,
+                                                   float2* __restrict__ pos32,
+                                                   double2* __restrict__ pos64,
+                                                   float4* __restrict__ pos4,
+                                                   uint2* __restrict__ posh) {
+  const int64_t n = V + 2 * kPosPad;
+  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
+       k += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t v = k - kPosPad;
+    const int id = v >= 0 && v < V ? ids[v] : 0;
+    const int x = id % nx, y = id / nx, s = x * x + y * y;
+    const int sh = (s + 2048) >> 12, sl = s - (sh << 12);
+    const half4_t h{(_Float16)(-2 * x), (_Float16)(-2 * y), (_Float16)sh, (_Float16)sl};
+    pos32[k] = make_float2((float)x, (float)y);
+    pos64[k] = make_double2(x, y);
+    pos4[k] = make_float4((float)(-2 * x), (float)(-2 * y), (float)s, 0.0f);
+    posh[k] = __builtin_bit_cast(uint2, h);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Grid-mapped kernels: wavefront w of block b takes item 4 b + w.  RANGE = 1
 // marks the launches of a visit-range query: the same code as a whole-scan
 // query, instantiated apart so that kernel traces report the two separately.
 template <int R, int RANGE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_arrival_far32(const float4* __restrict__ pos,
+k_arrival_far32(const uint2* __restrict__ pos,
                                                        const float* __restrict__ rows,
                                                        const ArrItem* __restrict__ items, int n_items,
                                                        int64_t V, DegreeBounds bnd,
@@ -198,10 +222,17 @@ hipError_t launch_lag_rows(int64_t n0, int64_t count, double f, double kappa, do
   return hipGetLastError();
 }
 
+hipError_t launch_positions(const int32_t* ids, int64_t V, int nx, float2* pos32, double2* pos64,
+                            float4* pos4, uint2* posh, hipStream_t st) {
+  hipLaunchKernelGGL(k_positions, dim3(grid_for(V + 2 * kPosPad, 4096)), dim3(256), 0, st, ids, V,
+                     nx, pos32, pos64, pos4, posh);
+  return hipGetLastError();
+}
+
 template <int R, int RANGE>
 static void launch_arrival_r(const ArrivalLaunch& L, hipStream_t st, unsigned blocks) {
   if (L.mixed) {
-    hipLaunchKernelGGL((k_arrival_far32<R, RANGE>), dim3(blocks), dim3(256), 0, st, L.pos4,
+    hipLaunchKernelGGL((k_arrival_far32<R, RANGE>), dim3(blocks), dim3(256), 0, st, L.posh,
                        L.rows32, L.items, L.n_items, L.V, L.bounds, L.partial, L.pstride, L.pj0);
   } else {
     hipLaunchKernelGGL((k_arrival_far64<R, RANGE>), dim3(blocks), dim3(256), 0, st,

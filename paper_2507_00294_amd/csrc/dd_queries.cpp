@@ -46,7 +46,7 @@ static dd_status upload(DevBuf& b, const std::vector<T>& h, hipStream_t st) {
 using namespace dd;
 
 // Positions of every visit in pitch units, padded by kPosPad zeros on both
-// sides; integer rows 0 .. V + margin for the current scan parameters.
+// sides, formed on the device from the visits' probe ids.
 dd_status dd_scan::prepare(hipStream_t st) {
   dd_status rc = ensure_device();
   if (rc != DD_OK) return rc;
@@ -55,22 +55,15 @@ dd_status dd_scan::prepare(hipStream_t st) {
   if (dev >= 0 && dev != cur) release_device();
   if (dev == cur) return DD_OK;
   const int64_t n = V + 2 * (int64_t)kPosPad;
-  std::vector<float2> p32(n, make_float2(0.f, 0.f));
-  std::vector<double2> p64(n, make_double2(0.0, 0.0));
-  std::vector<float4> p4(n, make_float4(0.f, 0.f, 0.f, 0.f));
-  for (int64_t v = 0; v < V; ++v) {
-    const int32_t id = ids[v];
-    const double x = id % desc.nx, y = id / desc.nx;
-    p32[kPosPad + v] = make_float2((float)x, (float)y);
-    p64[kPosPad + v] = make_double2(x, y);
-    p4[kPosPad + v] = make_float4((float)(-2 * x), (float)(-2 * y), (float)(x * x + y * y), 0.f);
-  }
-  rc = upload(pos32, p32, st);
+  rc = upload(aux2, ids, st);
   if (rc != DD_OK) return rc;
-  rc = upload(pos64, p64, st);
-  if (rc != DD_OK) return rc;
-  rc = upload(pos4, p4, st);
-  if (rc != DD_OK) return rc;
+  DD_HIP(pos32.ensure(sizeof(float2) * n), "device allocation");
+  DD_HIP(pos64.ensure(sizeof(double2) * n), "device allocation");
+  DD_HIP(pos4.ensure(sizeof(float4) * n), "device allocation");
+  DD_HIP(posh.ensure(sizeof(uint2) * n), "device allocation");
+  DD_HIP(launch_positions(aux2.as<int32_t>(), V, desc.nx, pos32.as<float2>(), pos64.as<double2>(),
+                          pos4.as<float4>(), posh.as<uint2>(), st),
+         "position kernel launch");
   rc = upload(flag, std::vector<unsigned long long>(1, 0ull), st);
   if (rc != DD_OK) return rc;
   seq = 0;
@@ -471,7 +464,7 @@ dd_status run_arrival(dd_scan* s, bool mixed, double* out_dev, const OutFlag& fl
   ArrivalLaunch L{};
   L.pos = mixed ? (const void*)(s->pos32.as<float2>() + kPosPad)
                 : (const void*)(s->pos64.as<double2>() + kPosPad);
-  L.pos4 = s->pos4.as<float4>() + kPosPad;
+  L.posh = s->posh.as<uint2>() + kPosPad;
   L.rows64 = s->rows64.as<double>();
   L.rows32 = s->rows32.as<float>();
   L.V = s->V;
@@ -566,7 +559,7 @@ dd_status dd::launch_range(dd_scan* s, bool mixed, const RangePlan& rp, int64_t 
   ArrivalLaunch L{};
   L.pos = mixed ? (const void*)(s->pos32.as<float2>() + kPosPad)
                 : (const void*)(s->pos64.as<double2>() + kPosPad);
-  L.pos4 = s->pos4.as<float4>() + kPosPad;
+  L.posh = s->posh.as<uint2>() + kPosPad;
   L.rows64 = s->rows64.as<double>();
   L.rows32 = s->rows32.as<float>();
   L.V = s->V;
@@ -1187,6 +1180,7 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
     B.pos = mixed ? (const void*)(s->pos32.as<float2>() + kPosPad)
                   : (const void*)(s->pos64.as<double2>() + kPosPad);
     B.pos4 = s->pos4.as<float4>() + kPosPad;
+    B.posh = s->posh.as<uint2>() + kPosPad;
     B.rows64 = s->rows64.as<double>();
     B.rows32 = s->rows32.as<float>();
     B.V = s->V;
@@ -1213,6 +1207,11 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
           lattice_work(s, C.lat.job, AP.far_pairs, AP.far_flops);
         } else {
           plan_arrival(s, mixed, R, RN, K, AP, C.near, C.far, C.tile_slots, count);
+          // chunk by chunk: items in flight together then read the same lag
+          // rows (32 mixed scans of 16..256 probes a side: 18.9 -> 18.6 ms)
+          std::stable_sort(C.far.begin(), C.far.end(), [](const ArrItem& a, const ArrItem& b) {
+            return a.n_lo < b.n_lo;
+          });
         }
         C.mixed = mixed;
         C.R = R;

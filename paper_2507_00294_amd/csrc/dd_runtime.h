@@ -173,7 +173,7 @@ struct dd_scan {
 
   // Device state (created on first query, on the then-current device).
   int dev = -1;
-  dd::DevBuf pos32, pos64, pos4;    // padded probe positions by visit
+  dd::DevBuf pos32, pos64, pos4, posh;  // padded probe positions by visit
   dd::DevBuf rows64, rows32;        // integer-lag rows n = 0 .. n_rows-1
   int64_t n_rows = 0;
   dd::DevBuf partial, items, aux, aux2, aux3, tmp_out, maprows64, maprows32;
@@ -224,7 +224,7 @@ struct dd_scan {
   std::shared_ptr<dd::StreamEvent> last, own;
 
   void release_device() {
-    for (dd::DevBuf* b : {&pos32, &pos64, &pos4, &rows64, &rows32, &partial, &items, &aux, &aux2, &aux3,
+    for (dd::DevBuf* b : {&pos32, &pos64, &pos4, &posh, &rows64, &rows32, &partial, &items, &aux, &aux2, &aux3,
                           &tmp_out, &maprows64, &maprows32, &sur, &flag})
       b->release();
     sur_state = 0;
