@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(256) k_batch_arrival_near(const BatchScan* __r
 // Map items (mixed precision); NEAR selects the near-band items (per-pair
 // regimes) or the far-region items (degree segments).
 template <int RM, bool NEAR>
-__global__ void __launch_bounds__(256) k_batch_map(const BatchScan* __restrict__ scans,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) k_batch_map(const BatchScan* __restrict__ scans,
                                                    const BatchItem* __restrict__ items,
                                                    int n_items, int* __restrict__ counter) {
   const int lane = threadIdx.x & 63;
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(256) k_batch_map(const BatchScan* __restrict__
     const BatchItem bi = items[it];
     const BatchScan& S = scans[bi.scan];
     const MapItem mi{bi.tile, 0, bi.n_lo, bi.n_hi, bi.slot_flags & kSlotMask, NEAR ? 1 : 0, 0, 0};
-    do_map<RM>(mi, S.map_time, (const float2*)S.pos, S.pos4, S.rows64, S.rows32, (double)S.map_x0,
+    do_map<RM, NEAR>(mi, S.map_time, S.posh, S.pos4, S.rows64, S.rows32, (double)S.map_x0,
                (double)S.map_y0, (double)S.map_step, (double)S.map_step, S.map_w, S.map_h,
                S.map_partial);
   }
@@ -163,8 +163,8 @@ hipError_t launch_batch_map(const BatchScan* scans, const BatchItem* items, int3
 #define DD_LAUNCH_BATCH_MAP(C)                                                                  \
   if (RM == C) {                                                                                \
     if (near)                                                                                   \
-      hipLaunchKernelGGL((k_batch_map<C, true>), dim3(blocks), dim3(256), 0, st, scans, items,  \
-                         n_items, counter);                                                     \
+      hipLaunchKernelGGL((k_batch_map<map_near_r(C), true>), dim3(blocks), dim3(256), 0, st,    \
+                         scans, items, n_items, counter);                                       \
     else                                                                                        \
       hipLaunchKernelGGL((k_batch_map<C, false>), dim3(blocks), dim3(256), 0, st, scans, items, \
                          n_items, counter);                                                     \

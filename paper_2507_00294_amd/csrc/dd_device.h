@@ -78,7 +78,7 @@ struct InvFact {
 // 2^-y for y >= 0 in double precision, y -> 2^-n 2^-f with n = rint(y),
 // f in [-1/2, 1/2]; 2^-f = e^{-f ln 2} by its Taylor polynomial of degree
 // DEG: relative remainder < 1.3e-14 for DEG = 11 (the FP64 path's per-term
-// budget is 1e-13), < 7.4e-9 for DEG = 7 (the mixed path's general form).
+// budget is 1e-13).
 // Returns 0 for y > 1100.
 template <int DEG = 11>
 __device__ __forceinline__ double exp2_neg(double y) {
@@ -194,24 +194,21 @@ struct E1SeriesCoef {
 };
 
 // E1(x) for x > 0 in double precision.  Power series about 0 (A&S 5.1.11)
-// with NSER terms for x <= 2.5; for x > 2.5 the even continued fraction
+// for x <= 2.5.  Above, the FP64 path takes the even continued fraction
 //   E1(x) = e^-x / (x+1 - 1/(x+3 - 4/(x+5 - ...)))   (A&S 5.1.22)
-// truncated after CFA + CFB/x levels and evaluated by the forward three-term
+// truncated after 5 + 90/x levels and evaluated by the forward three-term
 // recurrence of its convergents (no divisions inside the loop).  The depths
-// come from a numerical study against the oracle's E1:
-//   e1_f64  (24 terms, 5 + 90/x, exp degree 11): relative error < 3e-15 for
-//           x <= 2.5, < 1e-14 above;
-//   e1_mixed (18 terms, 4 + 30/x, exp degree 7): < 1e-8, for the mixed path.
-template <int NSER, int CFA, int CFB, int EXPDEG>
-__device__ __forceinline__ double e1_eval(double x) {
+// come from a numerical study against the oracle's E1: relative error < 3e-15
+// for x <= 2.5, < 1e-14 above.
+__device__ __forceinline__ double e1_f64(double x) {
   if (x <= 2.5) {
     constexpr E1SeriesCoef k{};
-    double s = k.c[NSER - 1];
+    double s = k.c[23];
 #pragma unroll
-    for (int n = NSER - 2; n >= 0; --n) s = fma(s, x, k.c[n]);
+    for (int n = 22; n >= 0; --n) s = fma(s, x, k.c[n]);
     return -kEulerGamma - ::log(x) - x * s;
   }
-  const int depth = CFA + (int)((double)CFB / x);
+  const int depth = 5 + (int)(90.0 / x);
   double am1 = 1.0, bm1 = 0.0, a0 = x + 1.0, b0 = 1.0;
   double bj = x + 1.0;
   for (int j = 1; j <= depth; ++j) {
@@ -221,11 +218,65 @@ __device__ __forceinline__ double e1_eval(double x) {
     const double b1 = fma(bj, b0, aj * bm1);
     am1 = a0; bm1 = b0; a0 = a1; b0 = b1;
   }
-  return exp2_neg<EXPDEG>(x * kLog2e) * (b0 / a0);
+  return exp2_neg<11>(x * kLog2e) * (b0 / a0);
 }
 
-__device__ __forceinline__ double e1_f64(double x) { return e1_eval<24, 5, 90, 11>(x); }
-__device__ __forceinline__ double e1_mixed(double x) { return e1_eval<18, 4, 30, 7>(x); }
+// The mixed path's E1: 18 terms of the series (< 1e-8 at 2.5); above 2.5,
+// x e^x E1(x) as a polynomial in t = 5/x - 1 on [-1, 1] (degree 16,
+// interpolating it at the 17 Chebyshev points, formed in 40 digits; within 6e-11)
+// and e^-x to 7e-12.  It costs a wave the same whatever its lanes' x; the
+// continued fraction took as many steps as the wave's smallest x.  Its
+// coefficients are read through the scalar cache where they are used: as
+// literals the compiler kept them in vector registers over the whole loop, and
+// spilled (512 maps of 128x128 over a 64x64 raster scan, near band with every
+// general pair queued: continued fraction 4.6 ms, literals 7.1, this 4.35).
+struct MixedCoef {
+  double e1s[18], e1p[17], exp[10];
+};
+constexpr MixedCoef mixed_coef() {
+  MixedCoef m{};
+  constexpr E1SeriesCoef s{};
+  constexpr InvFact f{};
+  for (int k = 0; k < 18; ++k) m.e1s[k] = s.c[k];
+  for (int k = 0; k < 10; ++k) m.exp[k] = f.v[k];
+  constexpr double p[17] = {
+      0.85211088142366098,     -0.11266528819442803,    0.024605713240480186,
+      -0.0069088690386625989,  0.0022722826450839707,   -0.00083505357622084631,
+      0.00033371406707880869,  -0.00014390868613839555, 6.5053977960993602e-05,
+      -2.5881915064510224e-05, 1.2100089677974122e-05,  -1.5046115680018144e-05,
+      8.5631640067449008e-06,  4.9682094211146733e-06,  -3.2013126951199133e-06,
+      -3.6250416266124557e-06, 2.1882907458483264e-06};
+  for (int k = 0; k < 17; ++k) m.e1p[k] = p[k];
+  return m;
+}
+static __constant__ MixedCoef g_mixed_coef = mixed_coef();
+__device__ __forceinline__ const MixedCoef* mixed_coef_here() {
+  const MixedCoef* c = &g_mixed_coef;
+  asm volatile("" : "+s"(c));  // loads through it stay behind this point
+  return c;
+}
+
+__device__ __forceinline__ double e1_mixed(double x, const MixedCoef* c) {
+  if (x <= 2.5) {
+    double s = ldc(c->e1s + 17);
+#pragma unroll
+    for (int n = 16; n >= 0; --n) s = fma(s, x, ldc(c->e1s + n));
+    return -kEulerGamma - ::log(x) - x * s;
+  }
+  double r = __builtin_amdgcn_rcp(x);  // 1/x, by two Newton steps
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  const double t = fma(5.0, r, -1.0);
+  double p = ldc(c->e1p + 16);
+#pragma unroll
+  for (int k = 15; k >= 0; --k) p = fma(p, t, ldc(c->e1p + k));
+  // e^-x as in exp2_neg, to degree 9
+  const double y = fmin(x * kLog2e, 1100.0), n = __builtin_rint(y), g = (n - y) * kLn2;
+  double e = ldc(c->exp + 9);
+#pragma unroll
+  for (int k = 8; k >= 0; --k) e = fma(e, g, ldc(c->exp + k));
+  return __builtin_ldexp(e, -(int)n) * (p * r);
+}
 
 // Series form in double precision with P_0..P_M read from an FP64 row.
 // The two factors of the term: returns q and sets t = exp(-x1) (term = t q).
@@ -265,7 +316,8 @@ __device__ __forceinline__ double phi_general_f64(double a, const double* __rest
 // dx > 1: E1(x1) - E1(x0) by e1_mixed (the two values differ by more than a
 // factor e, so the difference keeps ~2e-8).
 __device__ __forceinline__ double phi_general_mixed(float a, const double* __restrict__ r64,
-                                                    const float* __restrict__ r32) {
+                                                    const float* __restrict__ r32,
+                                                    const MixedCoef* c) {
   const double ad = (double)a;
   const double z = ad * r64[kR64_C];
   if (z <= kThr64) {
@@ -283,8 +335,26 @@ __device__ __forceinline__ double phi_general_mixed(float a, const double* __res
   const double x1 = ad * r64[kR64_RB1];
   if (x1 > 745.0) return 0.0;
   const double x0 = ad * r64[kR64_RB0];
-  const double e0 = x0 > 745.0 ? 0.0 : e1_mixed(x0);
-  return e1_mixed(x1) - e0;
+  const double e0 = x0 > 745.0 ? 0.0 : e1_mixed(x0, c);
+  return e1_mixed(x1, c) - e0;
+}
+
+// The same for 0.25 < dx <= kMidDx by the whole FP64 row, read as uniform:
+// truncation e^{2 dx} dx^18 / 18! <= 2.3e-9 of the term at dx = 2.
+constexpr float kMidDx = 2.0f;
+__device__ __forceinline__ double phi_mid_mixed(float a, const double* __restrict__ r64,
+                                                const float* __restrict__ r32) {
+  const double z = (double)a * ldc(r64 + kR64_C);
+  double q = ldc(r64 + kR64_P + kM64);
+#pragma unroll
+  for (int m = kM64 - 1; m >= 0; --m) q = fma(q, z, ldc(r64 + kR64_P + m));
+  const float rhi = ldc(r32 + kR32_RHI);
+  const float yh = a * rhi;
+  float yl = __builtin_fmaf(a, rhi, -yh);
+  yl = __builtin_fmaf(a, ldc(r32 + kR32_RLO), yl);
+  float t = __builtin_amdgcn_exp2f(-yh);
+  t = __builtin_fmaf(t, yl * (float)(-kLn2), t);
+  return (double)t * q;
 }
 
 // Mixed-precision series with P_0..P_M from an FP32 row.  `a` is exact

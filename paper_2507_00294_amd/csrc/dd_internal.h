@@ -89,6 +89,10 @@ struct MapItem {
   int32_t slot, near, pad0, pad1;
 };
 
+// Pixels per lane of a map's near-band tile, for R of its far tiles: two at
+// most, for the registers of the general form.
+constexpr int map_near_r(int R) { return R < 2 ? R : 2; }
+
 // Degree segments of the far region: for rows n in [bound[M], bound[M-1]) the
 // series needs P_0..P_M.  bound[-1] is +inf; bound[kMaxSeg] ... bound[0].
 //

@@ -528,18 +528,25 @@ __device__ __forceinline__ void do_arrival_far64(const ArrItem& item, const doub
 // ..., and each lane then adds its own values in the order it queued them
 // (deterministic; the general-form terms of a flush enter the FP64 sum after
 // the series terms of the same lags).
-constexpr int kNearQ = 6;  // queued general-form pairs per lane
+// Q entries per lane; the values overwrite the packed list.
+template <int Q>
 struct NearQueue {
-  float a[kNearQ][64];
-  int32_t n[kNearQ][64];  // lag | (r << 29)
-  float fa[64 * kNearQ];  // the packed list
-  int32_t fn[64 * kNearQ];
-  double fv[64 * kNearQ];
+  float a[Q][64];
+  int32_t n[Q][64];  // lag | (r << 29)
+  union {
+    struct {
+      float a;
+      int32_t n;
+    } in;
+    double v;
+  } list[64 * Q];
 };
 
-template <int R>
-__device__ __forceinline__ void near_flush(NearQueue& Q, int& cnt, const double* __restrict__ rows64,
+template <int R, int Q>
+__device__ __forceinline__ void near_flush(NearQueue<Q>& q, int& cnt,
+                                           const double* __restrict__ rows64,
                                            const float* __restrict__ rows32, double (&acc)[R]) {
+  static_assert(R <= 4, "the queue entry holds r in two bits");
   const int lane = threadIdx.x & 63;
   const int c = cnt;
   int s = c;  // inclusive prefix sum of the queue lengths over the lanes
@@ -550,22 +557,24 @@ __device__ __forceinline__ void near_flush(NearQueue& Q, int& cnt, const double*
   }
   const int base = s - c, total = __shfl(s, 63);
 #pragma unroll
-  for (int k = 0; k < kNearQ; ++k)
+  for (int k = 0; k < Q; ++k)
     if (k < c) {
-      Q.fa[base + k] = Q.a[k][lane];
-      Q.fn[base + k] = Q.n[k][lane];
+      q.list[base + k].in.a = q.a[k][lane];
+      q.list[base + k].in.n = q.n[k][lane] & 0x1fffffff;
     }
   wave_sync();
+  const MixedCoef* coef = mixed_coef_here();
   for (int e = lane; e < total; e += 64) {
-    const int n = Q.fn[e] & 0x1fffffff;
-    Q.fv[e] = phi_general_mixed(Q.fa[e], rows64 + (int64_t)n * kRow64, rows32 + (int64_t)n * kRow32);
+    const float a = q.list[e].in.a;
+    const int64_t n = q.list[e].in.n;
+    q.list[e].v = phi_general_mixed(a, rows64 + n * kRow64, rows32 + n * kRow32, coef);
   }
   wave_sync();
 #pragma unroll
-  for (int k = 0; k < kNearQ; ++k)
+  for (int k = 0; k < Q; ++k)
     if (k < c) {
-      const int r = Q.fn[base + k] >> 29;
-      const double v = Q.fv[base + k];
+      const int r = q.n[k][lane] >> 29 & 3;
+      const double v = q.list[base + k].v;
 #pragma unroll
       for (int rr = 0; rr < R; ++rr) acc[rr] += (rr == r) ? v : 0.0;  // no indexed registers
     }
@@ -594,26 +603,64 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
       ex[r] = e.x;
       ey[r] = e.y;
     }
-    static_assert(R <= 4, "the queue entry holds r in two bits");
-    __shared__ NearQueue queues[4];  // one per wave of the 256-thread block
-    NearQueue& Q = queues[threadIdx.x >> 6];
+    // G lags per step, the next step's positions and row fields in flight; the
+    // queue holds a step's pairs beyond the four that leave it as it is
+    constexpr int G = 8 / R, NP = G + R - 1, kQ = 12;
+    __shared__ NearQueue<kQ> queues[4];  // one per wave of the 256-thread block
+    NearQueue<kQ>& Q = queues[threadIdx.x >> 6];
     int cnt = 0;
-    for (int n = item.n_lo; n < item.n_hi; ++n) {
-      if (__ballot(cnt > kNearQ - R)) near_flush<R>(Q, cnt, rows64, rows32, acc);
-      const float* r32 = rows32 + (int64_t)n * kRow32;
+    float2 p[NP];
+    float c0[G], h0[G];
+    auto fetch = [&](int n) {  // visits jl - n - (G - 1) .. jl - n + R - 1
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int64_t i = jl + r - n;
-        if (i >= 0 && jl + r < V) {
-          const float2 p = pos[i];
-          const float dx = ex[r] - p.x, dy = ey[r] - p.y;
-          const float a = __builtin_fmaf(dy, dy, dx * dx);
-          if (a * ldc(r32 + kR32_C) <= kThr32) {
-            acc[r] += (double)series_f32<kMNear32>(a, r32);
-          } else if (a * ldc(r32 + kR32_RHI) <= kCull32Log2) {
-            Q.a[cnt][lane] = a;
-            Q.n[cnt][lane] = n | (r << 29);
+      for (int q = 0; q < NP; ++q) p[q] = pos[jl - n - (G - 1) + q];
+#pragma unroll
+      for (int s = 0; s < G; ++s) {
+        const float* row = rows32 + (int64_t)min(n + s, item.n_hi - 1) * kRow32;
+        c0[s] = ldc(row + kR32_C);
+        h0[s] = ldc(row + kR32_RHI);
+      }
+    };
+    if (item.n_lo < item.n_hi) fetch(item.n_lo);
+    for (int n = item.n_lo; n < item.n_hi; n += G) {
+      if (__ballot(cnt > kQ - G * R)) near_flush<R>(Q, cnt, rows64, rows32, acc);
+      float a[G][R];
+      float c1[G], h1[G];
+#pragma unroll
+      for (int s = 0; s < G; ++s) {
+        c1[s] = c0[s];
+        h1[s] = h0[s];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const float2 v = p[G - 1 + r - s];
+          const float dx = ex[r] - v.x, dy = ey[r] - v.y;
+          a[s][r] = __builtin_fmaf(dy, dy, dx * dx);
+        }
+      }
+      if (n + G < item.n_hi) fetch(n + G);
+#pragma unroll
+      for (int s = 0; s < G; ++s) {
+        if (n + s >= item.n_hi) break;
+        bool low[R], any = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const bool in = jl + r >= n + s && jl + r < V;
+          low[r] = in && a[s][r] * c1[s] <= kThr32;
+          any = any || low[r];
+          if (in && !low[r] && a[s][r] * h1[s] <= kCull32Log2) {
+            Q.a[cnt][lane] = a[s][r];
+            Q.n[cnt][lane] = (n + s) | (r << 29);
             ++cnt;
+          }
+        }
+        if (__ballot(any)) {
+          float w[kRow32];
+#pragma unroll
+          for (int k = 0; k < kRow32; ++k) w[k] = ldc(rows32 + (int64_t)(n + s) * kRow32 + k);
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const float v = series_f32<kMNear32>(a[s][r], w);
+            acc[r] += low[r] ? (double)v : 0.0;
           }
         }
       }
@@ -651,71 +698,92 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
 // Map query, mixed precision (FP64 maps: dd_gauss.hip).  Pixel pix = tile * 64 R
 // + R lane + r at (X0 + u DX, Y0 + v DY), u = pix % W, v = pix / W, all at the
 // item's time; visit v = K - n.  Pixel and probe coordinates are exact small
-// dyadic numbers (other grids run in FP64), so the three-operation a = |e|^2 +
-// |p|^2 - 2 e.p is exact.
+// dyadic numbers (other grids run in FP64), so the squared distances are exact
+// as in arr_far32: the four visits of lags n .. n + 3 are the rows of all 16
+// blocks of v_mfma_f32_4x4x4_16b_f16, the pixels their columns, and a lane gets
+// its pixel's distances to the four.  A pixel coordinate has up to 12 bits:
+// where it is no half-precision value, a second instruction adds its last bit.
+// Lag rows are uniform (scalar loads).
+//
+// Bound: VALU issue (10.4 instructions per pair; all cycles).  512 maps of 128x128
+// over a 64x64 raster scan, far items: 5.0 ms with the distance by three FP32
+// operations, 4.4 now.
 template <int R>
-__device__ __forceinline__ float map_a32(const float4& p, const float (&ex)[R], const float (&ey)[R],
-                                         const float (&ee)[R], int r) {
-  return __builtin_fmaf(ex[r], p.x, __builtin_fmaf(ey[r], p.y, ee[r] + p.z));
+struct MapPix {
+  half4_t hi[R], lo[R];  // (x, y, 4096, 1), rounded, and what is left of x and y
+  bool wide;             // some `lo` of the grid is not zero
+  float ee[R];
+};
+
+// Lane's row of the visits of lags n .. n + 3 (visits K - n - 3 .. K - n).
+__device__ __forceinline__ half4_t map_visits(const uint2* pos, int64_t K, int n) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(
+      half4_t, *reinterpret_cast<const __attribute__((address_space(1))) u2*>(
+                   reinterpret_cast<uintptr_t>(pos + (K - n - (int)(threadIdx.x & 3)))));
+}
+
+template <int R>
+__device__ __forceinline__ f32x4_t map_dist(const half4_t& visits, const MapPix<R>& px, int r) {
+  f32x4_t a = __builtin_amdgcn_mfma_f32_4x4x4f16(
+      visits, px.hi[r], f32x4_t{px.ee[r], px.ee[r], px.ee[r], px.ee[r]}, 0, 0, 0);
+  if (px.wide) a = __builtin_amdgcn_mfma_f32_4x4x4f16(visits, px.lo[r], a, 0, 0, 0);
+  return a;
 }
 
 template <int M, int R, int U>
-__device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const float4* __restrict__ pos,
-                                          const float* __restrict__ rows, const float (&ex)[R],
-                                          const float (&ey)[R], const float (&ee)[R],
+__device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const uint2* __restrict__ pos,
+                                          const float* __restrict__ rows, const MapPix<R>& px,
                                           double (&acc)[R]) {
   using Row = typename RowSel<M>::type;
   int n = lo;
   if (n + U <= hi) {
     Row cur[U];
-    float4 pc[U];
+    half4_t pc[U / 4];
 #pragma unroll
     for (int s = 0; s < U; ++s) {
       cur[s] = fetch_row<M>(rows, n + s);
-      pc[s] = ldc(pos + (K - (n + s)));
+      if (s % 4 == 0) pc[s / 4] = map_visits(pos, K, n + s);
     }
     for (; n + U <= hi; n += U) {
       Row nxt[U];
-      float4 pn[U];
+      half4_t pn[U / 4];
 #pragma unroll
       for (int s = 0; s < U; ++s) {
-        const int nn = min(n + U + s, hi - 1);
-        nxt[s] = fetch_row<M>(rows, nn);
-        pn[s] = ldc(pos + (K - nn));
-      }
-      float t[R][U], qv[R][U];
-#pragma unroll
-      for (int s = 0; s < U; ++s) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          qv[r][s] = series_row32_q<M>(map_a32<R>(pc[s], ex, ey, ee, r), cur[s], t[r][s]);
+        nxt[s] = fetch_row<M>(rows, min(n + U + s, hi - 1));
+        if (s % 4 == 0) pn[s / 4] = map_visits(pos, K, n + U + s);
       }
       // Groups of four lags in lag order, each summed by an explicit chain
       // of fused multiply-adds: the arithmetic of a pixel is then the same
       // for every tile width and unroll depth.
 #pragma unroll
-      for (int r = 0; r < R; ++r)
+      for (int q = 0; q < U; q += 4) {
+        f32x4_t a[R];
 #pragma unroll
-        for (int q = 0; q < U; q += 4) {
-          float g = t[r][q] * qv[r][q];
-          g = __builtin_fmaf(t[r][q + 1], qv[r][q + 1], g);
-          g = __builtin_fmaf(t[r][q + 2], qv[r][q + 2], g);
-          g = __builtin_fmaf(t[r][q + 3], qv[r][q + 3], g);
+        for (int r = 0; r < R; ++r) a[r] = map_dist<R>(pc[q / 4], px, r);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          float g = 0.0f;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            float t;
+            const float qv = series_row32_q<M>(a[r][s], cur[q + s], t);
+            g = s == 0 ? t * qv : __builtin_fmaf(t, qv, g);
+          }
           acc[r] += (double)g;
         }
-#pragma unroll
-      for (int s = 0; s < U; ++s) {
-        cur[s] = nxt[s];
-        pc[s] = pn[s];
       }
+#pragma unroll
+      for (int s = 0; s < U; ++s) cur[s] = nxt[s];
+#pragma unroll
+      for (int s = 0; s < U / 4; ++s) pc[s] = pn[s];
     }
   }
   for (; n < hi; ++n) {
-    const float4 p = ldc(pos + (K - n));
+    const half4_t p = map_visits(pos, K, n);
     const Row row = fetch_row<M>(rows, n);
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      acc[r] += (double)series_row32<M>(map_a32<R>(p, ex, ey, ee, r), row);
+    for (int r = 0; r < R; ++r) acc[r] += (double)series_row32<M>(map_dist<R>(p, px, r)[0], row);
   }
 }
 
@@ -726,20 +794,24 @@ __device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const float
 // the current ones are evaluated, and read back by broadcast.  The arithmetic
 // and its order are those of map_far32: groups of four lags from lo, each an
 // explicit FMA chain, then single lags.
-__device__ __forceinline__ float4* map_r1_stage() {
-  __shared__ float4 stage[4 * 2 * 64 * 3];  // wave, buffer, lag, (row lo, row hi, position)
-  return stage;
+constexpr int kMapQ = 8;
+// A wave's LDS: the staging of one-pixel tiles (two buffers of 64 lags: row
+// fields, position) or the near band's queues.
+template <int R>
+__device__ __forceinline__ char* map_lds() {
+  constexpr int kStage = R == 1 ? 2 * 64 * 3 * 16 : 0, kQueue = sizeof(NearQueue<kMapQ>);
+  __shared__ __attribute__((aligned(16))) char lds[4][kStage > kQueue ? kStage : kQueue];
+  return lds[threadIdx.x >> 6];
 }
 
 template <int M>
 __device__ __forceinline__ void map_far32_r1(int lo, int hi, int64_t K, const float4* __restrict__ pos,
-                                             const float* __restrict__ rows, const float (&ex)[1],
-                                             const float (&ey)[1], const float (&ee)[1],
-                                             double (&acc)[1]) {
+                                             const float* __restrict__ rows, float ex, float ey,
+                                             float ee, double (&acc)[1]) {
   static_assert(M <= kMaxA, "row staging holds the 8 fields of degrees <= 3");
   if (lo >= hi) return;
   const int lane = threadIdx.x & 63;
-  float4* const st = map_r1_stage() + (threadIdx.x >> 6) * (2 * 64 * 3);
+  float4* const st = reinterpret_cast<float4*>(map_lds<1>());
   // lane i fetches lag base + i (clamped into [lo, hi))
   auto fetch = [&](int base, float4& r0, float4& r1, float4& pp) {
     const int n = min(base + lane, hi - 1);
@@ -758,7 +830,8 @@ __device__ __forceinline__ void map_far32_r1(int lo, int hi, int64_t K, const fl
     const float4* d = st + (buf * 64 + j) * 3;
     const float4 u = d[0], v = d[1], p = d[2];
     const RowA row{u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-    return series_f32a_q<M>(map_a32<1>(p, ex, ey, ee, 0), row, t);
+    const float a = __builtin_fmaf(ex, p.x, __builtin_fmaf(ey, p.y, ee + p.z));
+    return series_f32a_q<M>(a, row, t);
   };
   float4 r0, r1, pp;
   fetch(lo, r0, r1, pp);
@@ -795,49 +868,149 @@ __device__ __forceinline__ void map_far32_r1(int lo, int hi, int64_t K, const fl
 
 template <int R, int U>
 __device__ __forceinline__ void map_far32_u(int M, int lo, int hi, int64_t K,
-                                            const float4* __restrict__ pos,
-                                            const float* __restrict__ rows, const float (&ex)[R],
-                                            const float (&ey)[R], const float (&ee)[R],
+                                            const uint2* __restrict__ pos,
+                                            const float* __restrict__ rows, const MapPix<R>& px,
                                             double (&acc)[R]) {
   switch (M) {
-    case 0: map_far32<0, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 1: map_far32<1, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 2: map_far32<2, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 3: map_far32<3, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 4: map_far32<4, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    case 5: map_far32<5, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
-    default: map_far32<6, R, U>(lo, hi, K, pos, rows, ex, ey, ee, acc); break;
+    case 0: map_far32<0, R, U>(lo, hi, K, pos, rows, px, acc); break;
+    case 1: map_far32<1, R, U>(lo, hi, K, pos, rows, px, acc); break;
+    case 2: map_far32<2, R, U>(lo, hi, K, pos, rows, px, acc); break;
+    case 3: map_far32<3, R, U>(lo, hi, K, pos, rows, px, acc); break;
+    case 4: map_far32<4, R, U>(lo, hi, K, pos, rows, px, acc); break;
+    case 5: map_far32<5, R, U>(lo, hi, K, pos, rows, px, acc); break;
+    default: map_far32<6, R, U>(lo, hi, K, pos, rows, px, acc); break;
   }
 }
 
 template <int R>
 __device__ __forceinline__ void map_far32_seg(int M, int lo, int hi, int64_t K,
-                                              const float4* __restrict__ pos,
-                                              const float* __restrict__ rows, const float (&ex)[R],
-                                              const float (&ey)[R], const float (&ee)[R],
+                                              const uint2* __restrict__ pos,
+                                              const float4* __restrict__ pos4,
+                                              const float* __restrict__ rows, const MapPix<R>& px,
                                               double (&acc)[R]) {
   // One pixel per lane: degrees <= 3 from rows staged in LDS; higher degrees
   // eight lags per step for more loads in flight.  The sum runs over groups
   // of four in lag order either way, so the result does not depend on the
   // tile width.
   if constexpr (R == 1) {
+    const float ex = (float)px.hi[0][0] + (float)px.lo[0][0];
+    const float ey = (float)px.hi[0][1] + (float)px.lo[0][1], ee = px.ee[0];
     switch (M) {
-      case 0: map_far32_r1<0>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
-      case 1: map_far32_r1<1>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
-      case 2: map_far32_r1<2>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
-      case 3: map_far32_r1<3>(lo, hi, K, pos, rows, ex, ey, ee, acc); return;
+      case 0: map_far32_r1<0>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
+      case 1: map_far32_r1<1>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
+      case 2: map_far32_r1<2>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
+      case 3: map_far32_r1<3>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
       default: break;
     }
     const int mid = lo + ((hi - lo) & ~7);
-    map_far32_u<R, 8>(M, lo, mid, K, pos, rows, ex, ey, ee, acc);
+    map_far32_u<R, 8>(M, lo, mid, K, pos, rows, px, acc);
     lo = mid;
   }
-  map_far32_u<R, 4>(M, lo, hi, K, pos, rows, ex, ey, ee, acc);
+  map_far32_u<R, 4>(M, lo, hi, K, pos, rows, px, acc);
 }
 
+// Near band: per-pair choice.  A pixel tile lies together, so pairs of dx up to
+// kMidDx come in whole waves and take the FP64 series in place, its row in
+// scalar registers; the few beyond are queued as in do_arrival_near.  (512 maps
+// of 128x128 over a 64x64 raster scan: 3.6 ms with the general form where it
+// occurs, 4.4 with all of its pairs queued, whose evaluation gathers a row per
+// lane, 2.6 now; final maps of 32 mixed scans of 16..256 probes a side: 1.31,
+// 0.64, 0.48.)
 template <int R>
+__device__ __forceinline__ void map_near32(int lo, int hi, int64_t K, const uint2* __restrict__ pos,
+                                           const double* __restrict__ rows64,
+                                           const float* __restrict__ rows32, const MapPix<R>& px,
+                                           double (&acc)[R]) {
+  const int lane = threadIdx.x & 63;
+  NearQueue<kMapQ>& Q = *reinterpret_cast<NearQueue<kMapQ>*>(map_lds<R>());
+  // lags as differences from lo: queue entries hold 29 bits
+  rows64 += (int64_t)lo * kRow64;
+  rows32 += (int64_t)lo * kRow32;
+  int cnt = 0;
+  // general-form terms have their own sum, so that a pixel's result does not
+  // depend on when its queue is emptied (on the tile width)
+  double gen[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) gen[r] = 0.0;
+  wave_sync();
+  half4_t pn = map_visits(pos, K, lo);
+  float cc[4], rhi[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const float* row = rows32 + (int64_t)min(s, hi - 1 - lo) * kRow32;
+    cc[s] = ldc(row + kR32_C);
+    rhi[s] = ldc(row + kR32_RHI);
+  }
+  for (int n = 0; n < hi - lo; n += 4) {
+    const half4_t p = pn;
+    pn = map_visits(pos, K, lo + n + 4);
+    f32x4_t a[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) a[r] = map_dist<R>(p, px, r);
+    float c0[4], h0[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      c0[s] = cc[s];
+      h0[s] = rhi[s];
+      const float* row = rows32 + (int64_t)min(n + 4 + s, hi - 1 - lo) * kRow32;
+      cc[s] = ldc(row + kR32_C);
+      rhi[s] = ldc(row + kR32_RHI);
+    }
+    // not unrolled (one copy of the flush); the four lags move up in turn
+#pragma unroll 1
+    for (int s = 0; s < min(4, hi - lo - n); ++s) {
+      if (__ballot(cnt > kMapQ - R)) near_flush<R>(Q, cnt, rows64, rows32, gen);
+      const float* row = rows32 + (int64_t)(n + s) * kRow32;
+      bool low[R], mid[R], any_low = false, any_mid = false;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float d = a[r][0], z = d * c0[0];
+        const bool in = d * h0[0] <= kCull32Log2;
+        low[r] = z <= kThr32;
+        mid[r] = !low[r] && in && z <= kMidDx;
+        any_low = any_low || low[r];
+        any_mid = any_mid || mid[r];
+        if (in && z > kMidDx) {
+          Q.a[cnt][lane] = d;
+          Q.n[cnt][lane] = (n + s) | (r << 29);
+          ++cnt;
+        }
+      }
+      if (__ballot(any_low)) {
+        float w[kRow32];
+#pragma unroll
+        for (int k = 0; k < kRow32; ++k) w[k] = ldc(row + k);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const float v = series_f32<kMNear32>(a[r][0], w);
+          acc[r] += low[r] ? (double)v : 0.0;
+        }
+      }
+      if (__ballot(any_mid)) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const double v = phi_mid_mixed(a[r][0], rows64 + (int64_t)(n + s) * kRow64, row);
+          acc[r] += mid[r] ? v : 0.0;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) a[r] = f32x4_t{a[r][1], a[r][2], a[r][3], 0.0f};
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        c0[q] = c0[q + 1];
+        h0[q] = h0[q + 1];
+      }
+    }
+  }
+  if (__ballot(cnt > 0)) near_flush<R>(Q, cnt, rows64, rows32, gen);
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] += gen[r];
+}
+
+// NEAR: a near-band item or a far one.
+template <int R, bool NEAR>
 __device__ __forceinline__ void do_map(const MapItem& item, const MapTime& tm,
-                                       const float2* __restrict__ pos,
+                                       const uint2* __restrict__ pos,
                                        const float4* __restrict__ pos4,
                                        const double* __restrict__ rows64,
                                        const float* __restrict__ rows32, double X0, double Y0,
@@ -847,37 +1020,32 @@ __device__ __forceinline__ void do_map(const MapItem& item, const MapTime& tm,
   const int64_t npix = (int64_t)W * H;
   const int64_t p0 = (int64_t)item.tile * (64 * R) + (int64_t)R * lane;
   double acc[R];
-  float ex[R], ey[R], ee[R];
+  MapPix<R> px;
+  bool wide = false;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int64_t pix = min(p0 + r, npix - 1);
-    ex[r] = (float)(X0 + (double)(pix % W) * DX);
-    ey[r] = (float)(Y0 + (double)(pix / W) * DY);
-    ee[r] = __builtin_fmaf(ey[r], ey[r], ex[r] * ex[r]);
+    const float x = (float)(X0 + (double)(pix % W) * DX);
+    const float y = (float)(Y0 + (double)(pix / W) * DY);
+    const _Float16 xh = (_Float16)x, yh = (_Float16)y;
+    const _Float16 xl = (_Float16)(x - (float)xh), yl = (_Float16)(y - (float)yh);
+    px.hi[r] = half4_t{xh, yh, (_Float16)4096.0f, (_Float16)1.0f};
+    px.lo[r] = half4_t{xl, yl, (_Float16)0.0f, (_Float16)0.0f};
+    px.ee[r] = __builtin_fmaf(y, y, x * x);
+    wide = wide || xl != (_Float16)0.0f || yl != (_Float16)0.0f;
     acc[r] = 0.0;
   }
+  px.wide = __ballot(wide) != 0;
   const double* r64b = rows64 + tm.row_base * kRow64;
   const float* r32b = rows32 + tm.row_base * kRow32;
-  if (item.near) {
-    for (int n = item.n_lo; n < item.n_hi; ++n) {
-      const float2 p = ldc(pos + (tm.K - n));
-      const float* r32 = r32b + (int64_t)n * kRow32;
-      const double* r64 = r64b + (int64_t)n * kRow64;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const float dx = ex[r] - p.x, dy = ey[r] - p.y;
-        const float a = __builtin_fmaf(dy, dy, dx * dx);
-        if (a * ldc(r32 + kR32_C) <= kThr32)
-          acc[r] += (double)series_f32<kMNear32>(a, r32);
-        else if (a * ldc(r32 + kR32_RHI) <= kCull32Log2)
-          acc[r] += phi_general_mixed(a, r64, r32);
-      }
-    }
+  if constexpr (NEAR) {
+    if (item.n_lo < item.n_hi)
+      map_near32<R>(item.n_lo, item.n_hi, tm.K, pos, r64b, r32b, px, acc);
   } else {
     for (int M = tm.bounds.m_max; M >= 0; --M) {
       int lo, hi;
       seg_range(tm.bounds, M, item.n_lo, item.n_hi, lo, hi);
-      if (lo < hi) map_far32_seg<R>(M, lo, hi, tm.K, pos4, r32b, ex, ey, ee, acc);
+      if (lo < hi) map_far32_seg<R>(M, lo, hi, tm.K, pos, pos4, r32b, px, acc);
     }
   }
   double* out = partial + (tm.slot_base + item.slot) * npix;

@@ -39,12 +39,12 @@ hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st);
 
 // A mixed-precision map call (FP64: dd_gauss.h).
 struct MapLaunch {
-  const float2* pos;        // probe positions by visit
+  const uint2* posh;        // four halves by visit (see arr_far32)
   const float4* pos4;       // (-2x, -2y, x^2+y^2, 0) by visit
   const double* rows64;
   const float* rows32;
-  const MapItem* items;
-  int32_t n_items;
+  const MapItem* items;     // the near items first
+  int32_t n_items, n_near;
   const MapTime* times;
   double X0, Y0, DX, DY;    // pixel grid in pitch units
   int32_t W, H;

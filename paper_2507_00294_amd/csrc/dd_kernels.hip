@@ -101,19 +101,18 @@ __global__ void __launch_bounds__(256) k_arrival_near(const void* __restrict__ p
   do_arrival_near<R, MIXED>(items[it], pos_v, rows64, rows32, V, partial, pstride, pj0);
 }
 
-template <int R>
-__global__ void __launch_bounds__(256) k_map(const float2* __restrict__ pos,
-                                             const float4* __restrict__ pos4,
-                                             const double* __restrict__ rows64,
-                                             const float* __restrict__ rows32,
-                                             const MapItem* __restrict__ items, int n_items,
-                                             const MapTime* __restrict__ times, double X0, double Y0,
-                                             double DX, double DY, int W, int H,
-                                             double* __restrict__ partial) {
+// Near-band and far items in launches of their own, each with the registers of
+// its own code.
+template <int R, bool NEAR>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_map(const uint2* __restrict__ pos, const float4* __restrict__ pos4,
+      const double* __restrict__ rows64, const float* __restrict__ rows32,
+      const MapItem* __restrict__ items, int n_items, const MapTime* __restrict__ times, double X0,
+      double Y0, double DX, double DY, int W, int H, double* __restrict__ partial) {
   const int it = blockIdx.x * 4 + wave_id();
   if (it >= n_items) return;
   const MapItem item = items[it];
-  do_map<R>(item, times[item.m], pos, pos4, rows64, rows32, X0, Y0, DX, DY, W, H, partial);
+  do_map<R, NEAR>(item, times[item.m], pos, pos4, rows64, rows32, X0, Y0, DX, DY, W, H, partial);
 }
 
 // ---------------------------------------------------------------------------
@@ -197,7 +196,7 @@ __global__ void __launch_bounds__(256) k_pair_terms(double kappa, double s2, int
       if (af * r32[kR32_C] <= kThr32)
         v = (double)series_f32<kMNear32>(af, r32);
       else
-        v = phi_general_mixed(af, r64, r32);
+        v = phi_general_mixed(af, r64, r32, mixed_coef_here());
     } else {
       v = phi_general_f64(ak, r64);
     }
@@ -271,20 +270,26 @@ hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int R>
+static void launch_map_r(const MapLaunch& L, hipStream_t st) {
+  const int n_far = L.n_items - L.n_near;
+  if (n_far > 0)
+    hipLaunchKernelGGL((k_map<R, false>), dim3((n_far + 3) / 4), dim3(256), 0, st, L.posh, L.pos4,
+                       L.rows64, L.rows32, L.items + L.n_near, n_far, L.times, L.X0, L.Y0, L.DX,
+                       L.DY, L.W, L.H, L.partial);
+  if (L.n_near > 0)
+    hipLaunchKernelGGL((k_map<map_near_r(R), true>), dim3((L.n_near + 3) / 4), dim3(256), 0, st, L.posh,
+                       L.pos4, L.rows64, L.rows32, L.items, L.n_near, L.times, L.X0, L.Y0, L.DX,
+                       L.DY, L.W, L.H, L.partial);
+}
+
 hipError_t launch_map(const MapLaunch& L, hipStream_t st) {
-  if (L.n_items <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((L.n_items + 3) / 4);
-#define DD_LAUNCH_MAP(RR)                                                                        \
-  hipLaunchKernelGGL((k_map<RR>), dim3(blocks), dim3(256), 0, st, L.pos, L.pos4, L.rows64,       \
-                     L.rows32, L.items, L.n_items, L.times, L.X0, L.Y0, L.DX, L.DY, L.W, L.H,    \
-                     L.partial);
   switch (L.R) {
-    case 1: DD_LAUNCH_MAP(1) break;
-    case 2: DD_LAUNCH_MAP(2) break;
-    case 4: DD_LAUNCH_MAP(4) break;
+    case 1: launch_map_r<1>(L, st); break;
+    case 2: launch_map_r<2>(L, st); break;
+    case 4: launch_map_r<4>(L, st); break;
     default: return hipErrorInvalidValue;
   }
-#undef DD_LAUNCH_MAP
   return hipGetLastError();
 }
 

@@ -681,6 +681,7 @@ struct MapPlan {
   double X0 = 0, Y0 = 0, DX = 0, DY = 0;
   double pairs = 0, flops = 0;
   int R = 1;
+  int32_t n_near = 0;
 };
 
 // Pixel coordinates (pitch units) are multiples of 2^-q for some q <= 8 and
@@ -715,6 +716,8 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
   P.R = R;
   const int T = 64 * R;
   const int64_t n_tiles = (npix + T - 1) / T;
+  const int TN = 64 * map_near_r(R);
+  const int64_t near_tiles = (npix + TN - 1) / TN;
   // largest squared distance between any pixel and any probe (bounding boxes)
   const double xa = P.X0, xb = P.X0 + (g->w - 1) * P.DX, ya = P.Y0, yb = P.Y0 + (g->h - 1) * P.DY;
   const double mx = std::max({std::fabs(xa), std::fabs(xb), std::fabs(xa - (s->desc.nx - 1)),
@@ -813,7 +816,7 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
         1, std::min<int64_t>((64 + units - 1) / units, near_len / 32));
     for (int64_t j = 0; j < np; ++j) {
       const int64_t a = nlo[m] + near_len * j / np, e = nlo[m] + near_len * (j + 1) / np;
-      for (int64_t t = 0; t < n_tiles; ++t)
+      for (int64_t t = 0; t < near_tiles; ++t)
         near.push_back(MapItem{(int32_t)t, m, (int32_t)a, (int32_t)e, (int32_t)j, 1, 0, 0});
     }
     int c = 0;
@@ -844,6 +847,7 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
     std::stable_sort(far.begin(), far.end(), longer);
   }
   P.items = near;
+  P.n_near = (int32_t)near.size();
   P.items.insert(P.items.end(), far.begin(), far.end());
 }
 
@@ -929,12 +933,13 @@ dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, 
   DD_HIP(s->partial.ensure(sizeof(double) * (size_t)P.slots * (size_t)P.npix),
          "device allocation");
   MapLaunch L{};
-  L.pos = s->pos32.as<float2>() + kPosPad;
+  L.posh = s->posh.as<uint2>() + kPosPad;
   L.pos4 = s->pos4.as<float4>() + kPosPad;
   L.rows64 = s->maprows64.as<double>();
   L.rows32 = s->maprows32.as<float>();
   L.items = s->aux2.as<MapItem>();
   L.n_items = (int32_t)P.items.size();
+  L.n_near = P.n_near;
   L.times = s->aux3.as<MapTime>();
   L.X0 = P.X0; L.Y0 = P.Y0; L.DX = P.DX; L.DY = P.DY;
   L.W = g->w; L.H = g->h;
@@ -1314,7 +1319,8 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
       partial_total += C->slots * C->npix;
       const double near_w = 6.0;
       for (const MapItem& m : C->items) {
-        const int64_t tile_pix = std::min<int64_t>(64 * RM, C->npix - (int64_t)m.tile * 64 * RM);
+        const int64_t T = 64 * (m.near ? map_near_r(RM) : RM);
+        const int64_t tile_pix = std::min<int64_t>(T, C->npix - (int64_t)m.tile * T);
         const double cost = (double)(m.n_hi - m.n_lo) * tile_pix * (m.near ? near_w : 1.0);
         const int64_t c = (int64_t)cost;
         (m.near ? map_near_items : map_items)

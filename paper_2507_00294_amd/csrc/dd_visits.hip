@@ -426,7 +426,8 @@ __device__ __forceinline__ void map_careful_rows(const MapRow* __restrict__ rows
       double term = (double)(__builtin_amdgcn_exp2f(-yh) * s);
       if (__ballot(far) && far) {
         const double x0 = x1 + dx;
-        term = e1_mixed(x1) - (x0 > 745.0 ? 0.0 : e1_mixed(x0));
+        const MixedCoef* coef = mixed_coef_here();
+        term = e1_mixed(x1, coef) - (x0 > 745.0 ? 0.0 : e1_mixed(x0, coef));
       }
 #pragma unroll
       for (int i = 0; i < kMapPix; ++i)

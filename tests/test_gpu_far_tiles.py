@@ -54,3 +54,51 @@ def test_far_tiles(ora, tmp_path, R):
     finally:
         path.write_text(json.dumps(default))
         dd.tune_load(str(path))
+
+
+# (scan side, pixel spacing in pitches, first pixel, w, h): one row; lattices whose
+# pixel coordinates are half-precision values and, with 12 bits, are not; negative
+# coordinates; far and near bands with remainders of four lags
+GRIDS = [(5, 0.5, 0.0, 37, 1), (12, 1 / 256, 0.0, 61, 45), (15, 1 / 256, 15 - 60 / 256, 70, 66),
+         (24, 0.25, -8.0, 130, 50), (33, 1.0, 3.0, 9, 31)]
+
+
+@pytest.mark.parametrize("R", [1, 2, 4])
+def test_map_tiles(ora, tmp_path, R):
+    import json
+
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2507_00294_amd as dd
+    from paper_2507_00294_amd import workloads as wl
+
+    shapes = {"arch": "gfx950", "arrival_mixed": {"R": 4, "RN": 2, "K": 2048},
+              "arrival_fp64": {"R": 2, "RN": 2, "K": 1024}, "map_mixed": {"R": 4, "K": 4096},
+              "map_fp64": {"R": 1}}
+    path = tmp_path / "tune.json"
+
+    def maps(width):
+        path.write_text(json.dumps(dict(shapes, map_mixed={"R": width, "K": 4096})))
+        dd.tune_load(str(path))
+        out = []
+        for side, px, x0, w, h in GRIDS:
+            spec = wl.ScanSpec(side, side, "random", 1e-9, 1e-6, 0.5e-9, 5e-13, 1.0, seed=side)
+            grid = (x0 * 1e-9, x0 * 1e-9, px * 1e-9, px * 1e-9, w, h)
+            V = spec.n_visits
+            times = [t * spec.tau_v for t in (0.5, 3, 1 + V // 3, V - 0.25, V, 2 * V + 0.5)]
+            scan = dd.Scan(**spec.kwargs())
+            out.append((spec, scan, grid, times,
+                        scan.damage_map(*grid, times, "mixed").cpu().numpy()))
+        return out
+
+    try:
+        widest = maps(4)
+        for (spec, scan, grid, times, got), ref in zip(maps(R), widest):
+            want = oracle_scan(ora, spec, scan).psi_map(*grid, times)
+            assert_close(got, want, spec, "mixed", f"{spec.nx} {grid}, R {R}")
+            assert np.array_equal(got, ref[4]), f"{spec.nx} {grid}, R {R}"
+    finally:
+        path.write_text(json.dumps(shapes))
+        dd.tune_load(str(path))
