@@ -163,90 +163,163 @@ __global__ void __launch_bounds__(256) k_render(RenderArgs A) {
   }
 }
 
-// Maps of at most kMapPixMax pixels, a multiple of 4, into a 4-byte aligned
-// image: one block per map.  The automatic range (the same reduction as
-// k_render_range), then each pixel's colour bin (kept in registers by the
-// thread that colours it) and level (into LDS, for the neighbours), so that
-// every pixel takes one logarithm (k_render takes three with iso-lines),
-// then the colours, four pixels (12 bytes) per thread and step as three
-// 4-byte stores.  The host sends here only psi arrays that start 16-byte
-// aligned; a map holds a multiple of four values, so four pixels load as two
-// 16-byte vectors.  Per pixel the arithmetic is k_render's, so both give the
-// same image.  The iso-line test reads the neighbours' levels at clamped
-// indices and selects: a short-circuit form of it compiled to code whose
-// vertical comparison did not take effect.
-constexpr int kMapPixMax = 16384;
-constexpr int kMapSteps = kMapPixMax / (4 * 256);  // groups of four pixels per thread
+// 256 t of a log scale to single precision, from log2 of the value's ratio to lo:
+//   x = (k + log2 f) / log2(hi / lo) 256,  v / lo = f 2^k,  f in [1, 2).
+// The sum and the quotient are rounded in FP32 and v_log_f32 is off by a few 1e-7
+// at most, so x is within `slack` of the FP64 value; where a decision (a bin or
+// level boundary, 0 or 256) lies closer than that, the pixel takes scale_t.
+// slack >= 1/8 (a range below 0.1%): every pixel does.
+struct QuickLog {
+  double inv_lo;
+  float mul, slack;
+};
+__device__ __forceinline__ QuickLog make_quick(const Scale& s) {
+  const float bits = (float)((1.0 / s.inv) * 1.4426950408889634);  // log2(hi / lo)
+  QuickLog q;
+  q.inv_lo = 1.0 / s.lo;
+  q.mul = 256.0f / bits;
+  q.slack = q.mul * (1e-6f + 2.4e-7f * bits) + 1e-4f;
+  if (!(q.slack < 0.125f) || !(bits < 1024.0f)) q.slack = 1.0f;
+  return q;
+}
+__device__ __forceinline__ float quick_x(double v, const QuickLog& q) {
+  const double r = v * q.inv_lo;
+  const float f = 2.0f * (float)__builtin_amdgcn_frexp_mant(r);  // may round up to 2: log2 is 1
+  return ((float)(__builtin_amdgcn_frexp_exp(r) - 1) + __builtin_amdgcn_logf(f)) * q.mul;
+}
 
-__global__ void __launch_bounds__(256) k_render_map(RenderArgs A, double fac) {
+// Maps of at most kMapPixMax pixels, a multiple of 4, into a 4-byte aligned
+// image: one block per map, of TH threads, each of which keeps its pixels in
+// registers, so that a map is read once.  The automatic range (the same reduction as
+// k_render_range), then each pixel's colour bin (kept in registers by the
+// thread that colours it) and level (into LDS, for the neighbours), then the
+// colours, four pixels (12 bytes) per thread and step as three 4-byte stores.
+// The host sends here only psi arrays that start 16-byte aligned; a map holds a
+// multiple of four values, so four pixels load as two 16-byte vectors.  Every
+// decision is k_render's (quick_x leaves the close ones to scale_t), so both
+// give the same image.  QUAD: rows of a multiple of four pixels, the levels of a
+// thread's four and of their neighbours compared as packed bytes.  Otherwise the
+// iso-line test reads the neighbours' levels at clamped indices and selects: a
+// short-circuit form of it compiled to code whose vertical comparison did not
+// take effect.
+//
+// Bound: HBM, 11 bytes per pixel.  2048 log-scale maps of 128x128 with six
+// levels: 80 us, 4.6 TB/s (two reads, an FP64 logarithm per pixel and levels byte
+// by byte: 155; two reads, FP32 logarithm and packed levels: 114).
+constexpr int kMapPixMax = 16384;  // 4 x 512 threads x kMapSteps
+constexpr int kMapSteps = 8;  // groups of four pixels per thread, kept in registers
+
+template <bool QUAD, int TH>
+__global__ void __launch_bounds__(TH) k_render_map(RenderArgs A, double fac) {
   __shared__ uint32_t tab[256];
-  __shared__ double red[256];
-  __shared__ uint8_t s_lev[kMapPixMax];
+  __shared__ double red[TH / 64];
+  __shared__ uint32_t s_lev4[TH * kMapSteps];
+  const uint8_t* const s_lev = reinterpret_cast<const uint8_t*>(s_lev4);
   const int tid = threadIdx.x;
   const int npix = (int)A.npix, w = A.w, L = A.levels;
   const int64_t m = blockIdx.x;
   const double* p = A.psi + m * A.npix;
-  tab[tid] = A.table.rgb[tid];
+  const double2* p2 = reinterpret_cast<const double2*>(p);
+  if (tid < 256) tab[tid] = A.table.rgb[tid];
   double lo = A.lo, hi = A.hi;
+  // the thread's pixels 4 g .. 4 g + 3, g = tid + TH j
+  double2 px[2 * kMapSteps];
+#pragma unroll
+  for (int j = 0; j < kMapSteps; ++j) {
+    const int g = tid + TH * j;
+    px[2 * j] = px[2 * j + 1] = make_double2(0.0, 0.0);
+    if (4 * g >= npix) continue;
+    px[2 * j] = p2[2 * g];
+    px[2 * j + 1] = p2[2 * g + 1];
+  }
   if (A.autor) {
     double mx = 0.0;
-    for (int i = tid; i < npix; i += 256) {
-      const double v = p[i];
-      if (__builtin_isfinite(v) && v > mx) mx = v;
+#pragma unroll
+    for (int i = 0; i < 2 * kMapSteps; ++i) {
+      if (px[i].x > mx && px[i].x < __builtin_inf()) mx = px[i].x;
+      if (px[i].y > mx && px[i].y < __builtin_inf()) mx = px[i].y;
     }
-    red[tid] = mx;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) mx = fmax(mx, __shfl_xor(mx, d));
+    if ((tid & 63) == 0) red[tid >> 6] = mx;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (tid < s) red[tid] = fmax(red[tid], red[tid + s]);
-      __syncthreads();
-    }
     hi = red[0];
+#pragma unroll
+    for (int i = 1; i < TH / 64; ++i) hi = fmax(hi, red[i]);
     lo = A.log_scale ? fmax(hi * fac, 2.2250738585072014e-308) : 0.0;
   }
   const bool blank = !(hi > lo);
-  // the thread's pixels 4 g .. 4 g + 3, g = tid + 256 j: colour bins packed
-  // four to a register, levels into LDS for the neighbours' tests
+  // colour bins packed four to a register, levels into LDS for the neighbours'
+  // tests
   uint32_t bins[kMapSteps];
   const Scale sc = make_scale(lo, hi, A.log_scale);
+  const QuickLog ql = A.log_scale && !blank ? make_quick(sc) : QuickLog{0.0, 0.0f, 1.0f};
+  const float per_level = (float)L / 256.0f;
 #pragma unroll
   for (int j = 0; j < kMapSteps; ++j) {
-    const int g = tid + 256 * j;
+    const int g = tid + TH * j;
     bins[j] = 0;
     if (blank || 4 * g >= npix) continue;
-    const double2 v01 = *reinterpret_cast<const double2*>(p + 4 * g);
-    const double2 v23 = *reinterpret_cast<const double2*>(p + 4 * g + 2);
-    const double v[4] = {v01.x, v01.y, v23.x, v23.y};
+    const double v[4] = {px[2 * j].x, px[2 * j].y, px[2 * j + 1].x, px[2 * j + 1].y};
+    uint32_t lev = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const double t = scale_t(v[k], sc);
-      bins[j] |= (uint32_t)min(255, (int)(t * 256.0)) << (8 * k);
-      if (L > 0) s_lev[4 * g + k] = (uint8_t)level_of(t, L);
+      // x above 256 or below 0 by less than its error is close to a boundary
+      const float x = quick_x(v[k], ql), xl = x * per_level;
+      const bool in = v[k] > lo && v[k] < hi;
+      int bin = in ? (int)x : v[k] >= hi ? 255 : 0, lv = in ? (int)xl : v[k] >= hi ? L - 1 : 0;
+      const bool close = !(fabsf(x - __builtin_rintf(x)) > ql.slack) ||  // also if not a number
+                         (L > 0 && !(fabsf(xl - __builtin_rintf(xl)) > ql.slack * per_level));
+      if (in && close) {
+        const double t = scale_t(v[k], sc);
+        bin = min(255, (int)(t * 256.0));
+        lv = level_of(t, L);
+      }
+      bins[j] |= (uint32_t)bin << (8 * k);
+      lev |= (uint32_t)lv << (8 * k);
     }
+    if (L > 0) s_lev4[g] = lev;
   }
   __syncthreads();
   uint32_t* out = reinterpret_cast<uint32_t*>(A.rgb + 3 * (m * A.npix));
 #pragma unroll
   for (int j = 0; j < kMapSteps; ++j) {
-    const int g = tid + 256 * j;
+    const int g = tid + TH * j;
     if (4 * g >= npix) continue;
     uint32_t c[4];
-    // coordinates of the group's first pixel, then stepped pixel by pixel
-    int y = (4 * g) / w, x = 4 * g - y * w;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = 4 * g + k;
-      c[k] = tab[blank ? 0 : (bins[j] >> (8 * k)) & 0xFFu];
+    if (QUAD) {
+      uint32_t edge = 0;
       if (!blank && L > 0) {
-        // neighbours read at clamped (in-range) indices, then selected
-        const int lv = s_lev[i];
-        const int lr = s_lev[min(i + 1, npix - 1)], ld = s_lev[min(i + w, npix - 1)];
-        const int er = (x + 1 < w) ? (lr ^ lv) : 0;
-        const int ed = (y + 1 < A.h) ? (ld ^ lv) : 0;
-        c[k] = (er | ed) ? 0xFFFFFFu : c[k];
+        const int w4 = w / 4, last = npix / 4 - 1;
+        const uint32_t lv = s_lev4[g], next = s_lev4[min(g + 1, last)];
+        const uint32_t down = s_lev4[min(g + w4, last)];
+        const uint32_t er = lv ^ (lv >> 8 | next << 24);
+        edge = ((g + 1) % w4 == 0 ? er & 0xFFFFFFu : er) | (g + w4 <= last ? lv ^ down : 0u);
       }
-      if (++x == w) {
-        x = 0;
-        ++y;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        c[k] = tab[blank ? 0 : (bins[j] >> (8 * k)) & 0xFFu];
+        if (edge >> (8 * k) & 0xFFu) c[k] = 0xFFFFFFu;
+      }
+    } else {
+      // coordinates of the group's first pixel, then stepped pixel by pixel
+      int y = (4 * g) / w, x = 4 * g - y * w;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int i = 4 * g + k;
+        c[k] = tab[blank ? 0 : (bins[j] >> (8 * k)) & 0xFFu];
+        if (!blank && L > 0) {
+          // neighbours read at clamped (in-range) indices, then selected
+          const int lv = s_lev[i];
+          const int lr = s_lev[min(i + 1, npix - 1)], ld = s_lev[min(i + w, npix - 1)];
+          const int er = (x + 1 < w) ? (lr ^ lv) : 0;
+          const int ed = (y + 1 < A.h) ? (ld ^ lv) : 0;
+          c[k] = (er | ed) ? 0xFFFFFFu : c[k];
+        }
+        if (++x == w) {
+          x = 0;
+          ++y;
+        }
       }
     }
     // bytes r0 g0 b0 r1 | g1 b1 r2 g2 | b2 r3 g3 b3 (little endian)
@@ -303,7 +376,10 @@ dd_status dd_render_maps(const double* psi, int64_t n, int32_t w, int32_t h,
       reinterpret_cast<uintptr_t>(rgb) % 4 == 0 && reinterpret_cast<uintptr_t>(psi) % 16 == 0) {
     A.autor = autor ? 1 : 0;
     const double fac = autor ? std::pow(10.0, -opt->decades) : 0.0;
-    hipLaunchKernelGGL(k_render_map, dim3((unsigned)n), dim3(256), 0, st, A, fac);
+    const bool quad = w % 4 == 0, wide = npix > 4 * 256 * kMapSteps;
+    auto k = quad ? (wide ? k_render_map<true, 512> : k_render_map<true, 256>)
+                  : (wide ? k_render_map<false, 512> : k_render_map<false, 256>);
+    hipLaunchKernelGGL(k, dim3((unsigned)n), dim3(wide ? 512 : 256), 0, st, A, fac);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "render kernel launch");
     return DD_OK;
