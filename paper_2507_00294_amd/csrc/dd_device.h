@@ -193,43 +193,74 @@ struct E1SeriesCoef {
   }
 };
 
-// E1(x) for x > 0 in double precision.  Power series about 0 (A&S 5.1.11)
-// for x <= 2.5.  Above, the FP64 path takes the even continued fraction
-//   E1(x) = e^-x / (x+1 - 1/(x+3 - 4/(x+5 - ...)))   (A&S 5.1.22)
-// truncated after 5 + 90/x levels and evaluated by the forward three-term
-// recurrence of its convergents (no divisions inside the loop).  The depths
-// come from a numerical study against the oracle's E1: relative error < 3e-15
-// for x <= 2.5, < 1e-14 above.
-__device__ __forceinline__ double e1_f64(double x) {
-  if (x <= 2.5) {
-    constexpr E1SeriesCoef k{};
-    double s = k.c[23];
-#pragma unroll
-    for (int n = 22; n >= 0; --n) s = fma(s, x, k.c[n]);
-    return -kEulerGamma - ::log(x) - x * s;
-  }
-  const int depth = 5 + (int)(90.0 / x);
-  double am1 = 1.0, bm1 = 0.0, a0 = x + 1.0, b0 = 1.0;
-  double bj = x + 1.0;
-  for (int j = 1; j <= depth; ++j) {
-    bj += 2.0;
-    const double aj = -(double)j * (double)j;
-    const double a1 = fma(bj, a0, aj * am1);
-    const double b1 = fma(bj, b0, aj * bm1);
-    am1 = a0; bm1 = b0; a0 = a1; b0 = b1;
-  }
-  return exp2_neg<11>(x * kLog2e) * (b0 / a0);
-}
-
-// The mixed path's E1: 18 terms of the series (< 1e-8 at 2.5); above 2.5,
-// x e^x E1(x) as a polynomial in t = 5/x - 1 on [-1, 1] (degree 16,
-// interpolating it at the 17 Chebyshev points, formed in 40 digits; within 6e-11)
-// and e^-x to 7e-12.  It costs a wave the same whatever its lanes' x; the
-// continued fraction took as many steps as the wave's smallest x.  Its
-// coefficients are read through the scalar cache where they are used: as
+// E1(x) for x > 0.  Power series about 0 (A&S 5.1.11) for x <= 2.5; above,
+// x e^x E1(x) as a polynomial in t = 5/x - 1 on [-1, 1], interpolating it at the
+// Chebyshev points (formed in 50 digits), times e^-x / x.  It costs a wave the
+// same whatever its lanes' x; the even continued fraction (A&S 5.1.22), 5 + 90/x
+// levels in double precision, took as many as the wave's smallest x (25600
+// visits of a measured raster list, FP64 arrival: 1.21 ms, 1.08 with this).  Relative errors:
+//   e1_f64: 24 terms, degree 27, e^-x by degree 11: < 3e-15 for x <= 2.5, < 1e-14
+//           above;
+//   e1_mixed: 18 terms, degree 16, e^-x by degree 9: < 1e-8 at 2.5, < 1e-10 above.
+// The coefficients are read through the scalar cache where they are used: as
 // literals the compiler kept them in vector registers over the whole loop, and
 // spilled (512 maps of 128x128 over a 64x64 raster scan, near band with every
 // general pair queued: continued fraction 4.6 ms, literals 7.1, this 4.35).
+struct E1Coef {
+  double e1s[24], e1p[28], exp[12];
+};
+constexpr E1Coef e1_coef64() {
+  E1Coef m{};
+  constexpr E1SeriesCoef s{};
+  constexpr InvFact f{};
+  for (int k = 0; k < 24; ++k) m.e1s[k] = s.c[k];
+  for (int k = 0; k < 12; ++k) m.exp[k] = f.v[k];
+  constexpr double p[28] = {
+      0.85211088142366054,     -0.11266528854196572,    0.024605713456218568,
+      -0.0069088524922641479,  0.0022722723724399197,   -0.00083528067421447471,
+      0.00033385513528776421,  -0.00014252919697465435, 6.4195520285397357e-05,
+      -3.0236875189450238e-05, 1.4826575324334165e-05,  -7.5024747375011427e-06,
+      3.7373281248863727e-06,  -1.9692852600550294e-06, 1.6580230589741762e-06,
+      -9.9746100573012787e-07, -8.5413108906820068e-07, 6.3860956694177865e-07,
+      2.0636461768882854e-06,  -1.4255097338348177e-06, -2.0772284268090886e-06,
+      1.4497712328551951e-06,  1.5337473362622037e-06,  -1.0651451258185052e-06,
+      -6.423368262048952e-07,  4.4610121677846819e-07,  1.3207590773136581e-07,
+      -9.1218064392828507e-08};
+  for (int k = 0; k < 28; ++k) m.e1p[k] = p[k];
+  return m;
+}
+static __constant__ E1Coef g_e1_coef64 = e1_coef64();
+
+// NS terms of the series, degree NP of the polynomial and NE of e^-x.
+template <int NS, int NP, int NE, typename C>
+__device__ __forceinline__ double e1_eval(double x, const C* c) {
+  if (x <= 2.5) {
+    double s = ldc(c->e1s + NS - 1);
+#pragma unroll
+    for (int n = NS - 2; n >= 0; --n) s = fma(s, x, ldc(c->e1s + n));
+    return -kEulerGamma - ::log(x) - x * s;
+  }
+  double r = __builtin_amdgcn_rcp(x);  // 1/x, by two Newton steps
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  const double t = fma(5.0, r, -1.0);
+  double p = ldc(c->e1p + NP);
+#pragma unroll
+  for (int k = NP - 1; k >= 0; --k) p = fma(p, t, ldc(c->e1p + k));
+  // e^-x as in exp2_neg
+  const double y = fmin(x * kLog2e, 1100.0), n = __builtin_rint(y), g = (n - y) * kLn2;
+  double e = ldc(c->exp + NE);
+#pragma unroll
+  for (int k = NE - 1; k >= 0; --k) e = fma(e, g, ldc(c->exp + k));
+  return __builtin_ldexp(e, -(int)n) * (p * r);
+}
+
+__device__ __forceinline__ double e1_f64(double x) {
+  const E1Coef* c = &g_e1_coef64;
+  asm volatile("" : "+s"(c));  // loads through it stay behind this point
+  return e1_eval<24, 27, 11>(x, c);
+}
+
 struct MixedCoef {
   double e1s[18], e1p[17], exp[10];
 };
@@ -257,25 +288,7 @@ __device__ __forceinline__ const MixedCoef* mixed_coef_here() {
 }
 
 __device__ __forceinline__ double e1_mixed(double x, const MixedCoef* c) {
-  if (x <= 2.5) {
-    double s = ldc(c->e1s + 17);
-#pragma unroll
-    for (int n = 16; n >= 0; --n) s = fma(s, x, ldc(c->e1s + n));
-    return -kEulerGamma - ::log(x) - x * s;
-  }
-  double r = __builtin_amdgcn_rcp(x);  // 1/x, by two Newton steps
-  r = fma(fma(-x, r, 1.0), r, r);
-  r = fma(fma(-x, r, 1.0), r, r);
-  const double t = fma(5.0, r, -1.0);
-  double p = ldc(c->e1p + 16);
-#pragma unroll
-  for (int k = 15; k >= 0; --k) p = fma(p, t, ldc(c->e1p + k));
-  // e^-x as in exp2_neg, to degree 9
-  const double y = fmin(x * kLog2e, 1100.0), n = __builtin_rint(y), g = (n - y) * kLn2;
-  double e = ldc(c->exp + 9);
-#pragma unroll
-  for (int k = 8; k >= 0; --k) e = fma(e, g, ldc(c->exp + k));
-  return __builtin_ldexp(e, -(int)n) * (p * r);
+  return e1_eval<18, 16, 9>(x, c);
 }
 
 // Series form in double precision with P_0..P_M read from an FP64 row.

@@ -18,7 +18,9 @@ namespace dd {
 
 constexpr int kVisTile = 256;     // evaluation points per tile (one per thread)
 constexpr int kVisStage = 256;    // visits staged in LDS at a time
-constexpr int kVisMaxSlots = 32;  // visit chunks (partial sums) per tile at most
+// Visit chunks (partial sums) per tile at most.  25600 visits: 32 chunks, 1300
+// items for the 768 blocks that fit the chip, 1.08 ms; 64 chunks 1.01.
+constexpr int kVisMaxSlots = 64;
 
 // Map grid (pixel (u, v) at (x0 + u dx, y0 + v dy), w columns).
 struct VisGrid {

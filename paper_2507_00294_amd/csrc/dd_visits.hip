@@ -34,6 +34,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "dd_device.h"
 #include "dd_visit_rows.h"
@@ -156,9 +157,8 @@ __device__ __noinline__ double far_or_log_term(double x1, double dx, double q) {
 }
 
 // The term of a pair that passed the cull (x1 <= 745); active = the pair
-// contributes at all.  The linear near form, almost every pair of a long
-// scan, runs with the node count the wave's lanes need at most, so that
-// the branch is the same for the whole wave.
+// contributes at all.  The linear near form runs with the node count the wave's
+// lanes need at most, so that the branch is the same for the whole wave.
 template <bool MIXED>
 __device__ __forceinline__ double pair_term(bool active, double x1, double dx, double q) {
   const bool lin = active && dx <= 1.0 && q <= 1.0 && x1 > 0.0;
@@ -552,21 +552,31 @@ __attribute__((amdgpu_waves_per_eu(3, 8))) void k_visit_map(
 }
 
 // ---------------------------------------------------------------------------
-// Arrival query: the bulk form.
+// Arrival query: the bulk forms, for small u = db/b1 and v = x1 u (or their
+// halves, delta and X), where a short polynomial replaces the integral.  A
+// wave whose contributing pairs of a visit are all in the domain takes it (98%
+// of the visit steps of a long raster list); otherwise the general form
+// (pair_term).
 //
-// With u = db/b1 and v = x1 u (so q = u/(1-u), dx = x1 q = v/(1-u)), the
-// term is e^{-x1} u F(u, v) with
+// FP64: about the middle of the visit's interval of b, bm = (b0 + b1)/2, with
+// b = bm (1 + delta tau), delta = db / (2 bm), x = a/bm and X = x delta,
+//   term = delta e^{-x} int_-1^1 exp(x delta tau / (1 + delta tau)) / (1 + delta tau)
+//        = 2 delta e^{-x} sum_k L_2k(x) delta^2k / (2k + 1):
+// the integrand is the generating function of the Laguerre polynomials at
+// t = -delta tau, whose odd powers cancel.  On delta <= 2^-9, X <= 2^-5 the sum
+// to k = 3, written in powers of X, is within 1e-15 of the term (its terms
+// beyond, and delta^5 X and delta^6, are dropped): 17 operations, and bm needs
+// one reciprocal per pair.  (Expanded at b1 instead, in u and v to degrees 5,5,5,
+// 4,3,2,1, 1e-14 on half the domain: 31 operations and 43 constants in LDS;
+// 25600 visits of a measured raster list 1.34 ms, with this 1.21.)
+//
+// Mixed, in FP32: with u and v (so q = u/(1-u), dx = x1 q = v/(1-u)), the term
+// is e^{-x1} u F(u, v) with
 //   F = int_0^1 exp(-v s/(1-u)) / (1 - u(1-s)) ds = sum_{m,n} C_{m,n} v^m u^n,
 //   C_{m,n} = (-1)^m sum_{k=0..n} binom(m+n-k-1, n-k) k! / (m+k+1)!
 // ((1 - u(1-s))^-1 and (1-u)^-m expanded in u, the exponential in v, and
-// int_0^1 s^m (1-s)^k ds = m! k! / (m+k+1)!).  It needs one reciprocal per
-// pair (1/b1), and for small u and v a short polynomial: on u <= 2^-8,
-// v <= 2^-5 (FP64) the degrees in u for m = 0..6 are 5,5,5,4,3,2,1 with a
-// truncation below 1e-14 of the term; on u <= 2^-6, v <= 2^-5 (mixed, in
-// FP32) the degrees for m = 0..3 are 4,3,3,1, below 2e-8.  A wave whose
-// contributing pairs of a visit are all in that domain takes this form (98%
-// of the visit steps of a long raster list); otherwise the general form
-// (pair_term).
+// int_0^1 s^m (1-s)^k ds = m! k! / (m+k+1)!); on u <= 2^-6, v <= 2^-5 the degrees
+// in u for m = 0..3 are 4,3,3,1, below 2e-8.
 constexpr double binom_d(int a, int b) {
   if (b == 0) return 1.0;
   if (a < b || a < 0) return 0.0;
@@ -589,7 +599,7 @@ struct BulkCoef {
       }
   }
 };
-constexpr double kBulkU64 = 1.0 / 256, kBulkV64 = 1.0 / 32;
+constexpr double kBulkD64 = 1.0 / 512, kBulkX64 = 1.0 / 32;
 constexpr float kBulkU32 = 1.0f / 64, kBulkV32 = 1.0f / 32;
 
 // F(u, v) by Horner in u per power of v, then in v.
@@ -609,38 +619,6 @@ __device__ __forceinline__ T bulk_f(T u, T v) {
   return acc;
 }
 
-// The FP64 bulk's 43 constants (F's coefficients, rows of kBulkStride, and
-// the degree-9 exp2 interpolant) do not fit the scalar registers beside the
-// kernel's own; the arrival kernel keeps them in LDS (kBulkLds doubles) and
-// reads them as wave-uniform loads.  Same values, same operations.
-constexpr int kBulkStride = 6, kBulkE = 7 * kBulkStride, kBulkLds = kBulkE + 10;
-__device__ __forceinline__ double bulk_const64(int k) {
-  constexpr BulkCoef C{};
-  constexpr Exp2Cheb<9> E{};
-  if (k >= kBulkE) return E.c[k - kBulkE];
-  return C.c[k / kBulkStride][k % kBulkStride];
-}
-__device__ __forceinline__ double bulk_term64_lds(double x1, double u, double v,
-                                                  const double* __restrict__ bc) {
-  constexpr int deg[7] = {5, 5, 5, 4, 3, 2, 1};
-  double g = 0;
-#pragma unroll
-  for (int m = 6; m >= 0; --m) {
-    double cm = bc[m * kBulkStride + deg[m]];
-#pragma unroll
-    for (int n = deg[m] - 1; n >= 0; --n) cm = cm * u + bc[m * kBulkStride + n];
-    g = (m == 6) ? cm : g * v + cm;
-  }
-  // 2^-y, y <= 1000 log2(e), by exp2_neg9's interpolant without its clamp
-  const double y = x1 * kLog2e;
-  const double mm = __builtin_rint(-y);
-  const double h = -y - mm;
-  double p = bc[kBulkE + 9];
-#pragma unroll
-  for (int k = 8; k >= 0; --k) p = fma(p, h, bc[kBulkE + k]);
-  return __builtin_ldexp(p, (int)mm) * (u * g);
-}
-
 // The mixed bulk term e^{-x1} u F(u, v) (x1 <= cull).
 __device__ __forceinline__ double bulk_term32(double x1, double u, double v) {
   const double y = x1 * kLog2e;
@@ -653,8 +631,8 @@ __device__ __forceinline__ double bulk_term32(double x1, double u, double v) {
 }
 
 // One arrival pair (point at (px, py) at time pt, visit v): the quantities
-// of both forms and whether the pair contributes (act) and lies in the bulk
-// domain.
+// of the general form (and, mixed, of the bulk form), and whether the pair
+// contributes (act) and lies in the bulk domain.
 template <bool MIXED>
 struct ArrPair {
   double x1, u, w, b0, db;
@@ -674,17 +652,61 @@ struct ArrPair {
     u = db * r1;
     w = x1 * u;
     act = started && x1 <= cull;
-    bulk = MIXED ? ((float)u <= kBulkU32 && (float)w <= kBulkV32)
-                 : (u <= kBulkU64 && w <= kBulkV64);
+    bulk = MIXED && (float)u <= kBulkU32 && (float)w <= kBulkV32;
   }
   // Lanes outside the domain (idle, culled) may compute a non-finite value;
   // the select drops it.
-  __device__ __forceinline__ double bulk_value(const double* __restrict__ bc) const {
-    double t;
-    if constexpr (MIXED)
-      t = bulk_term32(x1, u, w);
-    else
-      t = bulk_term64_lds(x1, u, w, bc);
+  __device__ __forceinline__ double bulk_value() const {
+    const double t = bulk_term32(x1, u, w);
+    return act ? t : 0.0;
+  }
+};
+
+// The FP64 bulk form of a pair: `out` if the pair contributes and is outside
+// its domain (a visit still on included).  hdb = th4 v.w / 2.
+struct BulkPair {
+  double x, d, X;
+  bool act, out;
+  __device__ __forceinline__ void setup(const double4 v, double hdb, double px, double py,
+                                        double pt, bool live, double is2, double th4) {
+    const double lag = pt - v.z;
+    const double bm = fma(th4, fma(-0.5, v.w, lag), 2.0);
+    // 1/bm: the hardware estimate (2^-23 at least) and one cubic step
+    double r = __builtin_amdgcn_rcp(bm);
+    const double e = fma(-bm, r, 1.0);
+    r = fma(r, fma(e, e, e), r);
+    const double ex = px - v.x, ey = py - v.y;
+    x = fma(ex, ex, ey * ey) * (is2 * r);
+    d = hdb * r;
+    X = x * d;
+    // beyond the cull: x1 = x bm / b1 > 745 when x > 748 and d <= 2^-9
+    // (& and |: no branches)
+    const bool started = live & (lag > 0.0);
+    act = started & (x <= 748.0);
+    out = started & !((lag >= v.w) & (d <= kBulkD64) & ((X <= kBulkX64) | (x > 748.0)));
+  }
+  __device__ __forceinline__ double value() const {
+    constexpr Exp2Cheb<9> E{};
+    const double d2 = d * d;
+    const double c0 = fma(fma(d2, 1.0 / 5, 1.0 / 3), d2, 1.0);
+    const double c1 = d * fma(d2, -4.0 / 5, -2.0 / 3);
+    const double c2 = fma(fma(d2, 15.0 / 14, 3.0 / 5), d2, 1.0 / 6);
+    const double c3 = d * fma(d2, -10.0 / 21, -2.0 / 15);
+    const double c4 = fma(d2, 5.0 / 56, 1.0 / 120);
+    double g = fma(X, 1.0 / 5040, d * (-1.0 / 140));
+    g = fma(g, X, c4);
+    g = fma(g, X, c3);
+    g = fma(g, X, c2);
+    g = fma(g, X, c1);
+    g = fma(g, X, c0);
+    // 2 2^-y by exp2_neg9's interpolant without its clamp
+    const double y = x * kLog2e;
+    const double mm = __builtin_rint(-y);
+    const double h = -y - mm;
+    double p = 2.0 * E.c[9];
+#pragma unroll
+    for (int k = 8; k >= 0; --k) p = fma(p, h, 2.0 * E.c[k]);
+    const double t = __builtin_ldexp(p, (int)mm) * (d * g);
     return act ? t : 0.0;
   }
 };
@@ -692,12 +714,17 @@ struct ArrPair {
 // The term of one pair: the bulk form if the wave's contributing pairs of
 // this visit are all in its domain, else the general form.
 template <bool MIXED>
-__device__ __forceinline__ double arr_pair_term(const double4 v, double px, double py, double pt,
-                                                bool live, double is2, double th4,
-                                                const double* __restrict__ bc) {
+__device__ __forceinline__ double arr_pair_term(const double4 v, double hdb, double px, double py,
+                                                double pt, bool live, double is2, double th4) {
+  if constexpr (!MIXED) {
+    BulkPair b;
+    b.setup(v, hdb, px, py, pt, live, is2, th4);
+    if (!__ballot(b.out)) return b.value();
+  }
   ArrPair<MIXED> pr;
   pr.setup(v, px, py, pt, live, is2, th4);
-  if (!__ballot(pr.act && !pr.bulk)) return pr.bulk_value(bc);
+  if constexpr (MIXED)
+    if (!__ballot(pr.act && !pr.bulk)) return pr.bulk_value();
   const double q = pr.db / pr.b0;
   return pair_term<MIXED>(pr.act, pr.x1, pr.x1 * q, q);
 }
@@ -706,17 +733,14 @@ __device__ __forceinline__ double arr_pair_term(const double4 v, double px, doub
 // staged 256 at a time in LDS.  Visits are in start order, so the first one
 // that starts at or after the tile's latest time ends the item for the
 // whole block.
-// FP64: held to 168 VGPRs (3 waves per SIMD; the constants in LDS took it to
-// 182 and 2 waves unhinted).
 template <bool MIXED>
 __global__ __launch_bounds__(kVisTile)
 __attribute__((amdgpu_waves_per_eu(MIXED ? 1 : 3, 8))) void k_visit_arrival(
     const VisList* __restrict__ lists, const VisTile* __restrict__ tiles,
     const VisItem* __restrict__ items, int64_t n_items, double* __restrict__ partial) {
   __shared__ double4 s_v[kVisStage];
-  __shared__ double s_bc[MIXED ? 1 : kBulkLds];
+  __shared__ double s_d[MIXED ? 1 : kVisStage];  // half the visit's width in b
   const int lane = threadIdx.x;
-  if (!MIXED && lane < kBulkLds) s_bc[lane] = bulk_const64(lane);  // read after the stage barrier
   for (int64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
     const VisItem item = items[it];
     const VisTile tile = tiles[item.tile];
@@ -737,27 +761,43 @@ __attribute__((amdgpu_waves_per_eu(MIXED ? 1 : 3, 8))) void k_visit_arrival(
       const int64_t left = item.v0 + item.nv - v0;
       const int nk = left < kVisStage ? (int)left : kVisStage;
       __syncthreads();  // the previous stage is no longer read
-      if (lane < nk) s_v[lane] = vis[v0 + lane];
+      if (lane < nk) {
+        const double4 v = vis[v0 + lane];
+        s_v[lane] = v;
+        if (!MIXED) s_d[lane] = 0.5 * th4 * v.w;
+      }
       __syncthreads();
       int j = 0;
-      // four visits at a time (four independent chains per lane) while all
-      // four start before the tile's latest time and the wave's pairs are
-      // all in the bulk domain
-      for (; j + 4 <= nk && s_v[j + 3].z < tile.tmax; j += 4) {
-        ArrPair<MIXED> pr[4];
+      // U visits at a time (independent chains per lane) while all of them
+      // start before the tile's latest time and the wave's pairs are all in the
+      // bulk domain
+      constexpr int U = 4;
+      for (; j + U <= nk && s_v[j + U - 1].z < tile.tmax; j += U) {
+        std::conditional_t<MIXED, ArrPair<true>, BulkPair> pr[U];
         bool out = false;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          pr[i].setup(s_v[j + i], px, py, pt, live, is2, th4);
-          out |= pr[i].act && !pr[i].bulk;
+        for (int i = 0; i < U; ++i) {
+          if constexpr (MIXED) {
+            pr[i].setup(s_v[j + i], px, py, pt, live, is2, th4);
+            out |= pr[i].act && !pr[i].bulk;
+          } else {
+            pr[i].setup(s_v[j + i], s_d[j + i], px, py, pt, live, is2, th4);
+            out |= pr[i].out;
+          }
         }
         if (!__ballot(out)) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sum += pr[i].bulk_value(s_bc);
+          for (int i = 0; i < U; ++i) {
+            if constexpr (MIXED)
+              sum += pr[i].bulk_value();
+            else
+              sum += pr[i].value();
+          }
         } else {
 #pragma unroll 1
-          for (int i = 0; i < 4; ++i)
-            sum += arr_pair_term<MIXED>(s_v[j + i], px, py, pt, live, is2, th4, s_bc);
+          for (int i = 0; i < U; ++i)
+            sum += arr_pair_term<MIXED>(s_v[j + i], MIXED ? 0.0 : s_d[j + i], px, py, pt, live,
+                                        is2, th4);
         }
       }
       for (; j < nk; ++j) {
@@ -766,7 +806,7 @@ __attribute__((amdgpu_waves_per_eu(MIXED ? 1 : 3, 8))) void k_visit_arrival(
           done = true;  // uniform: no later visit starts before any point
           break;
         }
-        sum += arr_pair_term<MIXED>(v, px, py, pt, live, is2, th4, s_bc);
+        sum += arr_pair_term<MIXED>(v, MIXED ? 0.0 : s_d[j], px, py, pt, live, is2, th4);
       }
     }
     if (live) partial[tile.pbase + (int64_t)item.slot * kVisTile + lane] = sum;

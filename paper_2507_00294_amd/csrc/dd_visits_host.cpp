@@ -7,7 +7,7 @@
 // or, for the batch calls, many: every tile names its list, whose
 // descriptor (visits, order, output, grid and times, scaling) the kernels
 // read.  Evaluation points go in tiles of 256 (one thread each); visits in
-// chunks of K (a multiple of 256, at most 32 chunks per list).  A work item
+// chunks of K (a multiple of 256, at most 64 chunks per list).  A work item
 // is one tile against one chunk, written to a partial-sum slot of its own,
 // and the slots are summed in a fixed order, so results depend neither on
 // scheduling nor on the other lists of a batch.  Items are dropped on the
