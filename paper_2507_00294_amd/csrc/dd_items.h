@@ -101,6 +101,13 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// A wave's BYTES of the 256-thread block's LDS.
+template <int BYTES>
+__device__ __forceinline__ char* arr_lds() {
+  __shared__ __attribute__((aligned(16))) char lds[4][BYTES];
+  return lds[threadIdx.x >> 6];
+}
+
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // ---------------------------------------------------------------------------
@@ -193,10 +200,7 @@ struct FarRow {
   static constexpr int n = F == kFormFold ? 2 : M <= 1 ? 4 : M <= kMaxA ? 8 : 12;
 };
 constexpr int kRingLags = 128;
-__device__ __forceinline__ float* far_ring() {
-  __shared__ __attribute__((aligned(16))) float ring[4][kRingLags * 12];  // one per wave
-  return ring[threadIdx.x >> 6];
-}
+constexpr int kRingBytes = kRingLags * 12 * 4;  // per wave
 
 // The fields of a lag row, in the order the ring holds them.
 template <int M, int F>
@@ -272,12 +276,13 @@ __device__ __forceinline__ void load_posh(const uint2* p, half4_t (&q)[R]) {
 template <int M, int R, bool EDGE, bool CAS, int F = kFormFull>
 __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restrict__ pos, int64_t J,
                                           const half4_t (&e)[R], const float (&ee)[R],
-                                          const float* __restrict__ rows, double (&acc)[R]) {
+                                          const float* __restrict__ rows, char* lds,
+                                          double (&acc)[R]) {
   constexpr int NF = FarRow<M, F>::n;
   typedef float vec __attribute__((ext_vector_type(NF == 2 ? 2 : 4)));
   constexpr int NV = NF == 2 ? 1 : NF / 4;
   const int lane = threadIdx.x & 63, b = lane >> 2, c = lane & 3;
-  vec* const ring = reinterpret_cast<vec*>(far_ring());
+  vec* const ring = reinterpret_cast<vec*>(lds);
   const int L0 = lo - 3 * R;  // ring entry of lag n: (n - L0) % 128
   // lane l fetches the row of lag L0 + 64 k + l
   auto fetch = [&](int k, float(&w)[NF]) {
@@ -392,24 +397,24 @@ __device__ __forceinline__ void arr_far64(int lo, int hi, const double2* __restr
 template <int R, bool EDGE, bool CAS, bool PLAIN = false>
 __device__ __forceinline__ void arr_far32_seg(int M, int lo, int hi, const uint2* __restrict__ pos,
                                               int64_t J, const half4_t (&e)[R], const float (&ee)[R], const float* __restrict__ rows,
-                                              double (&acc)[R]) {
+                                              char* lds, double (&acc)[R]) {
   if constexpr (PLAIN) {
     switch (M) {
-      case 0: arr_far32<0, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
-      case 1: arr_far32<1, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
-      case 2: arr_far32<2, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
-      default: arr_far32<3, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, acc); break;
+      case 0: arr_far32<0, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+      case 1: arr_far32<1, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+      case 2: arr_far32<2, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+      default: arr_far32<3, R, EDGE, CAS, kFormPlain>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
     }
     return;
   }
   switch (M) {
-    case 0: arr_far32<0, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
-    case 1: arr_far32<1, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
-    case 2: arr_far32<2, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
-    case 3: arr_far32<3, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
-    case 4: arr_far32<4, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
-    case 5: arr_far32<5, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
-    default: arr_far32<6, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, acc); break;
+    case 0: arr_far32<0, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+    case 1: arr_far32<1, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+    case 2: arr_far32<2, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+    case 3: arr_far32<3, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+    case 4: arr_far32<4, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+    case 5: arr_far32<5, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
+    default: arr_far32<6, R, EDGE, CAS>(lo, hi, pos, J, e, ee, rows, lds, acc); break;
   }
 }
 
@@ -443,7 +448,7 @@ __device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint
                                                  const float* __restrict__ rows, int64_t V,
                                                  const DegreeBounds& bnd,
                                                  double* __restrict__ partial, int64_t pstride,
-                                                 int64_t pj0) {
+                                                 int64_t pj0, char* lds) {
   const int lane = threadIdx.x & 63;
   const int64_t J = (int64_t)item.tile * (64 * R), jl = J + (int64_t)R * lane;
   half4_t e[R];
@@ -467,18 +472,18 @@ __device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint
     if (lo >= hi) continue;
     const int mid = max(lo, min(hi, bnd.plain));
     if (edge) {
-      if (lo < mid) arr_far32_seg<R, true, CAS>(M, lo, mid, pos, J, e, ee, rows, acc);
-      if (mid < hi) arr_far32_seg<R, true, CAS, true>(M, mid, hi, pos, J, e, ee, rows, acc);
+      if (lo < mid) arr_far32_seg<R, true, CAS>(M, lo, mid, pos, J, e, ee, rows, lds, acc);
+      if (mid < hi) arr_far32_seg<R, true, CAS, true>(M, mid, hi, pos, J, e, ee, rows, lds, acc);
     } else {
-      if (lo < mid) arr_far32_seg<R, false, CAS>(M, lo, mid, pos, J, e, ee, rows, acc);
-      if (mid < hi) arr_far32_seg<R, false, CAS, true>(M, mid, hi, pos, J, e, ee, rows, acc);
+      if (lo < mid) arr_far32_seg<R, false, CAS>(M, lo, mid, pos, J, e, ee, rows, lds, acc);
+      if (mid < hi) arr_far32_seg<R, false, CAS, true>(M, mid, hi, pos, J, e, ee, rows, lds, acc);
     }
   }
   if (n_fold < item.n_hi) {
     if (edge)
-      arr_far32<0, R, true, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, acc);
+      arr_far32<0, R, true, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, lds, acc);
     else
-      arr_far32<0, R, false, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, acc);
+      arr_far32<0, R, false, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, lds, acc);
   }
   const int64_t base = (int64_t)(item.slot_flags & kSlotMask) * pstride - pj0;
 #pragma unroll
@@ -582,13 +587,16 @@ __device__ __forceinline__ void near_flush(NearQueue<Q>& q, int& cnt,
   cnt = 0;
 }
 
+constexpr int kNearQ = 12;
+
+// LDS: sizeof(NearQueue<Q>) bytes per wave (mixed).
 // Near band: per-pair regime choice, every pair masked by causality.
-template <int R, bool MIXED>
+template <int R, bool MIXED, int Q = kNearQ>
 __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void* __restrict__ pos_v,
                                                 const double* __restrict__ rows64,
                                                 const float* __restrict__ rows32, int64_t V,
                                                 double* __restrict__ partial, int64_t pstride,
-                                                int64_t pj0) {
+                                                int64_t pj0, char* lds) {
   const int lane = threadIdx.x & 63;
   const int64_t jl = (int64_t)item.tile * (64 * R) + (int64_t)R * lane;
   double acc[R];
@@ -605,9 +613,9 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
     }
     // G lags per step, the next step's positions and row fields in flight; the
     // queue holds a step's pairs beyond the four that leave it as it is
-    constexpr int G = 8 / R, NP = G + R - 1, kQ = 12;
-    __shared__ NearQueue<kQ> queues[4];  // one per wave of the 256-thread block
-    NearQueue<kQ>& Q = queues[threadIdx.x >> 6];
+    constexpr int G = 8 / R, NP = G + R - 1;
+    static_assert(Q > G * R, "a step's pairs fit the queue");
+    NearQueue<Q>& nq = *reinterpret_cast<NearQueue<Q>*>(lds);
     int cnt = 0;
     float2 p[NP];
     float c0[G], h0[G];
@@ -623,7 +631,7 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
     };
     if (item.n_lo < item.n_hi) fetch(item.n_lo);
     for (int n = item.n_lo; n < item.n_hi; n += G) {
-      if (__ballot(cnt > kQ - G * R)) near_flush<R>(Q, cnt, rows64, rows32, acc);
+      if (__ballot(cnt > Q - G * R)) near_flush<R>(nq, cnt, rows64, rows32, acc);
       float a[G][R];
       float c1[G], h1[G];
 #pragma unroll
@@ -648,8 +656,8 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
           low[r] = in && a[s][r] * c1[s] <= kThr32;
           any = any || low[r];
           if (in && !low[r] && a[s][r] * h1[s] <= kCull32Log2) {
-            Q.a[cnt][lane] = a[s][r];
-            Q.n[cnt][lane] = (n + s) | (r << 29);
+            nq.a[cnt][lane] = a[s][r];
+            nq.n[cnt][lane] = (n + s) | (r << 29);
             ++cnt;
           }
         }
@@ -665,7 +673,7 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
         }
       }
     }
-    if (__ballot(cnt > 0)) near_flush<R>(Q, cnt, rows64, rows32, acc);
+    if (__ballot(cnt > 0)) near_flush<R>(nq, cnt, rows64, rows32, acc);
   } else {
     const double2* pos = (const double2*)pos_v;
     double ex[R], ey[R];

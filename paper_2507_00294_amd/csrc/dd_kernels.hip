@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(256) k_positions(const int32_t* __restrict__ i
 
 // ---------------------------------------------------------------------------
 // Grid-mapped kernels: wavefront w of block b takes item 4 b + w.  RANGE = 1
-// marks the launches of a visit-range query: the same code as a whole-scan
+// marks the launches of an FP64 visit-range query: the same code as a whole-scan
 // query, instantiated apart so that kernel traces report the two separately.
 template <int R, int RANGE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
@@ -74,7 +74,8 @@ k_arrival_far32(const uint2* __restrict__ pos,
                                                        int64_t pj0) {
   const int it = blockIdx.x * 4 + wave_id();
   if (it >= n_items) return;
-  do_arrival_far32<R, false>(items[it], pos, rows, V, bnd, partial, pstride, pj0);
+  do_arrival_far32<R, false>(items[it], pos, rows, V, bnd, partial, pstride, pj0,
+                             arr_lds<kRingBytes>());
 }
 
 template <int R, int RANGE>
@@ -98,7 +99,35 @@ __global__ void __launch_bounds__(256) k_arrival_near(const void* __restrict__ p
                                                       int64_t pstride, int64_t pj0) {
   const int it = blockIdx.x * 4 + wave_id();
   if (it >= n_items) return;
-  do_arrival_near<R, MIXED>(items[it], pos_v, rows64, rows32, V, partial, pstride, pj0);
+  do_arrival_near<R, MIXED>(items[it], pos_v, rows64, rows32, V, partial, pstride, pj0,
+                            arr_lds<MIXED ? sizeof(NearQueue<kNearQ>) : 16>());
+}
+
+// Both bands of a visit range in mixed precision: blocks of near items first,
+// whose waves are few (a range's 1024 visits: 200) and long, then the far ones.
+// Queues short enough for four blocks of the far region per CU.  1024 visits of
+// 512x512 in random order: 18 us near and 69 us far one after the other, 72
+// together.
+constexpr int kRangeQ = 9;
+template <int R, int RN>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_arrival_range32(const float2* __restrict__ pos, const uint2* __restrict__ posh,
+                  const double* __restrict__ rows64, const float* __restrict__ rows32,
+                  const ArrItem* __restrict__ items, int n_near, int n_items, int64_t V,
+                  DegreeBounds bnd, double* __restrict__ partial, int64_t pstride, int64_t pj0) {
+  constexpr int kQueue = sizeof(NearQueue<kRangeQ>);
+  char* lds = arr_lds<(kQueue > kRingBytes ? kQueue : kRingBytes)>();
+  const int near_blocks = (n_near + 3) / 4;
+  if ((int)blockIdx.x < near_blocks) {
+    const int it = blockIdx.x * 4 + wave_id();
+    if (it < n_near)
+      do_arrival_near<RN, true, kRangeQ>(items[it], pos, rows64, rows32, V, partial, pstride, pj0,
+                                         lds);
+    return;
+  }
+  const int it = n_near + (blockIdx.x - near_blocks) * 4 + wave_id();
+  if (it >= n_items) return;
+  do_arrival_far32<R, false>(items[it], posh, rows32, V, bnd, partial, pstride, pj0, lds);
 }
 
 // Near-band and far items in launches of their own, each with the registers of
@@ -229,38 +258,45 @@ hipError_t launch_positions(const int32_t* ids, int64_t V, int nx, float2* pos32
 }
 
 template <int R, int RANGE>
-static void launch_arrival_r(const ArrivalLaunch& L, hipStream_t st, unsigned blocks) {
-  if (L.mixed) {
-    hipLaunchKernelGGL((k_arrival_far32<R, RANGE>), dim3(blocks), dim3(256), 0, st, L.posh,
-                       L.rows32, L.items, L.n_items, L.V, L.bounds, L.partial, L.pstride, L.pj0);
-  } else {
+static void launch_arrival64(const ArrivalLaunch& L, hipStream_t st, unsigned blocks) {
+  if (L.near)
+    hipLaunchKernelGGL((k_arrival_near<R, false, RANGE>), dim3(blocks), dim3(256), 0, st, L.pos,
+                       L.rows64, L.rows32, L.items, L.n_items, L.V, L.partial, L.pstride, L.pj0);
+  else
     hipLaunchKernelGGL((k_arrival_far64<R, RANGE>), dim3(blocks), dim3(256), 0, st,
                        (const double2*)L.pos, L.rows64, L.items, L.n_items, L.V, L.bounds,
                        L.partial, L.pstride, L.pj0);
-  }
-}
-
-template <int R, int RANGE>
-static void launch_arrival_near_r(const ArrivalLaunch& L, hipStream_t st, unsigned blocks) {
-  if (L.mixed)
-    hipLaunchKernelGGL((k_arrival_near<R, true, RANGE>), dim3(blocks), dim3(256), 0, st, L.pos,
-                       L.rows64, L.rows32, L.items, L.n_items, L.V, L.partial, L.pstride, L.pj0);
-  else
-    hipLaunchKernelGGL((k_arrival_near<R, false, RANGE>), dim3(blocks), dim3(256), 0, st, L.pos,
-                       L.rows64, L.rows32, L.items, L.n_items, L.V, L.partial, L.pstride, L.pj0);
 }
 
 template <int R>
 static void launch_arrival_kind(const ArrivalLaunch& L, hipStream_t st, unsigned blocks) {
-  if (L.near)
-    L.range ? launch_arrival_near_r<R, 1>(L, st, blocks) : launch_arrival_near_r<R, 0>(L, st, blocks);
+  if (!L.mixed)
+    L.range ? launch_arrival64<R, 1>(L, st, blocks) : launch_arrival64<R, 0>(L, st, blocks);
+  else if (L.near)
+    hipLaunchKernelGGL((k_arrival_near<R, true, 0>), dim3(blocks), dim3(256), 0, st, L.pos,
+                       L.rows64, L.rows32, L.items, L.n_items, L.V, L.partial, L.pstride, L.pj0);
   else
-    L.range ? launch_arrival_r<R, 1>(L, st, blocks) : launch_arrival_r<R, 0>(L, st, blocks);
+    hipLaunchKernelGGL((k_arrival_far32<R, 0>), dim3(blocks), dim3(256), 0, st, L.posh, L.rows32,
+                       L.items, L.n_items, L.V, L.bounds, L.partial, L.pstride, L.pj0);
+}
+
+hipError_t launch_arrival_range(const ArrivalLaunch& L, int n_near, int RN, hipStream_t st) {
+  const int n_far = L.n_items - n_near;
+  const unsigned blocks = (unsigned)((n_near + 3) / 4 + (n_far + 3) / 4);
+  if (blocks == 0) return hipSuccess;
+  auto k = L.R == 4 ? (RN == 4 ? k_arrival_range32<4, 4> : k_arrival_range32<4, 2>)
+                    : (RN == 4 ? k_arrival_range32<2, 4> : k_arrival_range32<2, 2>);
+  if (!L.mixed || (L.R != 2 && L.R != 4) || (RN != 2 && RN != 4)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, (const float2*)L.pos, L.posh, L.rows64,
+                     L.rows32, L.items, n_near, L.n_items, L.V, L.bounds, L.partial, L.pstride,
+                     L.pj0);
+  return hipGetLastError();
 }
 
 // Near-band and far-region items are launched separately (L.near).
 hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st) {
   if (L.n_items <= 0) return hipSuccess;
+  if (L.mixed && L.range) return hipErrorInvalidValue;  // launch_arrival_range
   const unsigned blocks = (unsigned)((L.n_items + 3) / 4);
   switch (L.R) {
     case 2: launch_arrival_kind<2>(L, st, blocks); break;
