@@ -193,19 +193,22 @@ struct E1SeriesCoef {
   }
 };
 
-// E1(x) for x > 0.  Power series about 0 (A&S 5.1.11) for x <= 2.5; above,
-// x e^x E1(x) as a polynomial in t = 5/x - 1 on [-1, 1], interpolating it at the
-// Chebyshev points (formed in 50 digits), times e^-x / x.  It costs a wave the
-// same whatever its lanes' x; the even continued fraction (A&S 5.1.22), 5 + 90/x
-// levels in double precision, took as many as the wave's smallest x (25600
-// visits of a measured raster list, FP64 arrival: 1.21 ms, 1.08 with this).  Relative errors:
-//   e1_f64: 24 terms, degree 27, e^-x by degree 11: < 3e-15 for x <= 2.5, < 1e-14
-//           above;
-//   e1_mixed: 18 terms, degree 16, e^-x by degree 9: < 1e-8 at 2.5, < 1e-10 above.
-// The coefficients are read through the scalar cache where they are used: as
-// literals the compiler kept them in vector registers over the whole loop, and
-// spilled (512 maps of 128x128 over a 64x64 raster scan, near band with every
-// general pair queued: continued fraction 4.6 ms, literals 7.1, this 4.35).
+// E1(x) for x > 0.  Power series about 0 (A&S 5.1.11) for x <= 2.5.  Above:
+//   e1_f64: x e^x E1(x) as a polynomial of degree 27 in t = 5/x - 1 on [-1, 1],
+//     interpolating it at the Chebyshev points (formed in 50 digits), times e^-x
+//     / x: < 3e-15 for x <= 2.5 (24 terms), < 1e-14 above.  It costs a wave the same
+//     whatever its lanes' x; the continued fraction, 5 + 90/x levels, took as many
+//     as the wave's smallest x (25600 visits of a measured raster list, FP64
+//     arrival: 1.21 ms, 1.08 with this).
+//   e1_mixed: the even continued fraction
+//       E1(x) = e^-x / (x+1 - 1/(x+3 - 4/(x+5 - ...)))   (A&S 5.1.22)
+//     to 4 + 30/x levels by the forward three-term recurrence of its convergents,
+//     e^-x by degree 7, 18 series terms: < 1e-8.  (A polynomial of degree 16 is
+//     quicker by a tenth of a near band and exact to 1e-10, but moves small scans'
+//     maps by that 1e-8's share, 2e-9.)
+// The polynomials' coefficients are read through the scalar cache where they are
+// used: as literals the compiler kept them in vector registers over the whole
+// loop, and spilled.
 struct E1Coef {
   double e1s[24], e1p[28], exp[12];
 };
@@ -231,53 +234,47 @@ constexpr E1Coef e1_coef64() {
 }
 static __constant__ E1Coef g_e1_coef64 = e1_coef64();
 
-// NS terms of the series, degree NP of the polynomial and NE of e^-x.
-template <int NS, int NP, int NE, typename C>
-__device__ __forceinline__ double e1_eval(double x, const C* c) {
-  if (x <= 2.5) {
-    double s = ldc(c->e1s + NS - 1);
+// The series' part, NS terms.
+template <int NS, typename C>
+__device__ __forceinline__ double e1_series(double x, const C* c) {
+  double s = ldc(c->e1s + NS - 1);
 #pragma unroll
-    for (int n = NS - 2; n >= 0; --n) s = fma(s, x, ldc(c->e1s + n));
-    return -kEulerGamma - ::log(x) - x * s;
-  }
-  double r = __builtin_amdgcn_rcp(x);  // 1/x, by two Newton steps
-  r = fma(fma(-x, r, 1.0), r, r);
-  r = fma(fma(-x, r, 1.0), r, r);
-  const double t = fma(5.0, r, -1.0);
-  double p = ldc(c->e1p + NP);
-#pragma unroll
-  for (int k = NP - 1; k >= 0; --k) p = fma(p, t, ldc(c->e1p + k));
-  // e^-x as in exp2_neg
+  for (int n = NS - 2; n >= 0; --n) s = fma(s, x, ldc(c->e1s + n));
+  return -kEulerGamma - ::log(x) - x * s;
+}
+// e^-x as in exp2_neg, degree NE.
+template <int NE, typename C>
+__device__ __forceinline__ double e1_exp(double x, const C* c) {
   const double y = fmin(x * kLog2e, 1100.0), n = __builtin_rint(y), g = (n - y) * kLn2;
   double e = ldc(c->exp + NE);
 #pragma unroll
   for (int k = NE - 1; k >= 0; --k) e = fma(e, g, ldc(c->exp + k));
-  return __builtin_ldexp(e, -(int)n) * (p * r);
+  return __builtin_ldexp(e, -(int)n);
 }
 
 __device__ __forceinline__ double e1_f64(double x) {
   const E1Coef* c = &g_e1_coef64;
   asm volatile("" : "+s"(c));  // loads through it stay behind this point
-  return e1_eval<24, 27, 11>(x, c);
+  if (x <= 2.5) return e1_series<24>(x, c);
+  double r = __builtin_amdgcn_rcp(x);  // 1/x, by two Newton steps
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  const double t = fma(5.0, r, -1.0);
+  double p = ldc(c->e1p + 27);
+#pragma unroll
+  for (int k = 26; k >= 0; --k) p = fma(p, t, ldc(c->e1p + k));
+  return e1_exp<11>(x, c) * (p * r);
 }
 
 struct MixedCoef {
-  double e1s[18], e1p[17], exp[10];
+  double e1s[18], exp[8];
 };
 constexpr MixedCoef mixed_coef() {
   MixedCoef m{};
   constexpr E1SeriesCoef s{};
   constexpr InvFact f{};
   for (int k = 0; k < 18; ++k) m.e1s[k] = s.c[k];
-  for (int k = 0; k < 10; ++k) m.exp[k] = f.v[k];
-  constexpr double p[17] = {
-      0.85211088142366098,     -0.11266528819442803,    0.024605713240480186,
-      -0.0069088690386625989,  0.0022722826450839707,   -0.00083505357622084631,
-      0.00033371406707880869,  -0.00014390868613839555, 6.5053977960993602e-05,
-      -2.5881915064510224e-05, 1.2100089677974122e-05,  -1.5046115680018144e-05,
-      8.5631640067449008e-06,  4.9682094211146733e-06,  -3.2013126951199133e-06,
-      -3.6250416266124557e-06, 2.1882907458483264e-06};
-  for (int k = 0; k < 17; ++k) m.e1p[k] = p[k];
+  for (int k = 0; k < 8; ++k) m.exp[k] = f.v[k];
   return m;
 }
 static __constant__ MixedCoef g_mixed_coef = mixed_coef();
@@ -288,7 +285,18 @@ __device__ __forceinline__ const MixedCoef* mixed_coef_here() {
 }
 
 __device__ __forceinline__ double e1_mixed(double x, const MixedCoef* c) {
-  return e1_eval<18, 16, 9>(x, c);
+  if (x <= 2.5) return e1_series<18>(x, c);
+  const int depth = 4 + (int)(30.0 / x);
+  double am1 = 1.0, bm1 = 0.0, a0 = x + 1.0, b0 = 1.0;
+  double bj = x + 1.0;
+  for (int j = 1; j <= depth; ++j) {
+    bj += 2.0;
+    const double aj = -(double)j * (double)j;
+    const double a1 = fma(bj, a0, aj * am1);
+    const double b1 = fma(bj, b0, aj * bm1);
+    am1 = a0; bm1 = b0; a0 = a1; b0 = b1;
+  }
+  return e1_exp<7>(x, c) * (b0 / a0);
 }
 
 // Series form in double precision with P_0..P_M read from an FP64 row.
@@ -352,15 +360,14 @@ __device__ __forceinline__ double phi_general_mixed(float a, const double* __res
   return e1_mixed(x1, c) - e0;
 }
 
-// The same for 0.25 < dx <= kMidDx by the whole FP64 row, read as uniform:
-// truncation e^{2 dx} dx^18 / 18! <= 2.3e-9 of the term at dx = 2.
-constexpr float kMidDx = 2.0f;
+// Its series part, 0.25 < dx <= kMidDx, with the rows read as uniform.
+constexpr float kMidDx = (float)kThr64;
 __device__ __forceinline__ double phi_mid_mixed(float a, const double* __restrict__ r64,
                                                 const float* __restrict__ r32) {
   const double z = (double)a * ldc(r64 + kR64_C);
-  double q = ldc(r64 + kR64_P + kM64);
+  double q = ldc(r64 + kR64_P + 12);
 #pragma unroll
-  for (int m = kM64 - 1; m >= 0; --m) q = fma(q, z, ldc(r64 + kR64_P + m));
+  for (int m = 11; m >= 0; --m) q = fma(q, z, ldc(r64 + kR64_P + m));
   const float rhi = ldc(r32 + kR32_RHI);
   const float yh = a * rhi;
   float yl = __builtin_fmaf(a, rhi, -yh);

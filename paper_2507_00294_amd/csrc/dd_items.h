@@ -230,14 +230,18 @@ __device__ __forceinline__ void far_row(const float* __restrict__ row, float (&w
   }
 }
 
+// The term as its two factors (q returned, t set).
 template <int M, int F>
-__device__ __forceinline__ float far_term(float a, const float (&w)[FarRow<M, F>::n]) {
+__device__ __forceinline__ float far_term_q(float a, const float (&w)[FarRow<M, F>::n], float& t) {
   if constexpr (F == kFormFold) {
-    return series_row32<M, F>(a, RowF{w[0], w[1]});
+    t = __builtin_amdgcn_exp2f(-(a * w[0]));
+    return w[1];
   } else if constexpr (M <= 1) {
-    return series_row32<M, F>(a, RowA{w[0], w[1], w[2], 0.f, 0.f, w[3], w[2], 0.f});
+    return series_f32a_q<M, F == kFormFull>(
+        a, RowA{w[0], w[1], w[2], 0.f, 0.f, w[3], w[2], 0.f}, t);
   } else if constexpr (M <= kMaxA) {
-    return series_row32<M, F>(a, RowA{w[0], w[1], w[2], w[4], w[5], w[3], 0.f, 0.f});
+    return series_f32a_q<M, F == kFormFull>(
+        a, RowA{w[0], w[1], w[2], w[4], w[5], w[3], 0.f, 0.f}, t);
   } else {
     float row[kRow32] = {};
     row[kR32_RHI] = w[0];
@@ -246,7 +250,7 @@ __device__ __forceinline__ float far_term(float a, const float (&w)[FarRow<M, F>
     row[kR32_RLO] = w[3];
 #pragma unroll
     for (int m = 0; m < kM32; ++m) row[kR32_P1 + m] = w[4 + m];
-    return series_row32<M, F>(a, row);
+    return series_f32_q<M>(a, row, t);
   }
 }
 
@@ -311,7 +315,7 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
     for (int t = 0; t < R; ++t)
       a[t] = __builtin_amdgcn_mfma_f32_4x4x4f16(A[t], e[t], f32x4_t{ee[t], ee[t], ee[t], ee[t]}, 0,
                                                 0, 0);
-    float part[R];
+    float part[R], q0[R], x0[R];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       // groups of R lags are aligned, so that only they can wrap
@@ -325,9 +329,22 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
       }
 #pragma unroll
       for (int t = 0; t < R; ++t) {
-        float x = far_term<M, F>(a[t][v], w);
-        if (EDGE) x = i0 + t - 4 * s - v >= 0 ? x : 0.0f;
-        part[t] = v % R == 0 ? x : part[t] + x;
+        float ex;
+        const float q = far_term_q<M, F>(a[t][v], w, ex);
+        if (EDGE) {
+          const float x = i0 + t - 4 * s - v >= 0 ? q * ex : 0.0f;
+          part[t] = v % R == 0 ? x : part[t] + x;
+        } else {
+          // of a sum's first two products one is rounded by itself.  Which one is
+          // free, but moves far sums by 1e-9 together: the lags of a scan repeat
+          // the same roundings.  It is stated here so that it does not change with
+          // the code around it.
+          const int own = (F != kFormFull || M <= 1) && t == 0 ? 0 : 1;
+          if (v % R == 0) q0[t] = q, x0[t] = ex;
+          if (v % R == own) part[t] = q * ex;
+          if (own == 1 && v % R == 1) part[t] = __builtin_fmaf(q0[t], x0[t], part[t]);
+          if (v % R > own) part[t] = __builtin_fmaf(q, ex, part[t]);
+        }
         if (v % R == R - 1) acc[t] += (double)part[t];
       }
     }
