@@ -339,7 +339,7 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
           // free, but moves far sums by 1e-9 together: the lags of a scan repeat
           // the same roundings.  It is stated here so that it does not change with
           // the code around it.
-          const int own = (F != kFormFull || M <= 1) && t == 0 ? 0 : 1;
+          const int own = M <= kMaxA && t == 0 ? 0 : 1;
           if (v % R == 0) q0[t] = q, x0[t] = ex;
           if (v % R == own) part[t] = q * ex;
           if (own == 1 && v % R == 1) part[t] = __builtin_fmaf(q0[t], x0[t], part[t]);
