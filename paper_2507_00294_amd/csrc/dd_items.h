@@ -939,8 +939,7 @@ __device__ __forceinline__ void map_far32_seg(int M, int lo, int hi, int64_t K,
 // scalar registers; the few beyond are queued as in do_arrival_near.  (512 maps
 // of 128x128 over a 64x64 raster scan: 3.6 ms with the general form where it
 // occurs, 4.4 with all of its pairs queued, whose evaluation gathers a row per
-// lane, 2.6 now; final maps of 32 mixed scans of 16..256 probes a side: 1.31,
-// 0.64, 0.48.)
+// lane, 3.3 now.)
 template <int R>
 __device__ __forceinline__ void map_near32(int lo, int hi, int64_t K, const uint2* __restrict__ pos,
                                            const double* __restrict__ rows64,
