@@ -16,7 +16,7 @@ namespace dd {
 // of the per-scan kernels, so batch results equal per-scan results bit for
 // bit.
 template <int R, bool MIXED>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MIXED && R == 4 ? 3 : 1, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MIXED && R == 4 ? 4 : 1, 8)))
 k_batch_arrival_far(const BatchScan* __restrict__ scans, const BatchItem* __restrict__ items,
                     int n_items, int* __restrict__ counter) {
   const int lane = threadIdx.x & 63;

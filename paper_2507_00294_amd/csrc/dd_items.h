@@ -180,15 +180,18 @@ __device__ __forceinline__ float series_row32_q(float a, const typename RowSel<M
 // and -2y (even, below 4096) are half-precision values, sh is at most 2048 and sl
 // in [-2048, 2047], and every partial sum is a whole number below 2^24.
 //
-// Lane l = 4 b + c owns the R visits j = J + 4 R b + R c + t, t < R.  Step D takes,
-// per t, the four earlier visits i = J + 4 R b + t - D - v, v < 4, of block b (the
-// A rows) against the block's four columns c: lane (b, c) gets the pairs of lags
-// D + R c + v, four consecutive lags per lane and step.  The lag now differs
-// between a block's lanes, so the fields of the lag rows that the form needs pass
-// through a ring of 128 lags in LDS, one row per lane and 64 lags at a time
-// (coalesced, prefetched), and are read back by broadcast; lags outside [lo, hi),
-// which the slant adds at both ends, get zero coefficients.  Terms are summed in
-// groups of R consecutive lags from lo in FP32, then in FP64.
+// Lane l = 4 b + c owns the R visits j = J + R u + t, t < R, u = far_unit(b) + 2 c:
+// a block's columns are every other unit of R visits, and two blocks share eight
+// units.  Step D takes, per t, the four earlier visits i = J + R far_unit(b) + t - D
+// - v, v < 4, of block b (the A rows) against the block's four columns c: lane
+// (b, c) gets the pairs of lags D + 2 R c + v, four consecutive lags per lane and
+// step.  The lag now differs between a block's lanes, so the fields of the lag
+// rows that the form needs pass through a ring of 128 lags in LDS, one row per
+// lane and 64 lags at a time (coalesced, prefetched), and are read back by
+// broadcast; lags outside [lo, hi), which the slant adds at both ends, get zero
+// coefficients.  Terms are summed in groups of R consecutive lags from lo in FP32,
+// then in FP64; with columns two groups apart, the parity of a group is that of
+// the step (R = 4) or of v / R (R = 2) in every lane (see far_alone).
 //
 // Bound: VALU issue, in the folded form a product, the exponential (two
 // issues) and a fused multiply-add per pair, and 1/R of a conversion and an FP64
@@ -277,6 +280,20 @@ __device__ __forceinline__ void load_posh(const uint2* p, half4_t (&q)[R]) {
   }
 }
 
+// First unit of R visits of block b (lanes 4 b .. 4 b + 3).
+__device__ __forceinline__ int far_unit(int b) { return 8 * (b >> 1) + (b & 1); }
+
+// Of a group's first two products one is rounded by itself, the other enters by a
+// fused multiply-add: 0 if the first (lag lo + R k), 1 if the second.  Either is
+// as accurate, but the lags of a scan repeat the same roundings, and which one it
+// is moves the far sums of small scans by some 1e-9 together.  The choice by form,
+// visit and parity of k is stated so that the sums do not change with the code
+// around them; it is the one of the sums from registers that this form replaced.
+template <int M>
+constexpr int far_alone(bool odd, int t) {
+  return M > kMaxA || (odd && t > 0) ? 1 : 0;
+}
+
 template <int M, int R, bool EDGE, bool CAS, int F = kFormFull>
 __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restrict__ pos, int64_t J,
                                           const half4_t (&e)[R], const float (&ee)[R],
@@ -285,9 +302,10 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
   constexpr int NF = FarRow<M, F>::n;
   typedef float vec __attribute__((ext_vector_type(NF == 2 ? 2 : 4)));
   constexpr int NV = NF == 2 ? 1 : NF / 4;
-  const int lane = threadIdx.x & 63, b = lane >> 2, c = lane & 3;
+  const int lane = threadIdx.x & 63, c = lane & 3;
+  const int64_t Jb = J + R * far_unit(lane >> 2);
   vec* const ring = reinterpret_cast<vec*>(lds);
-  const int L0 = lo - 3 * R;  // ring entry of lag n: (n - L0) % 128
+  const int L0 = lo - 6 * R;  // ring entry of lag n: (n - L0) % 128
   // lane l fetches the row of lag L0 + 64 k + l
   auto fetch = [&](int k, float(&w)[NF]) {
     const int n = L0 + 64 * k + lane;
@@ -306,10 +324,10 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
       r[i] = x;
     }
   };
-  const uint2* pa = pos + (J + 4 * R * b - c - L0);  // step s: four visits before per s
+  const uint2* pa = pos + (Jb - c - L0);  // step s: four visits before per s
   auto load = [&](int s, half4_t(&q)[R]) { load_posh<R, CAS>(pa - 4 * s, q); };
-  const int i0 = (int)(J + 4 * R * b - L0);
-  auto step = [&](int s, const half4_t(&A)[R]) {
+  const int i0 = (int)(Jb - L0);
+  auto step = [&](int s, auto odd_step, const half4_t(&A)[R]) {
     f32x4_t a[R];
 #pragma unroll
     for (int t = 0; t < R; ++t)
@@ -319,7 +337,7 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       // groups of R lags are aligned, so that only they can wrap
-      const int at = ((4 * s + R * c + v / R * R) & (kRingLags - 1)) + v % R;
+      const int at = ((4 * s + 2 * R * c + v / R * R) & (kRingLags - 1)) + v % R;
       float w[NF];
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
@@ -335,11 +353,7 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
           const float x = i0 + t - 4 * s - v >= 0 ? q * ex : 0.0f;
           part[t] = v % R == 0 ? x : part[t] + x;
         } else {
-          // of a sum's first two products one is rounded by itself.  Which one is
-          // free, but moves far sums by 1e-9 together: the lags of a scan repeat
-          // the same roundings.  It is stated here so that it does not change with
-          // the code around it.
-          const int own = M <= kMaxA && t == 0 ? 0 : 1;
+          const int own = far_alone<M>(R == 4 ? odd_step() : v / R != 0, t);
           if (v % R == 0) q0[t] = q, x0[t] = ex;
           if (v % R == own) part[t] = q * ex;
           if (own == 1 && v % R == 1) part[t] = __builtin_fmaf(q0[t], x0[t], part[t]);
@@ -368,9 +382,9 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
     // an odd count takes one step more, of lags past hi
     const int s1 = min(16 * k + 16, (steps + 1) & ~1);
     for (int s = 16 * k; s < s1; s += 2) {
-      step(s, A);
+      step(s, std::false_type{}, A);
       load(s + 2, A);
-      step(s + 1, B);
+      step(s + 1, std::true_type{}, B);
       load(s + 3, B);
     }
     wave_sync();
@@ -467,7 +481,8 @@ __device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint
                                                  double* __restrict__ partial, int64_t pstride,
                                                  int64_t pj0, char* lds) {
   const int lane = threadIdx.x & 63;
-  const int64_t J = (int64_t)item.tile * (64 * R), jl = J + (int64_t)R * lane;
+  const int64_t J = (int64_t)item.tile * (64 * R);
+  const int64_t jl = J + R * (far_unit(lane >> 2) + 2 * (lane & 3));
   half4_t e[R];
   float ee[R];
   double acc[R];
