@@ -70,9 +70,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))
     const BatchItem bi = items[it];
     const BatchScan& S = scans[bi.scan];
     const MapItem mi{bi.tile, 0, bi.n_lo, bi.n_hi, bi.slot_flags & kSlotMask, NEAR ? 1 : 0, 0, 0};
-    do_map<RM, NEAR>(mi, S.map_time, S.posh, S.pos4, S.rows64, S.rows32, (double)S.map_x0,
-               (double)S.map_y0, (double)S.map_step, (double)S.map_step, S.map_w, S.map_h,
-               S.map_partial);
+    // probes of a scan, whole numbers: exact on the matrix cores
+    do_map<RM, NEAR, true>(mi, S.map_time, MapPos{S.posh, S.pos4}, S.rows64, S.rows32,
+                           (double)S.map_x0, (double)S.map_y0, (double)S.map_step,
+                           (double)S.map_step, S.map_w, S.map_h, S.map_partial);
   }
 }
 

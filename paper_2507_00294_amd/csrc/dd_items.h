@@ -737,61 +737,111 @@ __device__ __forceinline__ void do_arrival_near(const ArrItem& item, const void*
 // ---------------------------------------------------------------------------
 // Map query, mixed precision (FP64 maps: dd_gauss.hip).  Pixel pix = tile * 64 R
 // + R lane + r at (X0 + u DX, Y0 + v DY), u = pix % W, v = pix / W, all at the
-// item's time; visit v = K - n.  Pixel and probe coordinates are exact small
-// dyadic numbers (other grids run in FP64), so the squared distances are exact
-// as in arr_far32: the four visits of lags n .. n + 3 are the rows of all 16
-// blocks of v_mfma_f32_4x4x4_16b_f16, the pixels their columns, and a lane gets
-// its pixel's distances to the four.  A pixel coordinate has up to 12 bits:
+// item's time; visit v = K - n.  Pixel and probe coordinates are small dyadic
+// numbers (other grids run in FP64), and the squared distances come from the
+// matrix cores as in arr_far32: the four visits of lags n .. n + 3 are the rows of
+// all 16 blocks of v_mfma_f32_4x4x4_16b_f16, the pixels their columns, and a lane
+// gets its pixel's distances to the four.  A pixel coordinate has up to 12 bits:
 // where it is no half-precision value, a second instruction adds its last bit.
 // Lag rows are uniform (scalar loads).
+//
+// MM: the host has shown that every partial sum, in whatever order, is exact: in
+// units of 4^-q (pixels being multiples of 2^-q) below 2^24, although 4096 sh may
+// exceed |p|^2 by 2048.  Other grids (33x33 probes and more at 1/64 or 1/32 pitch,
+// far negative coordinates) take the distance by three FP32 operations per pair,
+// whose partial sums stay at |e|^2 + |p|^2.
 //
 // Bound: VALU issue (10.4 instructions per pair; all cycles).  512 maps of 128x128
 // over a 64x64 raster scan, far items: 5.0 ms with the distance by three FP32
 // operations, 4.4 now.
-template <int R>
+template <int R, bool MM>
 struct MapPix {
   half4_t hi[R], lo[R];  // (x, y, 4096, 1), rounded, and what is left of x and y
   bool wide;             // some `lo` of the grid is not zero
   float ee[R];
 };
+template <int R>
+struct MapPix<R, false> {
+  float ex[R], ey[R], ee[R];
+};
 
-// Lane's row of the visits of lags n .. n + 3 (visits K - n - 3 .. K - n).
-__device__ __forceinline__ half4_t map_visits(const uint2* pos, int64_t K, int n) {
-  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(
-      half4_t, *reinterpret_cast<const __attribute__((address_space(1))) u2*>(
-                   reinterpret_cast<uintptr_t>(pos + (K - n - (int)(threadIdx.x & 3)))));
+// The visits of lags n .. n + 3 (visits K - n - 3 .. K - n): a lane's row of them,
+// or all four, (-2x, -2y, x^2 + y^2), uniform.
+template <bool MM>
+struct MapVisits {
+  half4_t row;
+};
+template <>
+struct MapVisits<false> {
+  float4 v[4];
+};
+struct MapPos {
+  const uint2* half;
+  const float4* full;
+};
+template <bool MM>
+__device__ __forceinline__ MapVisits<MM> map_visits(const MapPos& pos, int64_t K, int n) {
+  MapVisits<MM> m;
+  if constexpr (MM) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    m.row = __builtin_bit_cast(
+        half4_t, *reinterpret_cast<const __attribute__((address_space(1))) u2*>(
+                     reinterpret_cast<uintptr_t>(pos.half + (K - n - (int)(threadIdx.x & 3)))));
+  } else {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) m.v[s] = ldc(pos.full + (K - n - s));
+  }
+  return m;
 }
 
-template <int R>
-__device__ __forceinline__ f32x4_t map_dist(const half4_t& visits, const MapPix<R>& px, int r) {
+// A lane's four distances; DIFF: by coordinate differences, where not from the
+// matrix cores (the near band, which also rounds to the same value above 2^24).
+template <int R, bool DIFF = false>
+__device__ __forceinline__ f32x4_t map_dist(const MapVisits<true>& vis, const MapPix<R, true>& px,
+                                            int r) {
   f32x4_t a = __builtin_amdgcn_mfma_f32_4x4x4f16(
-      visits, px.hi[r], f32x4_t{px.ee[r], px.ee[r], px.ee[r], px.ee[r]}, 0, 0, 0);
-  if (px.wide) a = __builtin_amdgcn_mfma_f32_4x4x4f16(visits, px.lo[r], a, 0, 0, 0);
+      vis.row, px.hi[r], f32x4_t{px.ee[r], px.ee[r], px.ee[r], px.ee[r]}, 0, 0, 0);
+  if (px.wide) a = __builtin_amdgcn_mfma_f32_4x4x4f16(vis.row, px.lo[r], a, 0, 0, 0);
+  return a;
+}
+template <int R, bool DIFF = false>
+__device__ __forceinline__ f32x4_t map_dist(const MapVisits<false>& vis, const MapPix<R, false>& px,
+                                            int r) {
+  f32x4_t a;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const float4 p = vis.v[s];
+    if constexpr (DIFF) {
+      const float dx = __builtin_fmaf(0.5f, p.x, px.ex[r]), dy = __builtin_fmaf(0.5f, p.y, px.ey[r]);
+      a[s] = __builtin_fmaf(dy, dy, dx * dx);
+    } else {
+      a[s] = __builtin_fmaf(px.ex[r], p.x, __builtin_fmaf(px.ey[r], p.y, px.ee[r] + p.z));
+    }
+  }
   return a;
 }
 
-template <int M, int R, int U>
-__device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const uint2* __restrict__ pos,
-                                          const float* __restrict__ rows, const MapPix<R>& px,
+template <int M, int R, int U, bool MM>
+__device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const MapPos& pos,
+                                          const float* __restrict__ rows, const MapPix<R, MM>& px,
                                           double (&acc)[R]) {
   using Row = typename RowSel<M>::type;
   int n = lo;
   if (n + U <= hi) {
     Row cur[U];
-    half4_t pc[U / 4];
+    MapVisits<MM> pc[U / 4];
 #pragma unroll
     for (int s = 0; s < U; ++s) {
       cur[s] = fetch_row<M>(rows, n + s);
-      if (s % 4 == 0) pc[s / 4] = map_visits(pos, K, n + s);
+      if (s % 4 == 0) pc[s / 4] = map_visits<MM>(pos, K, n + s);
     }
     for (; n + U <= hi; n += U) {
       Row nxt[U];
-      half4_t pn[U / 4];
+      MapVisits<MM> pn[U / 4];
 #pragma unroll
       for (int s = 0; s < U; ++s) {
         nxt[s] = fetch_row<M>(rows, min(n + U + s, hi - 1));
-        if (s % 4 == 0) pn[s / 4] = map_visits(pos, K, n + U + s);
+        if (s % 4 == 0) pn[s / 4] = map_visits<MM>(pos, K, n + U + s);
       }
       // Groups of four lags in lag order, each summed by an explicit chain
       // of fused multiply-adds: the arithmetic of a pixel is then the same
@@ -820,7 +870,7 @@ __device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const uint2
     }
   }
   for (; n < hi; ++n) {
-    const half4_t p = map_visits(pos, K, n);
+    const MapVisits<MM> p = map_visits<MM>(pos, K, n);
     const Row row = fetch_row<M>(rows, n);
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] += (double)series_row32<M>(map_dist<R>(p, px, r)[0], row);
@@ -906,47 +956,53 @@ __device__ __forceinline__ void map_far32_r1(int lo, int hi, int64_t K, const fl
   }
 }
 
-template <int R, int U>
+template <int R, int U, bool MM>
 __device__ __forceinline__ void map_far32_u(int M, int lo, int hi, int64_t K,
-                                            const uint2* __restrict__ pos,
-                                            const float* __restrict__ rows, const MapPix<R>& px,
+                                            const MapPos& pos,
+                                            const float* __restrict__ rows,
+                                            const MapPix<R, MM>& px,
                                             double (&acc)[R]) {
   switch (M) {
-    case 0: map_far32<0, R, U>(lo, hi, K, pos, rows, px, acc); break;
-    case 1: map_far32<1, R, U>(lo, hi, K, pos, rows, px, acc); break;
-    case 2: map_far32<2, R, U>(lo, hi, K, pos, rows, px, acc); break;
-    case 3: map_far32<3, R, U>(lo, hi, K, pos, rows, px, acc); break;
-    case 4: map_far32<4, R, U>(lo, hi, K, pos, rows, px, acc); break;
-    case 5: map_far32<5, R, U>(lo, hi, K, pos, rows, px, acc); break;
-    default: map_far32<6, R, U>(lo, hi, K, pos, rows, px, acc); break;
+    case 0: map_far32<0, R, U, MM>(lo, hi, K, pos, rows, px, acc); break;
+    case 1: map_far32<1, R, U, MM>(lo, hi, K, pos, rows, px, acc); break;
+    case 2: map_far32<2, R, U, MM>(lo, hi, K, pos, rows, px, acc); break;
+    case 3: map_far32<3, R, U, MM>(lo, hi, K, pos, rows, px, acc); break;
+    case 4: map_far32<4, R, U, MM>(lo, hi, K, pos, rows, px, acc); break;
+    case 5: map_far32<5, R, U, MM>(lo, hi, K, pos, rows, px, acc); break;
+    default: map_far32<6, R, U, MM>(lo, hi, K, pos, rows, px, acc); break;
   }
 }
 
-template <int R>
+template <int R, bool MM>
 __device__ __forceinline__ void map_far32_seg(int M, int lo, int hi, int64_t K,
-                                              const uint2* __restrict__ pos,
-                                              const float4* __restrict__ pos4,
-                                              const float* __restrict__ rows, const MapPix<R>& px,
-                                              double (&acc)[R]) {
+                                              const MapPos& pos, const float* __restrict__ rows,
+                                              const MapPix<R, MM>& px, double (&acc)[R]) {
   // One pixel per lane: degrees <= 3 from rows staged in LDS; higher degrees
   // eight lags per step for more loads in flight.  The sum runs over groups
   // of four in lag order either way, so the result does not depend on the
   // tile width.
   if constexpr (R == 1) {
-    const float ex = (float)px.hi[0][0] + (float)px.lo[0][0];
-    const float ey = (float)px.hi[0][1] + (float)px.lo[0][1], ee = px.ee[0];
+    float ex, ey;
+    const float ee = px.ee[0];
+    if constexpr (MM) {
+      ex = (float)px.hi[0][0] + (float)px.lo[0][0];
+      ey = (float)px.hi[0][1] + (float)px.lo[0][1];
+    } else {
+      ex = px.ex[0];
+      ey = px.ey[0];
+    }
     switch (M) {
-      case 0: map_far32_r1<0>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
-      case 1: map_far32_r1<1>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
-      case 2: map_far32_r1<2>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
-      case 3: map_far32_r1<3>(lo, hi, K, pos4, rows, ex, ey, ee, acc); return;
+      case 0: map_far32_r1<0>(lo, hi, K, pos.full, rows, ex, ey, ee, acc); return;
+      case 1: map_far32_r1<1>(lo, hi, K, pos.full, rows, ex, ey, ee, acc); return;
+      case 2: map_far32_r1<2>(lo, hi, K, pos.full, rows, ex, ey, ee, acc); return;
+      case 3: map_far32_r1<3>(lo, hi, K, pos.full, rows, ex, ey, ee, acc); return;
       default: break;
     }
     const int mid = lo + ((hi - lo) & ~7);
-    map_far32_u<R, 8>(M, lo, mid, K, pos, rows, px, acc);
+    map_far32_u<R, 8, MM>(M, lo, mid, K, pos, rows, px, acc);
     lo = mid;
   }
-  map_far32_u<R, 4>(M, lo, hi, K, pos, rows, px, acc);
+  map_far32_u<R, 4, MM>(M, lo, hi, K, pos, rows, px, acc);
 }
 
 // Near band: per-pair choice.  A pixel tile lies together, so pairs of dx up to
@@ -955,11 +1011,11 @@ __device__ __forceinline__ void map_far32_seg(int M, int lo, int hi, int64_t K,
 // of 128x128 over a 64x64 raster scan: 3.6 ms with the general form where it
 // occurs, 4.4 with all of its pairs queued, whose evaluation gathers a row per
 // lane, 3.3 now.)
-template <int R>
-__device__ __forceinline__ void map_near32(int lo, int hi, int64_t K, const uint2* __restrict__ pos,
+template <int R, bool MM>
+__device__ __forceinline__ void map_near32(int lo, int hi, int64_t K, const MapPos& pos,
                                            const double* __restrict__ rows64,
-                                           const float* __restrict__ rows32, const MapPix<R>& px,
-                                           double (&acc)[R]) {
+                                           const float* __restrict__ rows32,
+                                           const MapPix<R, MM>& px, double (&acc)[R]) {
   const int lane = threadIdx.x & 63;
   NearQueue<kMapQ>& Q = *reinterpret_cast<NearQueue<kMapQ>*>(map_lds<R>());
   // lags as differences from lo: queue entries hold 29 bits
@@ -972,7 +1028,7 @@ __device__ __forceinline__ void map_near32(int lo, int hi, int64_t K, const uint
 #pragma unroll
   for (int r = 0; r < R; ++r) gen[r] = 0.0;
   wave_sync();
-  half4_t pn = map_visits(pos, K, lo);
+  MapVisits<MM> pn = map_visits<MM>(pos, K, lo);
   float cc[4], rhi[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -981,11 +1037,11 @@ __device__ __forceinline__ void map_near32(int lo, int hi, int64_t K, const uint
     rhi[s] = ldc(row + kR32_RHI);
   }
   for (int n = 0; n < hi - lo; n += 4) {
-    const half4_t p = pn;
-    pn = map_visits(pos, K, lo + n + 4);
+    const MapVisits<MM> p = pn;
+    pn = map_visits<MM>(pos, K, lo + n + 4);
     f32x4_t a[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) a[r] = map_dist<R>(p, px, r);
+    for (int r = 0; r < R; ++r) a[r] = map_dist<R, true>(p, px, r);
     float c0[4], h0[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -1046,11 +1102,10 @@ __device__ __forceinline__ void map_near32(int lo, int hi, int64_t K, const uint
   for (int r = 0; r < R; ++r) acc[r] += gen[r];
 }
 
-// NEAR: a near-band item or a far one.
-template <int R, bool NEAR>
+// NEAR: a near-band item or a far one; MM: distances from the matrix cores.
+template <int R, bool NEAR, bool MM>
 __device__ __forceinline__ void do_map(const MapItem& item, const MapTime& tm,
-                                       const uint2* __restrict__ pos,
-                                       const float4* __restrict__ pos4,
+                                       const MapPos& pos,
                                        const double* __restrict__ rows64,
                                        const float* __restrict__ rows32, double X0, double Y0,
                                        double DX, double DY, int W, int H,
@@ -1059,32 +1114,37 @@ __device__ __forceinline__ void do_map(const MapItem& item, const MapTime& tm,
   const int64_t npix = (int64_t)W * H;
   const int64_t p0 = (int64_t)item.tile * (64 * R) + (int64_t)R * lane;
   double acc[R];
-  MapPix<R> px;
+  MapPix<R, MM> px;
   bool wide = false;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int64_t pix = min(p0 + r, npix - 1);
     const float x = (float)(X0 + (double)(pix % W) * DX);
     const float y = (float)(Y0 + (double)(pix / W) * DY);
-    const _Float16 xh = (_Float16)x, yh = (_Float16)y;
-    const _Float16 xl = (_Float16)(x - (float)xh), yl = (_Float16)(y - (float)yh);
-    px.hi[r] = half4_t{xh, yh, (_Float16)4096.0f, (_Float16)1.0f};
-    px.lo[r] = half4_t{xl, yl, (_Float16)0.0f, (_Float16)0.0f};
     px.ee[r] = __builtin_fmaf(y, y, x * x);
-    wide = wide || xl != (_Float16)0.0f || yl != (_Float16)0.0f;
+    if constexpr (MM) {
+      const _Float16 xh = (_Float16)x, yh = (_Float16)y;
+      const _Float16 xl = (_Float16)(x - (float)xh), yl = (_Float16)(y - (float)yh);
+      px.hi[r] = half4_t{xh, yh, (_Float16)4096.0f, (_Float16)1.0f};
+      px.lo[r] = half4_t{xl, yl, (_Float16)0.0f, (_Float16)0.0f};
+      wide = wide || xl != (_Float16)0.0f || yl != (_Float16)0.0f;
+    } else {
+      px.ex[r] = x;
+      px.ey[r] = y;
+    }
     acc[r] = 0.0;
   }
-  px.wide = __ballot(wide) != 0;
+  if constexpr (MM) px.wide = __ballot(wide) != 0;
   const double* r64b = rows64 + tm.row_base * kRow64;
   const float* r32b = rows32 + tm.row_base * kRow32;
   if constexpr (NEAR) {
     if (item.n_lo < item.n_hi)
-      map_near32<R>(item.n_lo, item.n_hi, tm.K, pos, r64b, r32b, px, acc);
+      map_near32<R, MM>(item.n_lo, item.n_hi, tm.K, pos, r64b, r32b, px, acc);
   } else {
     for (int M = tm.bounds.m_max; M >= 0; --M) {
       int lo, hi;
       seg_range(tm.bounds, M, item.n_lo, item.n_hi, lo, hi);
-      if (lo < hi) map_far32_seg<R>(M, lo, hi, tm.K, pos, pos4, r32b, px, acc);
+      if (lo < hi) map_far32_seg<R, MM>(M, lo, hi, tm.K, pos, r32b, px, acc);
     }
   }
   double* out = partial + (tm.slot_base + item.slot) * npix;

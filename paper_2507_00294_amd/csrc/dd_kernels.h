@@ -53,6 +53,7 @@ struct MapLaunch {
   int32_t W, H;
   double* partial;          // [slots][W*H]
   int R;
+  bool matrix;              // distances from the matrix cores (see MapPix)
 };
 hipError_t launch_map(const MapLaunch& L, hipStream_t st);
 

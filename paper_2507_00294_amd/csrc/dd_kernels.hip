@@ -132,7 +132,7 @@ k_arrival_range32(const float2* __restrict__ pos, const uint2* __restrict__ posh
 
 // Near-band and far items in launches of their own, each with the registers of
 // its own code.
-template <int R, bool NEAR>
+template <int R, bool NEAR, bool MM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_map(const uint2* __restrict__ pos, const float4* __restrict__ pos4,
       const double* __restrict__ rows64, const float* __restrict__ rows32,
@@ -141,7 +141,7 @@ k_map(const uint2* __restrict__ pos, const float4* __restrict__ pos4,
   const int it = blockIdx.x * 4 + wave_id();
   if (it >= n_items) return;
   const MapItem item = items[it];
-  do_map<R, NEAR>(item, times[item.m], pos, pos4, rows64, rows32, X0, Y0, DX, DY, W, H, partial);
+  do_map<R, NEAR, MM>(item, times[item.m], MapPos{pos, pos4}, rows64, rows32, X0, Y0, DX, DY, W, H, partial);
 }
 
 // ---------------------------------------------------------------------------
@@ -306,17 +306,18 @@ hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int R, bool NEAR>
+static void launch_map_items(const MapLaunch& L, const MapItem* items, int n, hipStream_t st) {
+  if (n <= 0) return;
+  auto k = L.matrix ? k_map<R, NEAR, true> : k_map<R, NEAR, false>;
+  hipLaunchKernelGGL(k, dim3((n + 3) / 4), dim3(256), 0, st, L.posh, L.pos4, L.rows64, L.rows32,
+                     items, n, L.times, L.X0, L.Y0, L.DX, L.DY, L.W, L.H, L.partial);
+}
+
 template <int R>
 static void launch_map_r(const MapLaunch& L, hipStream_t st) {
-  const int n_far = L.n_items - L.n_near;
-  if (n_far > 0)
-    hipLaunchKernelGGL((k_map<R, false>), dim3((n_far + 3) / 4), dim3(256), 0, st, L.posh, L.pos4,
-                       L.rows64, L.rows32, L.items + L.n_near, n_far, L.times, L.X0, L.Y0, L.DX,
-                       L.DY, L.W, L.H, L.partial);
-  if (L.n_near > 0)
-    hipLaunchKernelGGL((k_map<map_near_r(R), true>), dim3((L.n_near + 3) / 4), dim3(256), 0, st, L.posh,
-                       L.pos4, L.rows64, L.rows32, L.items, L.n_near, L.times, L.X0, L.Y0, L.DX,
-                       L.DY, L.W, L.H, L.partial);
+  launch_map_items<R, false>(L, L.items + L.n_near, L.n_items - L.n_near, st);
+  launch_map_items<map_near_r(R), true>(L, L.items, L.n_near, st);
 }
 
 hipError_t launch_map(const MapLaunch& L, hipStream_t st) {

@@ -695,17 +695,31 @@ struct MapPlan {
 };
 
 // Pixel coordinates (pitch units) are multiples of 2^-q for some q <= 8 and
-// small enough that |e|^2 + |p|^2 stays an exact single-precision value.
-bool grid_is_lattice(double X0, double Y0, double DX, double DY, int w, int h, int nx, int ny) {
+// small enough that |e|^2 + |p|^2 stays an exact single-precision value.  If so,
+// `matrix` tells whether the matrix cores may form the squared distances (see
+// MapPix): there |p|^2 = 4096 sh + sl, so that a partial sum may exceed |e|^2 +
+// |p|^2 by 2048 (sh = 0 below 2048), a 12-bit coordinate's last bit 2^-q comes
+// apart, and of a negative coordinate e the product -2 e p adds to the sum.
+bool grid_is_lattice(double X0, double Y0, double DX, double DY, int w, int h, int nx, int ny,
+                     bool& matrix) {
+  matrix = false;
   for (int q = 0; q <= 8; ++q) {
     const double sc = std::ldexp(1.0, q);
     bool ok = true;
     for (double v : {X0, Y0, DX, DY}) ok = ok && std::rint(v * sc) == v * sc;
     if (!ok) continue;
-    const double ex = std::max(std::fabs(X0), std::fabs(X0 + (w - 1) * DX));
-    const double ey = std::max(std::fabs(Y0), std::fabs(Y0 + (h - 1) * DY));
+    const double X1 = X0 + (w - 1) * DX, Y1 = Y0 + (h - 1) * DY;
+    const double ex = std::max(std::fabs(X0), std::fabs(X1));
+    const double ey = std::max(std::fabs(Y0), std::fabs(Y1));
     const double pe = (double)(nx - 1) * (nx - 1) + (double)(ny - 1) * (ny - 1);
     const double bound = (ex * ex + ey * ey + pe) * sc * sc;
+    auto side = [](double e0, double e1, double p) {
+      const double pos = std::max({0.0, e0, e1}), neg = std::max({0.0, -e0, -e1});
+      return std::max(pos * pos + p * p, (neg + p) * (neg + p));
+    };
+    const double most = side(X0, X1, nx - 1) + side(Y0, Y1, ny - 1) + (pe < 2048.0 ? 0.0 : 2048.0) +
+                        2.0 * (nx + ny) / sc;
+    matrix = most * sc * sc <= 16777216.0;
     return bound < 16777216.0 && (ex + nx) * sc < 4096.0 && (ey + ny) * sc < 4096.0;
   }
   return false;
@@ -919,8 +933,9 @@ dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, 
   // x1 * 1e-7 of relative accuracy, above the mixed bound where distant
   // probes (large x1) dominate a pixel, so such grids run in FP64.
   const double p = s->desc.pitch_m;
+  bool matrix = false;
   if (!mixed || !grid_is_lattice(g->x0_m / p, g->y0_m / p, g->dx_m / p, g->dy_m / p, g->w, g->h,
-                                 s->desc.nx, s->desc.ny))
+                                 s->desc.nx, s->desc.ny, matrix))
     return run_map64(s, g, t_s, n_t, out_dev, fl, st);
   const int R = tune().map_R_mixed;
   MapPlan P;
@@ -955,6 +970,7 @@ dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, 
   L.W = g->w; L.H = g->h;
   L.partial = s->partial.as<double>();
   L.R = R;
+  L.matrix = matrix;
   ProfToken tm = prof_begin("map", st);
   DD_HIP(launch_map(L, st), "map launch");
   prof_end(tm, st, P.pairs, P.flops);
