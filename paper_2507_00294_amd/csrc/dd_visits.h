@@ -18,13 +18,7 @@ namespace dd {
 
 constexpr int kVisTile = 256;     // evaluation points per tile (one per thread)
 constexpr int kVisStage = 256;    // visits staged in LDS at a time
-// Visit chunks (partial sums) per tile, and the items below which chunks are
-// halved: 25600 visits in 25 chunks are 1300 items for the 768 blocks that fit
-// the chip (FP64 arrival 1.08 ms), in 50 chunks 2600 (1.01); 65536 visits in 64
-// chunks instead of 32 took 3% (mixed arrival) to 13% (mixed map) longer, 28224
-// visits (1485 items, halved) 7% (mixed map).
-constexpr int kVisMaxSlots = 32;
-constexpr int64_t kVisMinItems = 1280;
+constexpr int kVisMaxSlots = 32;  // visit chunks (partial sums) per tile at most
 
 // Map grid (pixel (u, v) at (x0 + u dx, y0 + v dy), w columns).
 struct VisGrid {

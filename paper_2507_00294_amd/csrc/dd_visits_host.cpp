@@ -7,8 +7,8 @@
 // or, for the batch calls, many: every tile names its list, whose
 // descriptor (visits, order, output, grid and times, scaling) the kernels
 // read.  Evaluation points go in tiles of 256 (one thread each); visits in
-// chunks of K (a multiple of 256, at most 32 chunks per list, 64 for a list
-// of few items).  A work item is one tile against one chunk, written to a partial-sum slot of its own,
+// chunks of K (a multiple of 256, at most 32 chunks per list).  A work item
+// is one tile against one chunk, written to a partial-sum slot of its own,
 // and the slots are summed in a fixed order, so results depend neither on
 // scheduling nor on the other lists of a batch.  Items are dropped on the
 // host when no pair can contribute, that is when
@@ -582,8 +582,6 @@ dd_status dd_visits_create(int64_t n, const double* x_m, const double* y_m, cons
     }
     v->K = std::max<int64_t>(512, ((n + kVisMaxSlots - 1) / kVisMaxSlots + kVisStage - 1) /
                                       kVisStage * kVisStage);
-    if (v->K >= 1024 && (n / kVisTile) * (n / v->K) / 2 < kVisMinItems)
-      v->K = (v->K / 2 + kVisStage - 1) / kVisStage * kVisStage;
     for (int64_t c0 = 0; c0 < n; c0 += v->K) {
       Box b;
       for (int64_t i = c0; i < std::min(n, c0 + v->K); ++i) b.add(v->vis[i].x, v->vis[i].y);
