@@ -511,15 +511,21 @@ struct PinnedBuf {
   }
 };
 
-// Staging of a visit range's plan: one pinned buffer per thread, copied to
-// the device asynchronously; the next range query on the thread waits for
-// that copy (`copied`) before it rewrites the buffer.
+// Staging of a visit range's plan or an FP64 map's jobs: one pinned buffer per
+// thread and device (an event is recorded on its own device's streams only),
+// copied to the device asynchronously; the thread's next call of either kind
+// waits for that copy (`copied`) before it rewrites the buffer.
 struct RangeStage {
   PinnedBuf host;
   hipEvent_t copied = nullptr;  // kept until the process ends
   bool pending = false;
 };
-static thread_local RangeStage g_range;
+RangeStage& range_stage() {
+  static thread_local std::map<int, RangeStage> stages;
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  return stages[dev];
+}
 
 }  // namespace
 
@@ -617,7 +623,7 @@ dd_status run_arrival_range(dd_scan* s, bool mixed, int64_t j0, int64_t j1, doub
   const size_t bi = sizeof(ArrItem) * rp.items.size(), bt = sizeof(int32_t) * rp.tile_slots.size();
   DD_HIP(s->aux2.ensure(std::max<size_t>(bi, 16)), "device allocation");
   DD_HIP(s->aux3.ensure(std::max<size_t>(bt, 16)), "device allocation");
-  RangeStage& G = g_range;
+  RangeStage& G = range_stage();
   if (G.pending) DD_HIP(hipEventSynchronize(G.copied), "event synchronize");
   G.pending = false;
   DD_HIP(G.host.ensure(bi + bt), "pinned host allocation");
@@ -875,14 +881,14 @@ void plan_map(const dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
   P.items.insert(P.items.end(), far.begin(), far.end());
 }
 
-// FP64 maps: one job per time.  The jobs go up in the thread's pinned buffer,
-// asynchronously; the next call on the thread waits for that copy.
+// FP64 maps: one job per time.  The jobs go up in the thread's pinned buffer for
+// the device, asynchronously; its next call waits for that copy.
 dd_status run_map64(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, double* out_dev,
                     const OutFlag& fl, hipStream_t st) {
   const double p = s->desc.pitch_m;
   const int64_t npix = (int64_t)g->w * g->h;
   const GaussShape shape = gauss_shape(g->w, g->h, s->V, n_t);
-  RangeStage& G = g_range;
+  RangeStage& G = range_stage();
   const size_t bytes = sizeof(GaussJob) * (size_t)n_t;
   DD_HIP(s->aux2.ensure(bytes), "device allocation");
   if (G.pending) DD_HIP(hipEventSynchronize(G.copied), "event synchronize");
