@@ -932,6 +932,12 @@ dd_status run_map64(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t
 
 dd_status run_map(dd_scan* s, const dd_grid* g, const double* t_s, int32_t n_t, bool mixed,
                   double* out_dev, const OutFlag& fl, hipStream_t st) {
+  // a graph would copy the plan from host memory again at each replay, whatever later
+  // calls have written there
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone)
+    return fail(DD_EDEVICE, "a map call cannot be captured into a graph");
   dd_status rc = s->prepare(st);
   if (rc != DD_OK) return rc;
   // The FP32 bulk takes the squared distance a exactly only when pixels and
