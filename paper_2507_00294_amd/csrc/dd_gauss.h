@@ -61,6 +61,9 @@ struct GaussChunks {
   }
 };
 
+// Partial sums of the maps of one launch group in calls of many maps (256 MiB).
+constexpr int64_t kGaussGroup = (int64_t)1 << 25;
+
 // Split of maps of w x h pixels over at most n_vis visits, n_t of them in the
 // call: tile side 16 F and visits per chunk.
 struct GaussShape {

@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <numeric>
 #include <new>
 #include <vector>
 
@@ -1052,7 +1053,7 @@ struct BatchScratch {
   std::vector<BatchScan> h_scans;
   std::vector<BatchItem> h_items, h_near_items, h_map_items, h_map_near_items, h_tmp;
   std::vector<BatchReduce> h_reds;
-  std::vector<GaussJob> h_gauss;  // FP64 final maps, in scan order
+  std::vector<GaussJob> h_gauss, h_gauss_sorted;  // FP64 final maps
   std::vector<LatClass> h_lat_cls;  // FP64 arrival of scans made of rasters
   std::vector<LatPass> h_lat_passes;
   std::vector<LatJob> h_lat;
@@ -1313,8 +1314,6 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
       GaussJob j = gauss_job(s, (double)s->V, q.x0, q.y0, q.step, q.step, q.w, q.h);
       gauss_split(j, gauss_shape(q.w, q.h, s->V, 1));
       const int64_t npix = (int64_t)q.w * q.h;
-      map_off[k] = partial_total;
-      partial_total += j.n_chunks * npix;
       j.fl = scan_flag[k];
       j.fl.base = want_arr ? s->V : 0;
       j.fl2 = call_flag;
@@ -1378,6 +1377,34 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
   if (W.pending) DD_HIP(hipStreamWaitEvent(st, W.done, 0), "stream wait");
   for (std::vector<BatchItem>* v : {&items, &near_items, &map_items, &map_near_items})
     sort_longest_first(*v, W.h_tmp, W.h_ka, W.h_kb);
+  // FP64 maps by tile factor, in launch groups of one factor that share the same
+  // partial sums, one group after the other: at most kGaussGroup of them, or one map
+  std::vector<int32_t> gauss_of(W.h_gauss.size());  // the scan of each job
+  std::vector<size_t> gauss_end;                    // of each group
+  const int64_t gauss_off = partial_total;
+  {
+    std::iota(gauss_of.begin(), gauss_of.end(), 0);
+    std::stable_sort(gauss_of.begin(), gauss_of.end(),
+                     [&](int32_t a, int32_t b) { return W.h_gauss[a].F > W.h_gauss[b].F; });
+    std::vector<GaussJob>& sorted = W.h_gauss_sorted;
+    sorted.clear();
+    int64_t sums = 0, most = 0;
+    for (int32_t k : gauss_of) {
+      const GaussJob& j = W.h_gauss[k];
+      const int64_t n_sums = (int64_t)j.n_chunks * j.W * j.H;
+      if (!sorted.empty() && (sums + n_sums > kGaussGroup || j.F != sorted.back().F)) {
+        gauss_end.push_back(sorted.size());
+        sums = 0;
+      }
+      sorted.push_back(j);
+      sums += n_sums;
+      most = std::max(most, sums);
+    }
+    if (!sorted.empty()) gauss_end.push_back(sorted.size());
+    W.h_gauss.swap(sorted);
+    partial_total += most;
+  }
+  std::vector<double*> gauss_out(W.h_gauss.size());
   // tables: scans, far/near arrival items, far/near map items, reductions,
   // slots, FP64 maps, FP64 arrival sums of scans made of rasters
   struct Table {
@@ -1429,8 +1456,7 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
         ++r;
       }
       if (want_map && !mixed) {
-        W.h_gauss[k].partial = part + map_off[k];
-        W.h_gauss[k].out = o;
+        gauss_out[k] = o;
       } else if (want_map) {
         bs[k].map_partial = part + map_off[k];
         reds[r].partial = bs[k].map_partial;
@@ -1439,9 +1465,15 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
       }
     }
   }
-  // FP64 maps by tile factor (each map writes its own partial sums and output)
-  std::stable_sort(W.h_gauss.begin(), W.h_gauss.end(),
-                   [](const GaussJob& a, const GaussJob& b) { return a.F > b.F; });
+  for (size_t k = 0, g = 0; g < gauss_end.size(); ++g) {
+    double* sums = part + gauss_off;
+    for (; k < gauss_end[g]; ++k) {
+      GaussJob& j = W.h_gauss[k];
+      j.partial = sums;
+      j.out = gauss_out[gauss_of[k]];
+      sums += (int64_t)j.n_chunks * j.W * j.H;
+    }
+  }
   if (W.copy_pending) DD_HIP(hipEventSynchronize(W.copied), "event synchronize");
   W.copy_pending = false;
   DD_HIP(W.host_block.ensure(block_bytes), "pinned host allocation");
@@ -1481,24 +1513,23 @@ dd_status dd::run_batch(dd_scan* const* scans, int32_t n, uint32_t mask, bool mi
                           (int32_t)map_near_items.size(), W.counter.as<int>() + 3, RM, true, st),
          "batched map near-band launch");
   const GaussJob* d_gauss = (const GaussJob*)(blk + tab[7].off);
-  int64_t max_pixels = 0;
-  for (size_t k = 0, e; k < W.h_gauss.size(); k = e) {
-    int64_t most = 0;
-    for (e = k; e < W.h_gauss.size() && W.h_gauss[e].F == W.h_gauss[k].F; ++e) {
+  for (size_t k = 0, g = 0; g < gauss_end.size(); k = gauss_end[g++]) {
+    int64_t most = 0, max_pixels = 0;
+    for (size_t e = k; e < gauss_end[g]; ++e) {
       const GaussJob& j = W.h_gauss[e];
       most = std::max(most, (int64_t)j.tiles * j.n_chunks);
       max_pixels = std::max(max_pixels, (int64_t)j.W * j.H);
     }
-    DD_HIP(launch_gauss_map(d_gauss + k, (int32_t)(e - k), most, W.h_gauss[k].F, false, st),
+    const int32_t n_jobs = (int32_t)(gauss_end[g] - k);
+    DD_HIP(launch_gauss_map(d_gauss + k, n_jobs, most, W.h_gauss[k].F, false, st),
            "batched map launch");
+    DD_HIP(launch_gauss_reduce(d_gauss + k, n_jobs, max_pixels, st), "batched map reduce launch");
   }
   prof_end(tb, st, pairs, flops);
   ProfToken tq = prof_begin("reduce", st);
   DD_HIP(launch_reduce_batch((const BatchReduce*)(blk + tab[5].off), (int32_t)reds.size(),
                              reds_total, call_flag, st),
          "batched reduce launch");
-  DD_HIP(launch_gauss_reduce(d_gauss, (int32_t)W.h_gauss.size(), max_pixels, st),
-         "batched map reduce launch");
   prof_end(tq, st, 0, 0);
   if (!W.done) DD_HIP(hipEventCreateWithFlags(&W.done, hipEventDisableTiming), "event creation");
   DD_HIP(hipEventRecord(W.done, st), "event record");

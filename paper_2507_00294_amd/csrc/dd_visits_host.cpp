@@ -378,7 +378,7 @@ struct MapTiling {
 };
 
 // FP64 maps (dd_gauss.h) of lists[k], as run_maps: one job per list and time,
-// in launch groups of at most 2^25 partial sums (256 MiB) or one map.  A map's
+// in launch groups of at most kGaussGroup partial sums or one map.  A map's
 // split depends on its list and grid alone, so results depend neither on the
 // other times of a call nor on the other lists.
 dd_status launch_maps64(hipStream_t st) {
@@ -450,7 +450,7 @@ dd_status run_maps64(dd_visits* const* lists, int32_t n, const dd_grid* grids,
       j.out = outs[k] + m * npix;
       j.fl = fl;
       j.fl.base = off[k] + m * npix;
-      if (!W.h_gauss.empty() && sums + j.n_chunks * npix > ((int64_t)1 << 25)) {
+      if (!W.h_gauss.empty() && sums + j.n_chunks * npix > kGaussGroup) {
         rc = launch_maps64(st);
         if (rc != DD_OK) return rc;
         W.h_gauss.clear();
