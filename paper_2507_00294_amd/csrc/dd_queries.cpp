@@ -203,6 +203,12 @@ int64_t arrival_far_start(const dd_scan* s, bool mixed, int R, double& a_max) {
 //    sums: the table stays within the 64 V doubles that the pair form's partial
 //    sums may take (strides up to 8).  256x256 at strides 2, 4, 8: 0.056,
 //    0.117, 0.66 ms; in pairs 2.1 ms.
+//  * A row of the table is a block of its own, 5.5 ns each however narrow: many
+//    passes of a narrow scan have more of them than their pairs are worth.  Pairs
+//    take 0.6 to 1.2 ms up to 2e4 visits, then 0.95 ps each; rows are worth it up
+//    to 1.5e5 + 8e-5 V^2.  8x2048 at stride 8 (1.05e6 rows) 5.7 ms, in pairs 0.9;
+//    32x1024 2.6 and 1.6; 64x1024 2.6 and 2.7; 128x1024 2.6 and 7.1; 6x2048 at
+//    stride 6 2.6 and 0.9, 64x256 at stride 8 (1.3e5 rows) 0.65 and 0.61.
 //  * Frames are added up one after the other, 0.1 us each: more than 1024
 //    frames of fewer than 16 probes have too few pairs for that (4000 frames of
 //    2x1: 0.43 ms, in pairs 0.24; 256 frames of 4x4: 0.044 and 0.25).
@@ -249,7 +255,9 @@ bool plan_lattice(const dd_scan* s, int R, LatPlan& P) {
     j.n_frames = F;
     j.n_sum = n;
   }
-  if (keys * j.w > 64 * s->V || std::max(keys, blocks) > 0x7fffffff) return false;
+  const double V = (double)s->V;
+  if (keys * j.w > 64 * s->V || (double)keys > 1.5e5 + 8e-5 * V * V) return false;
+  if (std::max(keys, blocks) > 0x7fffffff) return false;
   j.n_cls = (int32_t)P.cls.size();
   j.n_passes = (int32_t)P.passes.size();
   j.n_keys = (int32_t)keys;
