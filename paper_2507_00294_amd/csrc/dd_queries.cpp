@@ -257,7 +257,7 @@ bool plan_lattice(const dd_scan* s, int R, LatPlan& P) {
   }
   const double V = (double)s->V;
   if (keys * j.w > 64 * s->V || (double)keys > 1.5e5 + 8e-5 * V * V) return false;
-  if (std::max(keys, blocks) > 0x7fffffff) return false;
+  if (std::max(keys, blocks) >= (int64_t)1 << 24) return false;  // 2^32 threads in a grid
   j.n_cls = (int32_t)P.cls.size();
   j.n_passes = (int32_t)P.passes.size();
   j.n_keys = (int32_t)keys;

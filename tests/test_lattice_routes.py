@@ -1,5 +1,5 @@
 """Host check (not a GPU test) of which FP64 arrival queries run as sums over rasters:
-those whose table is worth it."""
+those whose table is worth it, and none whose launch a grid cannot hold."""
 import fake_hip
 import pytest
 
@@ -9,7 +9,8 @@ CASES = [(64, 64, "raster", 1, 1, True), (1, 2048, "raster", 1, 1, True),
          (256, 256, "interleaved", 8, 1, True), (128, 1024, "interleaved", 8, 1, True),
          (8, 1024, "interleaved", 8, 1, False), (8, 2048, "interleaved", 8, 1, False),
          (32, 2048, "interleaved", 8, 1, False), (6, 2048, "interleaved", 6, 1, False),
-         (1, 256, "multiframe", 1, 1024, True), (1, 2048, "multiframe", 1, 64, True)]
+         (1, 256, "multiframe", 1, 1024, True), (1, 2048, "multiframe", 1, 64, True),
+         (1, 16, "multiframe", 1, 2 ** 20, False)]
 
 CODE = r"""
 nx, ny, order, stride, frames, sums = %r
