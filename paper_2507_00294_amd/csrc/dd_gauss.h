@@ -10,6 +10,9 @@
 
 namespace dd {
 
+// Pixels of a tile of a narrow map: two per lane.
+constexpr int kGaussRow = 128;
+
 // One map: the visits started before its time, its pixel grid, the split of
 // the work into items and where results go.  The visits are those of a scan
 // (pos: double2 by visit in pitch units, lag (K - i) + f dwells) or of a list
@@ -23,7 +26,7 @@ struct GaussJob {
   double s2, k4, is2;
   double X0, Y0, DX, DY;  // pixel (u, v) at (X0 + u DX, Y0 + v DY)
   int32_t W, H;
-  int32_t tiles_x, tiles;  // tiles of 16 F x 16 F pixels
+  int32_t tiles_x, tiles;  // tiles of 16 F x 16 F pixels, or (F = 0) of kGaussRow in a row
   int32_t base, near;      // chunks of visits (see GaussChunks)
   int32_t n_chunks, F;
   double* partial;         // [n_chunks][W * H]
@@ -65,7 +68,7 @@ struct GaussChunks {
 constexpr int64_t kGaussGroup = (int64_t)1 << 25;
 
 // Split of maps of w x h pixels over at most n_vis visits, n_t of them in the
-// call: tile side 16 F and visits per chunk.
+// call: tile side 16 F (0: kGaussRow pixels in a row) and visits per chunk.
 struct GaussShape {
   int32_t F, base, near;
 };
@@ -75,8 +78,8 @@ GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t);
 inline void gauss_split(GaussJob& j, const GaussShape& s) {
   const int32_t T = 16 * s.F;
   j.F = s.F;
-  j.tiles_x = (j.W + T - 1) / T;
-  j.tiles = j.tiles_x * ((j.H + T - 1) / T);
+  j.tiles_x = T ? (j.W + T - 1) / T : 0;
+  j.tiles = T ? j.tiles_x * ((j.H + T - 1) / T) : (int32_t)(((int64_t)j.W * j.H + kGaussRow - 1) / kGaussRow);
   j.base = s.base;
   j.near = s.near;
   j.n_chunks = GaussChunks::count(j.n, s.base, s.near);

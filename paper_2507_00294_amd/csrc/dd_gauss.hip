@@ -22,6 +22,11 @@
 // the F column and F row factors of its visit (k = lane / 16) and pixel
 // coordinate (lane % 16) in registers.
 //
+// Maps of one or two rows or columns leave most of a tile empty.  They go 128
+// pixels at a time in row order (F = 0), two per lane and two nodes at a time, each
+// Gaussian of the squared distance in one exponential and added by a vector
+// multiply-add.
+//
 // Bound: the FP64 pipe.  A v_mfma_f64_16x16x4 takes about 72 cycles and an FP64
 // vector operation 4, and the two do not overlap, not even from different
 // waves (measured); a step is F^2 MFMAs and 2 F exponentials of 18 operations,
@@ -256,12 +261,39 @@ __device__ __forceinline__ void gauss_node(const GaussStage& S, int n, int lane,
   }
 }
 
+// One or two nodes (NN; their (-beta log2(e), omega) in bw and bw2) of the stage's n
+// visits for a row of pixels, two per lane.  FLAT: the tile lies in one row or column
+// of the map, px is the coordinate along it, and xy holds a visit's coordinate along
+// it and the square of its distance from it.  No clamp: coordinates are bounded,
+// and below 2^-1075 the result is 0.
+template <int NN, bool FLAT>
+__device__ __forceinline__ void gauss_node_row(const GaussStage& S, const double2* bw2, int n,
+                                               const double (&px)[2], const double (&py)[2],
+                                               double (&acc)[2]) {
+  for (int s = 0; s < n; s += 2) {  // (the stage is padded)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const double2 xy = S.xy[s + k], b = S.bw[s + k];
+      double2 c{};
+      if (NN == 2) c = bw2[s + k];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const double dx = px[q] - xy.x, dy = FLAT ? 0.0 : py[q] - xy.y;
+        const double a = fma(dx, dx, FLAT ? xy.y : dy * dy);
+        acc[q] = fma(b.y, gauss_exp2<10>(b.x * a), acc[q]);
+        if (NN == 2) acc[q] = fma(c.y, gauss_exp2<10>(c.x * a), acc[q]);
+      }
+    }
+  }
+}
+
 // Wave w of block (x, y): item 4 x + w of job y -- tile item % tiles, chunk
 // item / tiles (the recent visits, which take most nodes, first).
 template <int F, bool VIS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F == 4 ? 2 : F == 2 ? 3 : 4, 8)))
 k_gauss_map(const GaussJob* __restrict__ jobs) {
   __shared__ GaussStage stages[4];
+  __shared__ double2 seconds[F ? 1 : 4][F ? 1 : kGaussLds];  // F = 0: the second node of two
   const GaussJob& j = jobs[blockIdx.y];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -271,18 +303,40 @@ k_gauss_map(const GaussJob* __restrict__ jobs) {
   const int tile = (int)(item % j.tiles), chunk = (int)(item / j.tiles);
   int64_t r0, r1;
   GaussChunks::range(chunk, j.n, j.base, j.near, r0, r1);
-  const int u0 = tile % j.tiles_x * (16 * F), v0 = tile / j.tiles_x * (16 * F);
-  const int u1 = min(u0 + 16 * F, j.W) - 1, v1 = min(v0 + 16 * F, j.H) - 1;
-  double px[F], py[F];
+  constexpr int N = F ? F : 2;
+  int u0, u1, v0, v1;  // first and last column and row
+  double px[N], py[N];
+  const int64_t npix = (int64_t)j.W * j.H, p0 = (int64_t)tile * kGaussRow;
+  if constexpr (F == 0) {
+    const int64_t p1 = min(p0 + kGaussRow, npix) - 1;
+    v0 = (int)(p0 / j.W);
+    v1 = (int)(p1 / j.W);
+    u0 = v0 == v1 ? (int)(p0 % j.W) : 0;
+    u1 = v0 == v1 ? (int)(p1 % j.W) : j.W - 1;
 #pragma unroll
-  for (int a = 0; a < F; ++a) {
-    px[a] = j.X0 + (double)min(u0 + 16 * a + (lane & 15), u1) * j.DX;
-    py[a] = j.Y0 + (double)min(v0 + 16 * a + (lane & 15), v1) * j.DY;
+    for (int q = 0; q < 2; ++q) {
+      const int64_t p = min(p0 + lane + 64 * q, p1);
+      px[q] = fmin(fmax(j.X0 + (double)(p % j.W) * j.DX, -1e130), 1e130);
+      py[q] = fmin(fmax(j.Y0 + (double)(p / j.W) * j.DY, -1e130), 1e130);
+    }
+  } else {
+    u0 = tile % j.tiles_x * (16 * F);
+    v0 = tile / j.tiles_x * (16 * F);
+    u1 = min(u0 + 16 * F, j.W) - 1;
+    v1 = min(v0 + 16 * F, j.H) - 1;
+#pragma unroll
+    for (int a = 0; a < F; ++a) {
+      px[a] = j.X0 + (double)min(u0 + 16 * a + (lane & 15), u1) * j.DX;
+      py[a] = j.Y0 + (double)min(v0 + 16 * a + (lane & 15), v1) * j.DY;
+    }
   }
   const double xa = j.X0 + (double)u0 * j.DX, xb = j.X0 + (double)u1 * j.DX;
   const double ya = j.Y0 + (double)v0 * j.DY, yb = j.Y0 + (double)v1 * j.DY;
   const double4 box = make_double4(fmin(xa, xb), fmax(xa, xb), fmin(ya, yb), fmax(ya, yb));
-  f64x4 acc[F][F];
+  f64x4 acc[N][N];
+  double row_acc[2] = {0.0, 0.0};
+  const bool flat = F == 0 && (v0 == v1 || u0 == u1);
+  const double along[2] = {v0 == v1 ? px[0] : py[0], v0 == v1 ? px[N > 1] : py[N > 1]};
 #pragma unroll
   for (int a = 0; a < F; ++a)
 #pragma unroll
@@ -300,36 +354,69 @@ k_gauss_map(const GaussJob* __restrict__ jobs) {
     const int n = __popcll(live);
     const int slot = __popcll(live & ((1ull << lane) - 1));
     gauss_lds_sync();  // the previous stage is no longer read
-    if (v.on) S.xy[slot] = make_double2(v.x, v.y);
+    if (v.on) {
+      double2 xy = make_double2(v.x, v.y);
+      if (F == 0 && flat) {
+        const double off = v0 == v1 ? py[0] - v.y : px[0] - v.x;
+        xy = make_double2(v0 == v1 ? v.x : v.y, off * off);
+      }
+      S.xy[slot] = xy;
+    }
     if (lane < 4) {  // the last step's idle entries
       S.xy[n + lane] = make_double2(0.0, 0.0);
       S.bw[n + lane] = make_double2(0.0, 0.0);
+      if constexpr (F == 0) seconds[wave][n + lane] = make_double2(0.0, 0.0);
     }
     // the rule of the stage: what its visits need at most
     const bool panels = __ballot(v.on && v.nodes == 0) != 0;
-    int N = kMaxNodes;
+    int nodes = kMaxNodes;
     if (!panels)
-      while (N > 2 && !__ballot(v.on && v.nodes >= N)) --N;
-    const int at = N * (N - 1) / 2 - 1;
+      while (nodes > 2 && !__ballot(v.on && v.nodes >= nodes)) --nodes;
+    const int at = nodes * (nodes - 1) / 2 - 1;
     const double rl2 = -kLog2e * v.rb;
     double s0 = 0.0, D = 20.0;
     do {  // one rule on [0, L], or panel by panel until every lane's end at its L
       double s1 = v.L;
       if (panels) s1 = s0 < v.L ? gauss_panel_end(s0, v.x1max, D, v.L) : s0;
-      for (int k = 0; k < N; ++k) {
+      auto put = [&](double2* to, int k) {
         const double s = fma(s1 - s0, kRules.z[at + k], s0);
-        gauss_lds_sync();
         if (v.on)
-          S.bw[slot] = make_double2(rl2 * gauss_exp2<12>(kLog2e * s),
-                                    (s1 - s0) * kRules.w[at + k]);
-        gauss_lds_sync();
-        gauss_node<F>(S, n, lane, px, py, acc);
+          to[slot] = make_double2(rl2 * gauss_exp2<12>(kLog2e * s), (s1 - s0) * kRules.w[at + k]);
+      };
+      if constexpr (F == 0) {
+        double2* const bw2 = seconds[wave];
+        for (int k = 0; k < nodes; k += 2) {
+          gauss_lds_sync();
+          put(S.bw, k);
+          if (k + 1 < nodes) put(bw2, k + 1);
+          gauss_lds_sync();
+          const bool two = k + 1 < nodes;
+          if (flat)
+            two ? gauss_node_row<2, true>(S, bw2, n, along, py, row_acc)
+                : gauss_node_row<1, true>(S, bw2, n, along, py, row_acc);
+          else
+            two ? gauss_node_row<2, false>(S, bw2, n, px, py, row_acc)
+                : gauss_node_row<1, false>(S, bw2, n, px, py, row_acc);
+        }
+      } else {
+        for (int k = 0; k < nodes; ++k) {
+          gauss_lds_sync();
+          put(S.bw, k);
+          gauss_lds_sync();
+          gauss_node<F>(S, n, lane, px, py, acc);
+        }
       }
       s0 = s1;
     } while (panels && __ballot(v.on && s0 < v.L));
   }
+  double* out = j.partial + (int64_t)chunk * npix;
+  if constexpr (F == 0) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (p0 + lane + 64 * q < npix) out[p0 + lane + 64 * q] = row_acc[q];
+    return;
+  }
   // D element v of a lane: row 4 v + lane / 16, column lane % 16
-  double* out = j.partial + (int64_t)chunk * j.W * j.H;
 #pragma unroll
   for (int a = 0; a < F; ++a)
 #pragma unroll
@@ -369,14 +456,22 @@ __global__ void __launch_bounds__(256) k_gauss_reduce(const GaussJob* __restrict
 
 // Larger tiles take fewer exponentials per multiply-add, smaller ones more
 // waves: the largest tile that still gives the call about two waves per SIMD
-// (2048 items), with chunks of at least 64 visits and at most ~130 per map.
-// Where a call has more than 16k items of that kind, chunks grow to leave
-// about 8k, which bounds the partial sums (at most 32 kB an item) and their
-// traffic.
+// (2048 items), with chunks of at least 64 visits and at most ~130 per map --
+// or a smaller one that leaves so much less of itself empty that a node of four
+// visits takes fewer cycles for the whole map: 1780, 600 and 230 per tile for F =
+// 4, 2, 1, and 600 per row of 128 pixels, where a call has 2048 items of them (64x1
+// pixels, 256x256 scan: 314 us, 142 with F = 1).  64 maps of a 64x64 scan, 4096x1
+// pixels: 7.8 ms with F = 4, 1.6 in rows; 512x8: 2.7 with F = 4, 0.95 with F = 1; 8x8:
+// 0.84 and 0.16.
+// Where a call has more than 16k items of that kind (64k rows), chunks grow to
+// leave about half as many.  (Partial sums: at most 32 kB an item, and one chunk's
+// for a call of more than 8k tiles.)
 GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t) {
   auto up64 = [](int64_t v) { return (v + 63) / 64 * 64; };
   const int64_t base0 = std::max<int64_t>(64, up64((n_vis + 127) / 128));
-  auto tiles = [&](int64_t F) { return ((w + 16 * F - 1) / (16 * F)) * ((h + 16 * F - 1) / (16 * F)); };
+  auto tiles = [&](int64_t F) {
+    return F ? ((w + 16 * F - 1) / (16 * F)) * ((h + 16 * F - 1) / (16 * F)) : (w * h + kGaussRow - 1) / kGaussRow;
+  };
   const int64_t chunks = (n_vis + base0 - 1) / base0;
   GaussShape s{1, (int32_t)base0, 1};
   for (int F : {4, 2})
@@ -384,11 +479,18 @@ GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t) {
       s.F = F;
       break;
     }
-  const int64_t maps = n_t * tiles(s.F);
+  auto cycles = [&](int F) { return tiles(F) * (F == 4 ? 1780 : F == 2 ? 600 : F == 1 ? 230 : 600); };
+  int64_t least = cycles(s.F);
+  for (int F : {2, 1, 0})
+    if (F < s.F && cycles(F) < least && (F > 0 || n_t * tiles(F) * chunks >= 2048)) {
+      s.F = F;
+      least = cycles(F);
+    }
+  const int64_t maps = n_t * tiles(s.F), most = s.F ? 16384 : 65536;
   if (maps * chunks >= 4096) s.near = 0;
-  if (maps * chunks > 16384)
+  if (maps * chunks > most)
     s.base = (int32_t)std::min<int64_t>(
-        up64(n_vis), std::max<int64_t>(base0, up64(n_vis / std::max<int64_t>(1, 8192 / maps))));
+        up64(n_vis), std::max<int64_t>(base0, up64(n_vis / std::max<int64_t>(1, most / 2 / maps))));
   return s;
 }
 
@@ -406,7 +508,7 @@ hipError_t launch_gauss_map(const GaussJob* jobs, int32_t n_jobs, int64_t items,
       hipLaunchKernelGGL((k_gauss_map<FF, false>), grid, dim3(256), 0, st, jobs + k);    \
     break;
     switch (F) {
-      DD_GAUSS(1) DD_GAUSS(2) DD_GAUSS(4)
+      DD_GAUSS(0) DD_GAUSS(1) DD_GAUSS(2) DD_GAUSS(4)
       default: return hipErrorInvalidValue;
     }
 #undef DD_GAUSS
