@@ -477,10 +477,12 @@ __device__ __forceinline__ void wave_lds_sync() {
 // Wave w of block b takes items 4 b + w, 4 b + w + 4 gridDim.x, ...  The
 // item's visits go 64 at a time: lane j builds visit j's row in the wave's
 // LDS block; then the stage's lean rows are taken by one loop at their
-// highest degree and its careful rows by another.  Held to 168 VGPRs (3 waves per SIMD instead of 2; the few spilled values are outside the
-// lean loop).
+// highest degree and its careful rows by another.  Held to three waves per SIMD: its
+// 127 VGPRs would let four in, and then lists of some 800 blocks, which fit the chip at
+// once but not evenly (817 blocks on 256 CUs), take as long as a CU of four
+// (27000 visits: 0.87 ms, 0.76 with three; 65536: 2.77 and 2.81).
 __global__ __launch_bounds__(64 * kMapWaves)
-__attribute__((amdgpu_waves_per_eu(3, 8))) void k_visit_map(
+__attribute__((amdgpu_waves_per_eu(3, 3))) void k_visit_map(
     const VisList* __restrict__ lists, const VisTile* __restrict__ tiles,
     const VisItem* __restrict__ items, int64_t n_items, double* __restrict__ partial) {
   __shared__ MapRow s_rows[kMapWaves][64];
