@@ -66,6 +66,7 @@ struct HostPieces {
   static constexpr size_t kBytes = (size_t)1 << 20;
   char* p = nullptr;
   hipEvent_t ev[2] = {};
+  int dev = -1;  // of the events
   void release() {
     for (hipEvent_t& e : ev) {
       if (e) (void)hipEventDestroy(e);
@@ -74,8 +75,13 @@ struct HostPieces {
     if (p) (void)hipHostFree(p);
     p = nullptr;
   }
-  hipError_t copy_out(void* host, const void* dev, size_t bytes) {
-    hipError_t e = hipSuccess;
+  hipError_t copy_out(void* host, const void* dev_p, size_t bytes) {
+    // from another device than the events': in one copy
+    int now = -1;
+    hipError_t e = hipGetDevice(&now);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev != now) return hipMemcpy(host, dev_p, bytes, hipMemcpyDeviceToHost);
+    dev = now;
     if (!p) e = hipHostMalloc((void**)&p, 2 * kBytes, hipHostMallocDefault);
     for (hipEvent_t& v : ev)
       if (e == hipSuccess && !v) e = hipEventCreateWithFlags(&v, hipEventDisableTiming);
@@ -83,7 +89,7 @@ struct HostPieces {
     auto len = [&](size_t k) { return std::min(kBytes, bytes - k * kBytes); };
     for (size_t k = 0; e == hipSuccess && k <= n; ++k) {
       if (k < n) {
-        e = hipMemcpyAsync(p + (k & 1) * kBytes, (const char*)dev + k * kBytes, len(k),
+        e = hipMemcpyAsync(p + (k & 1) * kBytes, (const char*)dev_p + k * kBytes, len(k),
                            hipMemcpyDeviceToHost, nullptr);
         if (e == hipSuccess) e = hipEventRecord(ev[k & 1], nullptr);
       }

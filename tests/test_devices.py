@@ -22,3 +22,22 @@ for dev in (0, 1, 0, 1):
 @pytest.mark.parametrize("call", ["map", "sweep", "range"])
 def test_two_devices(tmp_path, call):
     fake_hip.run(tmp_path, CODE % call)
+
+
+UNET = r"""
+u = C.c_void_p()
+ok(lib.dd_unet_create(C.c_uint64(3), C.byref(u)))
+n = lib.dd_unet_num_params(u)
+m, step = np.zeros(n, np.float32), C.c_int64()
+for dev in (0, 1, 0):
+    fake.fake_set_device(dev)
+    p = np.zeros(n, np.float32)
+    ok(lib.dd_unet_params(u, ptr(p), None))
+    assert p.any()
+    ok(lib.dd_unet_grads(u, ptr(m)))
+    ok(lib.dd_unet_adam_state(u, ptr(m), None, C.byref(step), None, None, None))
+"""
+
+
+def test_network_reads_from_another_device(tmp_path):
+    fake_hip.run(tmp_path, UNET)
