@@ -49,15 +49,6 @@ __device__ __forceinline__ double2 ldc(const double2* p) {
 }
 #undef DD_CONST_AS
 
-// Per-lane load known to be from global memory (a plain vector load, not a
-// flat one, also through a pointer read from memory).
-__device__ __forceinline__ float4 ldg4(const float4* p) {
-  typedef float v4 __attribute__((ext_vector_type(4)));
-  const v4 v =
-      *reinterpret_cast<const __attribute__((address_space(1))) v4*>(reinterpret_cast<uintptr_t>(p));
-  return make_float4(v[0], v[1], v[2], v[3]);
-}
-
 constexpr double kLog2e = 1.4426950408889634;
 constexpr double kLn2 = 0.6931471805599453;
 constexpr double kEulerGamma = 0.5772156649015329;
@@ -458,18 +449,10 @@ __device__ __forceinline__ void flag_nonfinite(const OutFlag& f, double v, int64
   atomicMax(f.word, (f.seq << kFlagIndexBits) | (lim - i));
 }
 
-// The 8 bulk fields of an FP32 row; CAS: through the constant address space
-// (scalar loads also where the table pointer was read from memory).
-template <bool CAS>
+// The 8 bulk fields of a uniform FP32 row (scalar loads).
 __device__ __forceinline__ RowA load_rowa(const float* __restrict__ row) {
-  float4 u, v;
-  if constexpr (CAS) {
-    u = ldc(reinterpret_cast<const float4*>(row));
-    v = ldc(reinterpret_cast<const float4*>(row + 4));
-  } else {
-    u = *(const float4*)row;
-    v = *(const float4*)(row + 4);
-  }
+  const float4 u = ldc(reinterpret_cast<const float4*>(row));
+  const float4 v = ldc(reinterpret_cast<const float4*>(row + 4));
   return RowA{u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
 }
 

@@ -79,20 +79,6 @@ __device__ inline void make_row(double lam, double kappa, double s2, const GLNod
 
 // ---------------------------------------------------------------------------
 // Small helpers.
-template <int R>
-__device__ __forceinline__ float pairwise_sum(const float (&t)[R]) {
-  if constexpr (R == 1) {
-    return t[0];
-  } else if constexpr (R == 2) {
-    return t[0] + t[1];
-  } else if constexpr (R == 4) {
-    return (t[0] + t[1]) + (t[2] + t[3]);
-  } else {
-    static_assert(R == 8, "R must be 1, 2, 4 or 8");
-    return ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-  }
-}
-
 __device__ __forceinline__ void wave_sync() {
   // a wave's LDS operations complete in order: a compiler barrier at
   // wavefront scope orders its writes before other lanes' reads
@@ -118,54 +104,31 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 // single exponential P_0 2^{-a RA}.
 enum { kFormFull = 0, kFormPlain = 1, kFormFold = 2 };
 
-// The two fields of the folded form.
-struct RowF {
-  float ra, p0;
-};
+// A uniform lag row (map tiles): the 8 bulk fields; degrees above 3 read the row in
+// place.
+template <int M>
+using RowSel = typename std::conditional<(M <= kMaxA), RowA, const float*>::type;
 
-template <int M, int F = kFormFull>
-struct RowSel {
-  // folded: RA and P_0; degree <= 3: the 8 bulk fields; higher degrees read
-  // the row in place
-  using type = typename std::conditional<
-      F == kFormFold, RowF,
-      typename std::conditional<(M <= kMaxA), RowA, const float*>::type>::type;
-};
-
-template <int M, bool CAS = true, int F = kFormFull>
-__device__ __forceinline__ typename RowSel<M, F>::type fetch_row(const float* __restrict__ rows,
-                                                                 int64_t n) {
-  if constexpr (F == kFormFold) {
-    const float* row = rows + n * kRow32;
-    if constexpr (CAS)
-      return RowF{ldc(row + kR32_RA), ldc(row + kR32_P0)};
-    else
-      return RowF{row[kR32_RA], row[kR32_P0]};
-  } else if constexpr (M <= kMaxA) {
-    return load_rowa<CAS>(rows + n * kRow32);
-  } else {
+template <int M>
+__device__ __forceinline__ RowSel<M> fetch_row(const float* __restrict__ rows, int64_t n) {
+  if constexpr (M <= kMaxA)
+    return load_rowa(rows + n * kRow32);
+  else
     return rows + n * kRow32;
-  }
 }
 
-template <int M, int F = kFormFull>
-__device__ __forceinline__ float series_row32(float a, const typename RowSel<M, F>::type& row) {
-  if constexpr (F == kFormFold) {
-    return row.p0 * __builtin_amdgcn_exp2f(-(a * row.ra));
-  } else if constexpr (M <= kMaxA) {
-    static_assert(F == kFormFull || F == kFormPlain, "unknown form");
-    return series_f32a<M, F == kFormFull>(a, row);
-  } else {
-    static_assert(F == kFormFull, "the lighter forms need degree <= 3");
+template <int M>
+__device__ __forceinline__ float series_row32(float a, const RowSel<M>& row) {
+  if constexpr (M <= kMaxA)
+    return series_f32a<M>(a, row);
+  else
     return series_f32<M>(a, row);
-  }
 }
 
 // The term as its two factors (q returned, t set), for sums that must not
 // depend on how the compiler fuses products into additions.
 template <int M>
-__device__ __forceinline__ float series_row32_q(float a, const typename RowSel<M>::type& row,
-                                                float& t) {
+__device__ __forceinline__ float series_row32_q(float a, const RowSel<M>& row, float& t) {
   if constexpr (M <= kMaxA)
     return series_f32a_q<M>(a, row, t);
   else
@@ -825,7 +788,7 @@ template <int M, int R, int U, bool MM>
 __device__ __forceinline__ void map_far32(int lo, int hi, int64_t K, const MapPos& pos,
                                           const float* __restrict__ rows, const MapPix<R, MM>& px,
                                           double (&acc)[R]) {
-  using Row = typename RowSel<M>::type;
+  using Row = RowSel<M>;
   int n = lo;
   if (n + U <= hi) {
     Row cur[U];

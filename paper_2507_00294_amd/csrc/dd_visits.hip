@@ -605,11 +605,10 @@ constexpr double kBulkD64 = 1.0 / 512, kBulkX64 = 1.0 / 32;
 constexpr float kBulkU32 = 1.0f / 64, kBulkV32 = 1.0f / 32;
 
 // F(u, v) by Horner in u per power of v, then in v.
-template <typename T, int NM, int D0, int D1, int D2, int D3, int D4 = -1, int D5 = -1,
-          int D6 = -1>
+template <typename T, int NM, int D0, int D1, int D2, int D3>
 __device__ __forceinline__ T bulk_f(T u, T v) {
   constexpr BulkCoef C{};
-  constexpr int deg[7] = {D0, D1, D2, D3, D4, D5, D6};
+  constexpr int deg[4] = {D0, D1, D2, D3};
   T acc = 0;
 #pragma unroll
   for (int m = NM - 1; m >= 0; --m) {
