@@ -171,12 +171,15 @@ void build_layers(dd_unet& u) {
 int64_t M_of(const dd_unet& u, const Conv& c) { return (int64_t)u.B * c.H * c.H; }
 
 // Partial sums of all weight, bias and head gradients of a batch of B maps, in
-// the order of the layers: where each part starts (floats) and the sums to
-// form, with `part` their base.
+// the order of the layers: where each part starts (floats), and with their base
+// `part` the sums to form.
 size_t grad_parts(const dd_unet& u, int B, float* part, nn::PartTable& tab,
                   std::vector<size_t>& w_at, std::vector<size_t>& b_at) {
   size_t at = 0;
   tab.n = 0;
+  auto add = [&](size_t from, int64_t stride, int64_t n, int splits, float* out) {
+    if (part) tab.l[tab.n++] = nn::PartDesc{part + from, stride, n, splits, out};
+  };
   w_at.clear();
   b_at.clear();
   float* g = u.g.as<float>();
@@ -185,15 +188,14 @@ size_t grad_parts(const dd_unet& u, int B, float* part, nn::PartTable& tab,
     const int64_t M = (int64_t)B * c.H * c.H, n = 9LL * c.ci * c.co;
     const int sp = nn::wgrad_splits(M, c.ci, c.co);
     w_at.push_back(at);
-    tab.l[tab.n++] = nn::PartDesc{part + at, n, n, sp, g + c.w_off};
+    add(at, n, n, sp, g + c.w_off);
     at += (size_t)sp * n;
     // the last layer's blocks also hold the head's sums: bias, then head
     const bool head = l + 1 == u.L.size();
     const int64_t len = head ? 2 * c.co + 1 : c.co;
     b_at.push_back(at);
-    tab.l[tab.n++] = nn::PartDesc{part + at, len, c.co, nn::kActBlocks, g + c.b_off};
-    if (head)
-      tab.l[tab.n++] = nn::PartDesc{part + at + c.co, len, c.co + 1, nn::kActBlocks, g + u.head_w};
+    add(at, len, c.co, nn::kActBlocks, g + c.b_off);
+    if (head) add(at + c.co, len, c.co + 1, nn::kActBlocks, g + u.head_w);
     at += (size_t)nn::kActBlocks * len;
   }
   return at;
