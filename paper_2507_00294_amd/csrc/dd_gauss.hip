@@ -459,13 +459,21 @@ __global__ void __launch_bounds__(256) k_gauss_reduce(const GaussJob* __restrict
 // (2048 items), with chunks of at least 64 visits and at most ~130 per map --
 // or a smaller one that leaves so much less of itself empty that a node of four
 // visits takes fewer cycles for the whole map: 1780, 600 and 230 per tile for F =
-// 4, 2, 1, and 600 per row of 128 pixels, where a call has 2048 items of them (64x1
-// pixels, 256x256 scan: 314 us, 142 with F = 1).  64 maps of a 64x64 scan, 4096x1
-// pixels: 7.8 ms with F = 4, 1.6 in rows; 512x8: 2.7 with F = 4, 0.95 with F = 1; 8x8:
-// 0.84 and 0.16.
+// 4, 2, 1, and 600 per row of 128 pixels, where a call has 2048 items of them, or
+// 1024 and they take half the cycles (64x1 pixels, 256x256 scan, 128 items: 314 us,
+// 142 with F = 1; 500x2 of 65536 visits, 1024 items: 380 and 231; 1x2048 of 4096 visits,
+// 1024 items: 12 and 28 a map).  64 maps of a 64x64 scan,
+// 4096x1 pixels: 7.8 ms with F = 4, 1.5 in rows; 512x8: 2.7 with F = 4, 0.95 with F = 1;
+// 8x8: 0.84 and 0.16.  (With the recent visits apart, below: 1.1, 0.65 and 0.09.)
 // Where a call has more than 16k items of that kind (64k rows), chunks grow to
-// leave about half as many.  (Partial sums: at most 32 kB an item, and one chunk's
-// for a call of more than 8k tiles.)
+// leave about half as many.
+// The 64 most recent visits of a map take up to a hundred nodes each, a million
+// cycles of one wave at F = 4, as much as thousands of older ones: they have chunks of
+// their own, unless the call's tiles alone are enough for every wave to have such a
+// share (256 maps of 33x33 of a 64x64 scan: 3.3 ms without, 0.59; 64 of 128x128:
+// 2.9 and 0.56; 512 of 128x128: 7.5 and 4.7; 4000 of 64x64 of an 8x8 scan: 0.87
+// without, 1.2).  Partial sums: at most 32 kB an item, 1 GiB in all, or one chunk's
+// for a call of more than 8k tiles.
 GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t) {
   auto up64 = [](int64_t v) { return (v + 63) / 64 * 64; };
   const int64_t base0 = std::max<int64_t>(64, up64((n_vis + 127) / 128));
@@ -481,13 +489,15 @@ GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t) {
     }
   auto cycles = [&](int F) { return tiles(F) * (F == 4 ? 1780 : F == 2 ? 600 : F == 1 ? 230 : 600); };
   int64_t least = cycles(s.F);
+  const int64_t row_items = n_t * tiles(0) * chunks;
   for (int F : {2, 1, 0})
-    if (F < s.F && cycles(F) < least && (F > 0 || n_t * tiles(F) * chunks >= 2048)) {
+    if (F < s.F && (F > 0 || row_items >= 2048 ? cycles(F) < least
+                                               : row_items >= 1024 && 2 * cycles(F) < least)) {
       s.F = F;
       least = cycles(F);
     }
   const int64_t maps = n_t * tiles(s.F), most = s.F ? 16384 : 65536;
-  if (maps * chunks >= 4096) s.near = 0;
+  if (maps >= (chunks > 1 ? 4096 : 2048)) s.near = 0;
   if (maps * chunks > most)
     s.base = (int32_t)std::min<int64_t>(
         up64(n_vis), std::max<int64_t>(base0, up64(n_vis / std::max<int64_t>(1, most / 2 / maps))));

@@ -34,3 +34,28 @@ for n_t in (4 if w * h > 50000 else 64,):
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"{s[0]}x{s[1]}")
 def test_tiles_fit(tmp_path, shape):
     fake_hip.run(tmp_path, CODE % (shape,))
+
+
+RECENT = r"""
+import re
+side, w, h, n_t, tiles, least = %r
+s = scan(side, side, "random", seed=1)
+V = side * side
+g, out = dd.Grid(0, 0, 1e-9, 1e-9, w, h), buf(n_t * w * h)
+t = (C.c_double * n_t)(*[V * 1e-6 * (k + 1) / n_t for k in range(n_t)])
+ok(lib.dd_damage_map(s.handle, C.byref(g), t, n_t, 0, ptr(out), 1, None))
+blocks = [(x, y) for name, x, y in launches() if "k_gauss_map" in name]
+assert len(blocks) == 1 and blocks[0][1] == n_t, blocks
+# chunks of 2, 2, 4, .. 32 recent visits beside those of older ones
+assert 4 * blocks[0][0] / tiles >= least, blocks
+"""
+
+
+@pytest.mark.parametrize("case", [(64, 33, 33, 256, 1, 69), (64, 48, 48, 256, 1, 69),
+                                  (128, 33, 33, 256, 1, 38), (64, 128, 128, 512, 4, 10),
+                                  (64, 100, 30, 16, 4, 69), (16, 64, 64, 256, 4, 9)],
+                         ids=lambda c: "-".join(map(str, c)))
+def test_recent_visits_split(tmp_path, case):
+    """The most recent visits take most nodes: they are spread over waves in every
+    call whose maps alone do not fill the chip many times over."""
+    fake_hip.run(tmp_path, RECENT % (case,))
