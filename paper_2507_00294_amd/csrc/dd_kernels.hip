@@ -130,18 +130,32 @@ k_arrival_range32(const float2* __restrict__ pos, const uint2* __restrict__ posh
   do_arrival_far32<R, false>(items[it], posh, rows32, V, bnd, partial, pstride, pj0, lds);
 }
 
-// Near-band and far items in launches of their own, each with the registers of
-// its own code.
-template <int R, bool NEAR, bool MM>
+// Far and near-band items of a mixed map call in one launch, far blocks first: a
+// small call is bound by its longest item, and an item of one kind fills the time of
+// the other's.  One 16x16 map of a 128x128 scan: 154 us far and 48 near in launches of
+// their own, 160 as mixed blocks of near and far waves, 145 so; 64 maps of 64x64 of
+// it 1.15 ms apart, 0.95 together (near blocks first: 1.18).
+template <int R, bool MM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_map(const uint2* __restrict__ pos, const float4* __restrict__ pos4,
       const double* __restrict__ rows64, const float* __restrict__ rows32,
-      const MapItem* __restrict__ items, int n_items, const MapTime* __restrict__ times, double X0,
-      double Y0, double DX, double DY, int W, int H, double* __restrict__ partial) {
-  const int it = blockIdx.x * 4 + wave_id();
-  if (it >= n_items) return;
+      const MapItem* __restrict__ items, int n_near, int n_items,
+      const MapTime* __restrict__ times, double X0, double Y0, double DX, double DY, int W, int H,
+      double* __restrict__ partial) {
+  const MapPos at{pos, pos4};
+  const int far_blocks = (n_items - n_near + 3) / 4;
+  if ((int)blockIdx.x < far_blocks) {
+    const int it = n_near + blockIdx.x * 4 + wave_id();
+    if (it >= n_items) return;
+    const MapItem item = items[it];
+    do_map<R, false, MM>(item, times[item.m], at, rows64, rows32, X0, Y0, DX, DY, W, H, partial);
+    return;
+  }
+  const int it = (blockIdx.x - far_blocks) * 4 + wave_id();
+  if (it >= n_near) return;
   const MapItem item = items[it];
-  do_map<R, NEAR, MM>(item, times[item.m], MapPos{pos, pos4}, rows64, rows32, X0, Y0, DX, DY, W, H, partial);
+  do_map<map_near_r(R), true, MM>(item, times[item.m], at, rows64, rows32, X0, Y0, DX, DY, W, H,
+                                  partial);
 }
 
 // ---------------------------------------------------------------------------
@@ -306,18 +320,13 @@ hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int R, bool NEAR>
-static void launch_map_items(const MapLaunch& L, const MapItem* items, int n, hipStream_t st) {
-  if (n <= 0) return;
-  auto k = L.matrix ? k_map<R, NEAR, true> : k_map<R, NEAR, false>;
-  hipLaunchKernelGGL(k, dim3((n + 3) / 4), dim3(256), 0, st, L.posh, L.pos4, L.rows64, L.rows32,
-                     items, n, L.times, L.X0, L.Y0, L.DX, L.DY, L.W, L.H, L.partial);
-}
-
 template <int R>
 static void launch_map_r(const MapLaunch& L, hipStream_t st) {
-  launch_map_items<R, false>(L, L.items + L.n_near, L.n_items - L.n_near, st);
-  launch_map_items<map_near_r(R), true>(L, L.items, L.n_near, st);
+  const unsigned blocks = (unsigned)((L.n_items - L.n_near + 3) / 4 + (L.n_near + 3) / 4);
+  if (blocks == 0) return;
+  auto k = L.matrix ? k_map<R, true> : k_map<R, false>;
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, L.posh, L.pos4, L.rows64, L.rows32, L.items,
+                     L.n_near, L.n_items, L.times, L.X0, L.Y0, L.DX, L.DY, L.W, L.H, L.partial);
 }
 
 hipError_t launch_map(const MapLaunch& L, hipStream_t st) {
