@@ -74,6 +74,16 @@ struct GaussShape {
 };
 GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t);
 
+// The job of block (x, y) of a grid of n_jobs by the jobs' blocks; y is the block of
+// the job.  The same blocks of all jobs are dealt out together, the recent (long)
+// chunks first, to the 32 shader engines in turn; the rotation by y keeps an engine
+// from having the same jobs, whose numbers of visits differ, in every row.  (A row
+// per job gave an engine the same chunks of every job in grids of 16, 32, .. blocks a
+// job: 384 maps of 1000x1 pixels of a 256x256 scan 60 ms, 16.6 so.)
+__host__ __device__ inline uint32_t gauss_job_of(uint32_t x, uint32_t y, uint32_t n_jobs) {
+  return (uint32_t)(((uint64_t)x + y) % n_jobs);
+}
+
 // Fills the tile and chunk fields of a job whose grid and n are set.
 inline void gauss_split(GaussJob& j, const GaussShape& s) {
   const int32_t T = 16 * s.F;

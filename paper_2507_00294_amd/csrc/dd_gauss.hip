@@ -287,17 +287,17 @@ __device__ __forceinline__ void gauss_node_row(const GaussStage& S, const double
   }
 }
 
-// Wave w of block (x, y): item 4 x + w of job y -- tile item % tiles, chunk
-// item / tiles (the recent visits, which take most nodes, first).
+// Wave w of block (x, y): item 4 (block0 + y) + w of job gauss_job_of(x, y) -- tile
+// item % tiles, chunk item / tiles (the recent visits, which take most nodes, first).
 template <int F, bool VIS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F == 4 ? 2 : F == 2 ? 3 : 4, 8)))
-k_gauss_map(const GaussJob* __restrict__ jobs) {
+k_gauss_map(const GaussJob* __restrict__ jobs, uint32_t block0) {
   __shared__ GaussStage stages[4];
   __shared__ double2 seconds[F ? 1 : 4][F ? 1 : kGaussLds];  // F = 0: the second node of two
-  const GaussJob& j = jobs[blockIdx.y];
+  const GaussJob& j = jobs[gauss_job_of(blockIdx.x, blockIdx.y, gridDim.x)];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t item = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t item = (int64_t)(block0 + blockIdx.y) * 4 + wave;
   if (item >= (int64_t)j.tiles * j.n_chunks) return;
   GaussStage& S = stages[wave];
   const int tile = (int)(item % j.tiles), chunk = (int)(item / j.tiles);
@@ -507,24 +507,25 @@ GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t) {
 hipError_t launch_gauss_map(const GaussJob* jobs, int32_t n_jobs, int64_t items, int32_t F,
                             bool vis, hipStream_t st) {
   if (n_jobs <= 0 || items <= 0) return hipSuccess;
-  const unsigned bx = (unsigned)((items + 3) / 4);
-  for (int32_t k = 0; k < n_jobs; k += 32768) {
-    const dim3 grid(bx, (unsigned)std::min(32768, n_jobs - k));
-#define DD_GAUSS(FF)                                                                     \
-  case FF:                                                                               \
-    if (vis)                                                                             \
-      hipLaunchKernelGGL((k_gauss_map<FF, true>), grid, dim3(256), 0, st, jobs + k);     \
-    else                                                                                 \
-      hipLaunchKernelGGL((k_gauss_map<FF, false>), grid, dim3(256), 0, st, jobs + k);    \
-    break;
-    switch (F) {
-      DD_GAUSS(0) DD_GAUSS(1) DD_GAUSS(2) DD_GAUSS(4)
-      default: return hipErrorInvalidValue;
+  if (F != 0 && F != 1 && F != 2 && F != 4) return hipErrorInvalidValue;
+  const int64_t blocks = (items + 3) / 4;
+  constexpr int32_t kJobs = 1 << 20, kBlocks = 32768;  // per launch
+  for (int32_t k = 0; k < n_jobs; k += kJobs)
+    for (int64_t b = 0; b < blocks; b += kBlocks) {
+      const dim3 grid((unsigned)std::min(kJobs, n_jobs - k),
+                      (unsigned)std::min<int64_t>(kBlocks, blocks - b));
+      auto map = vis ? (F == 0   ? k_gauss_map<0, true>
+                        : F == 1 ? k_gauss_map<1, true>
+                        : F == 2 ? k_gauss_map<2, true>
+                                 : k_gauss_map<4, true>)
+                     : (F == 0   ? k_gauss_map<0, false>
+                        : F == 1 ? k_gauss_map<1, false>
+                        : F == 2 ? k_gauss_map<2, false>
+                                 : k_gauss_map<4, false>);
+      hipLaunchKernelGGL(map, grid, dim3(256), 0, st, jobs + k, (uint32_t)b);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
     }
-#undef DD_GAUSS
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   return hipSuccess;
 }
 

@@ -45,9 +45,9 @@ g, out = dd.Grid(0, 0, 1e-9, 1e-9, w, h), buf(n_t * w * h)
 t = (C.c_double * n_t)(*[V * 1e-6 * (k + 1) / n_t for k in range(n_t)])
 ok(lib.dd_damage_map(s.handle, C.byref(g), t, n_t, 0, ptr(out), 1, None))
 blocks = [(x, y) for name, x, y in launches() if "k_gauss_map" in name]
-assert len(blocks) == 1 and blocks[0][1] == n_t, blocks
+assert len(blocks) == 1 and blocks[0][0] == n_t, blocks
 # chunks of 2, 2, 4, .. 32 recent visits beside those of older ones
-assert 4 * blocks[0][0] / tiles >= least, blocks
+assert 4 * blocks[0][1] / tiles >= least, blocks
 """
 
 
