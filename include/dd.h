@@ -235,7 +235,9 @@ dd_status dd_tune_load(const char *cache_path);
  * a table of distinct terms, the table's 29 + 2M per term and its sums; the
  * mixed arrival query's squared distance, 5 of these, runs on the matrix
  * cores).  Kernel names: "arrival_far", "arrival_near", "map", "batch",
- * "lag_rows", "reduce".                                                   */
+ * "lag_rows", "reduce".  Where both bands of a mixed arrival query share a
+ * launch, its time is that of "arrival_far", and "arrival_near" has the near
+ * band's pairs and operations alone.                                      */
 typedef struct {
   double ms;         /* summed event time of the launches                   */
   int64_t launches;

@@ -590,9 +590,10 @@ dd_status dd::launch_range(dd_scan* s, bool mixed, const RangePlan& rp, int64_t 
   if (mixed) {  // one launch for both bands
     L.n_items = P.n_near + P.n_far;
     L.R = P.R;
+    if (profile) prof_end(prof_begin("arrival_near", st), st, P.near_pairs, P.near_flops);
     ProfToken tf = profile ? prof_begin("arrival_far", st) : ProfToken{};
     DD_HIP(launch_arrival_range(L, P.n_near, P.RN, st), "arrival range launch");
-    if (profile) prof_end(tf, st, P.near_pairs + P.far_pairs, P.near_flops + P.far_flops);
+    if (profile) prof_end(tf, st, P.far_pairs, P.far_flops);
   } else {
     L.n_items = P.n_near;
     L.near = true;
