@@ -145,7 +145,7 @@ __device__ __forceinline__ float series_row32_q(float a, const RowSel<M>& row, f
 //
 // Lane l = 4 b + c owns the R visits j = J + R u + t, t < R, u = far_unit(b) + 2 c:
 // a block's columns are every other unit of R visits, and two blocks share eight
-// units.  Step D takes, per t, the four earlier visits i = J + R far_unit(b) + t - D
+// units (items with an edge: every unit, u = 4 b + c, see kFarSpace).  Step D takes, per t, the four earlier visits i = J + R far_unit(b) + t - D
 // - v, v < 4, of block b (the A rows) against the block's four columns c: lane
 // (b, c) gets the pairs of lags D + 2 R c + v, four consecutive lags per lane and
 // step.  The lag now differs between a block's lanes, so the fields of the lag
@@ -243,8 +243,17 @@ __device__ __forceinline__ void load_posh(const uint2* p, half4_t (&q)[R]) {
   }
 }
 
-// First unit of R visits of block b (lanes 4 b .. 4 b + 3).
-__device__ __forceinline__ int far_unit(int b) { return 8 * (b >> 1) + (b & 1); }
+// Units of R visits between a block's columns, and its first unit (b: lanes 4 b ..
+// 4 b + 3).  Items with an edge add their terms one by one, whatever the parity of a
+// group; there every unit is a column, and the slant adds half as many lags to each
+// segment, which in a small scan is short: 9x7 visits 69 us with every other unit,
+// 61 so.
+template <bool EDGE>
+constexpr int kFarSpace = EDGE ? 1 : 2;
+template <bool EDGE>
+__device__ __forceinline__ int far_unit(int b) {
+  return EDGE ? 4 * b : 8 * (b >> 1) + (b & 1);
+}
 
 // Of a group's first two products one is rounded by itself, the other enters by a
 // fused multiply-add: 0 if the first (lag lo + R k), 1 if the second.  Either is
@@ -262,13 +271,13 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
                                           const half4_t (&e)[R], const float (&ee)[R],
                                           const float* __restrict__ rows, char* lds,
                                           double (&acc)[R]) {
-  constexpr int NF = FarRow<M, F>::n;
+  constexpr int NF = FarRow<M, F>::n, SP = kFarSpace<EDGE>;
   typedef float vec __attribute__((ext_vector_type(NF == 2 ? 2 : 4)));
   constexpr int NV = NF == 2 ? 1 : NF / 4;
   const int lane = threadIdx.x & 63, c = lane & 3;
-  const int64_t Jb = J + R * far_unit(lane >> 2);
+  const int64_t Jb = J + R * far_unit<EDGE>(lane >> 2);
   vec* const ring = reinterpret_cast<vec*>(lds);
-  const int L0 = lo - 6 * R;  // ring entry of lag n: (n - L0) % 128
+  const int L0 = lo - 3 * SP * R;  // ring entry of lag n: (n - L0) % 128
   // lane l fetches the row of lag L0 + 64 k + l
   auto fetch = [&](int k, float(&w)[NF]) {
     const int n = L0 + 64 * k + lane;
@@ -300,7 +309,7 @@ __device__ __forceinline__ void arr_far32(int lo, int hi, const uint2* __restric
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       // groups of R lags are aligned, so that only they can wrap
-      const int at = ((4 * s + 2 * R * c + v / R * R) & (kRingLags - 1)) + v % R;
+      const int at = ((4 * s + SP * R * c + v / R * R) & (kRingLags - 1)) + v % R;
       float w[NF];
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
@@ -437,15 +446,14 @@ __device__ __forceinline__ void seg_range(const DegreeBounds& b, int M, int n_lo
 // One wavefront processes one arrival work item (far region).  The sums of
 // visit j go to partial[slot * pstride + j - pj0]: pstride = V and pj0 = 0
 // for a whole-scan query; a visit range keeps only the columns of its tiles.
-template <int R, bool CAS>
-__device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint2* __restrict__ pos,
-                                                 const float* __restrict__ rows, int64_t V,
-                                                 const DegreeBounds& bnd,
-                                                 double* __restrict__ partial, int64_t pstride,
-                                                 int64_t pj0, char* lds) {
+template <int R, bool CAS, bool EDGE>
+__device__ __forceinline__ void arrival_far32(const ArrItem& item, const uint2* __restrict__ pos,
+                                              const float* __restrict__ rows, int64_t V,
+                                              const DegreeBounds& bnd, double* __restrict__ partial,
+                                              int64_t pstride, int64_t pj0, char* lds) {
   const int lane = threadIdx.x & 63;
   const int64_t J = (int64_t)item.tile * (64 * R);
-  const int64_t jl = J + R * (far_unit(lane >> 2) + 2 * (lane & 3));
+  const int64_t jl = J + R * (far_unit<EDGE>(lane >> 2) + kFarSpace<EDGE> * (lane & 3));
   half4_t e[R];
   float ee[R];
   double acc[R];
@@ -457,7 +465,6 @@ __device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint
                    (_Float16)1.0f};
     acc[r] = 0.0;
   }
-  const bool edge = (item.slot_flags & kItemEdge) != 0;
   // rows [n_lo, fold) by degree segment, each split at `plain`; then the
   // folded rows [fold, n_hi) whatever their degree segment
   const int n_fold = max(item.n_lo, min(item.n_hi, bnd.fold));
@@ -466,24 +473,27 @@ __device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint
     seg_range(bnd, M, item.n_lo, n_fold, lo, hi);
     if (lo >= hi) continue;
     const int mid = max(lo, min(hi, bnd.plain));
-    if (edge) {
-      if (lo < mid) arr_far32_seg<R, true, CAS>(M, lo, mid, pos, J, e, ee, rows, lds, acc);
-      if (mid < hi) arr_far32_seg<R, true, CAS, true>(M, mid, hi, pos, J, e, ee, rows, lds, acc);
-    } else {
-      if (lo < mid) arr_far32_seg<R, false, CAS>(M, lo, mid, pos, J, e, ee, rows, lds, acc);
-      if (mid < hi) arr_far32_seg<R, false, CAS, true>(M, mid, hi, pos, J, e, ee, rows, lds, acc);
-    }
+    if (lo < mid) arr_far32_seg<R, EDGE, CAS>(M, lo, mid, pos, J, e, ee, rows, lds, acc);
+    if (mid < hi) arr_far32_seg<R, EDGE, CAS, true>(M, mid, hi, pos, J, e, ee, rows, lds, acc);
   }
-  if (n_fold < item.n_hi) {
-    if (edge)
-      arr_far32<0, R, true, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, lds, acc);
-    else
-      arr_far32<0, R, false, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, lds, acc);
-  }
+  if (n_fold < item.n_hi)
+    arr_far32<0, R, EDGE, CAS, kFormFold>(n_fold, item.n_hi, pos, J, e, ee, rows, lds, acc);
   const int64_t base = (int64_t)(item.slot_flags & kSlotMask) * pstride - pj0;
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (jl + r < V) partial[base + jl + r] = acc[r];
+}
+
+template <int R, bool CAS>
+__device__ __forceinline__ void do_arrival_far32(const ArrItem& item, const uint2* __restrict__ pos,
+                                                 const float* __restrict__ rows, int64_t V,
+                                                 const DegreeBounds& bnd,
+                                                 double* __restrict__ partial, int64_t pstride,
+                                                 int64_t pj0, char* lds) {
+  if (item.slot_flags & kItemEdge)
+    arrival_far32<R, CAS, true>(item, pos, rows, V, bnd, partial, pstride, pj0, lds);
+  else
+    arrival_far32<R, CAS, false>(item, pos, rows, V, bnd, partial, pstride, pj0, lds);
 }
 
 template <int R>

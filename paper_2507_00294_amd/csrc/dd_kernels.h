@@ -36,9 +36,9 @@ struct ArrivalLaunch {
   bool range = false;       // a visit-range query (its own kernel instantiations)
 };
 hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st);
-// Both bands of a mixed visit-range query in one launch: L.items holds n_near
-// near items (tile RN) first; L.R is the far tile, L.near and L.range are not read.
-hipError_t launch_arrival_range(const ArrivalLaunch& L, int n_near, int RN, hipStream_t st);
+// Both bands of a mixed query in one launch: L.items holds n_near near items (tile
+// RN) first; L.R is the far tile, L.range the choice of queues, L.near is not read.
+hipError_t launch_arrival_both(const ArrivalLaunch& L, int n_near, int RN, hipStream_t st);
 
 // A mixed-precision map call (FP64: dd_gauss.h).
 struct MapLaunch {

@@ -103,26 +103,26 @@ __global__ void __launch_bounds__(256) k_arrival_near(const void* __restrict__ p
                             arr_lds<MIXED ? sizeof(NearQueue<kNearQ>) : 16>());
 }
 
-// Both bands of a visit range in mixed precision: blocks of near items first,
-// whose waves are few (a range's 1024 visits: 200) and long, then the far ones.
-// Queues short enough for four blocks of the far region per CU.  1024 visits of
-// 512x512 in random order: 18 us near and 69 us far one after the other, 72
-// together.
+// Both bands of a visit range or of a small query in mixed precision: blocks of
+// near items first, whose waves are few (a range's 1024 visits: 200) and long, then
+// the far ones.  A range's queues (Q) are short enough for four blocks of the far
+// region per CU: 1024 visits of 512x512 in random order, 18 us near and 69 us far
+// one after the other, 72 together.  A query's are those of its near band in a
+// launch of its own, so that the sums are the same in either.
 constexpr int kRangeQ = 9;
-template <int R, int RN>
+template <int R, int RN, int Q>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_arrival_range32(const float2* __restrict__ pos, const uint2* __restrict__ posh,
+k_arrival_both32(const float2* __restrict__ pos, const uint2* __restrict__ posh,
                   const double* __restrict__ rows64, const float* __restrict__ rows32,
                   const ArrItem* __restrict__ items, int n_near, int n_items, int64_t V,
                   DegreeBounds bnd, double* __restrict__ partial, int64_t pstride, int64_t pj0) {
-  constexpr int kQueue = sizeof(NearQueue<kRangeQ>);
+  constexpr int kQueue = sizeof(NearQueue<Q>);
   char* lds = arr_lds<(kQueue > kRingBytes ? kQueue : kRingBytes)>();
   const int near_blocks = (n_near + 3) / 4;
   if ((int)blockIdx.x < near_blocks) {
     const int it = blockIdx.x * 4 + wave_id();
     if (it < n_near)
-      do_arrival_near<RN, true, kRangeQ>(items[it], pos, rows64, rows32, V, partial, pstride, pj0,
-                                         lds);
+      do_arrival_near<RN, true, Q>(items[it], pos, rows64, rows32, V, partial, pstride, pj0, lds);
     return;
   }
   const int it = n_near + (blockIdx.x - near_blocks) * 4 + wave_id();
@@ -294,23 +294,33 @@ static void launch_arrival_kind(const ArrivalLaunch& L, hipStream_t st, unsigned
                        L.items, L.n_items, L.V, L.bounds, L.partial, L.pstride, L.pj0);
 }
 
-hipError_t launch_arrival_range(const ArrivalLaunch& L, int n_near, int RN, hipStream_t st) {
-  const int n_far = L.n_items - n_near;
-  const unsigned blocks = (unsigned)((n_near + 3) / 4 + (n_far + 3) / 4);
-  if (blocks == 0) return hipSuccess;
-  auto k = L.R == 4 ? (RN == 4 ? k_arrival_range32<4, 4> : k_arrival_range32<4, 2>)
-                    : (RN == 4 ? k_arrival_range32<2, 4> : k_arrival_range32<2, 2>);
-  if (!L.mixed || (L.R != 2 && L.R != 4) || (RN != 2 && RN != 4)) return hipErrorInvalidValue;
+template <int R, int RN>
+static void launch_arrival_both_r(const ArrivalLaunch& L, int n_near, unsigned blocks,
+                                  hipStream_t st) {
+  auto k = L.range ? k_arrival_both32<R, RN, kRangeQ> : k_arrival_both32<R, RN, kNearQ>;
   hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, (const float2*)L.pos, L.posh, L.rows64,
                      L.rows32, L.items, n_near, L.n_items, L.V, L.bounds, L.partial, L.pstride,
                      L.pj0);
+}
+
+hipError_t launch_arrival_both(const ArrivalLaunch& L, int n_near, int RN, hipStream_t st) {
+  const int n_far = L.n_items - n_near;
+  const unsigned blocks = (unsigned)((n_near + 3) / 4 + (n_far + 3) / 4);
+  if (blocks == 0) return hipSuccess;
+  if (!L.mixed || (L.R != 2 && L.R != 4) || (RN != 2 && RN != 4)) return hipErrorInvalidValue;
+  if (L.R == 4)
+    RN == 4 ? launch_arrival_both_r<4, 4>(L, n_near, blocks, st)
+            : launch_arrival_both_r<4, 2>(L, n_near, blocks, st);
+  else
+    RN == 4 ? launch_arrival_both_r<2, 4>(L, n_near, blocks, st)
+            : launch_arrival_both_r<2, 2>(L, n_near, blocks, st);
   return hipGetLastError();
 }
 
 // Near-band and far-region items are launched separately (L.near).
 hipError_t launch_arrival(const ArrivalLaunch& L, hipStream_t st) {
   if (L.n_items <= 0) return hipSuccess;
-  if (L.mixed && L.range) return hipErrorInvalidValue;  // launch_arrival_range
+  if (L.mixed && L.range) return hipErrorInvalidValue;  // launch_arrival_both
   const unsigned blocks = (unsigned)((L.n_items + 3) / 4);
   switch (L.R) {
     case 2: launch_arrival_kind<2>(L, st, blocks); break;

@@ -409,6 +409,16 @@ void order_far_for_xcds(std::vector<ArrItem>& far) {
   far.swap(out);
 }
 
+// Items up to which the two bands of a mixed query share a launch: as many waves as
+// run at once (256 CUs, four blocks of four).  Up to there a launch lasts as long as
+// its longest item, and two launches take the sum of both.  Random order, apart and
+// together: 9x7 visits (1 item) 63 and 45 us, 230x230 (3,170) 797 and 545; with
+// diffusion 20 times faster 45 and 40, 500 and 425.  Above, the far region fills the
+// chip by itself, and the near band's queues leave it room for three blocks per CU
+// instead of four: 256x256 (4,700) 0.91 ms and 0.67, 300x300 (8,600) 1.25 and 1.08,
+// but with hardly any diffusion 1.30 and 1.37, and 512x512 (35,000) 6.65 and 7.2.
+constexpr int kOneLaunch = 4096;
+
 dd_status run_arrival(dd_scan* s, bool mixed, double* out_dev, const OutFlag& fl, hipStream_t st) {
   dd_status rc = s->prepare(st);
   if (rc != DD_OK) return rc;
@@ -484,19 +494,27 @@ dd_status run_arrival(dd_scan* s, bool mixed, double* out_dev, const OutFlag& fl
   L.R = R;
   L.mixed = mixed;
   L.items = s->items.as<ArrItem>();
-  L.n_items = P.n_near;
-  L.near = true;
-  L.R = RN;
-  ProfToken tn = prof_begin("arrival_near", st);
-  DD_HIP(launch_arrival(L, st), "arrival near-band launch");
-  prof_end(tn, st, P.near_pairs, P.near_flops);
-  L.items = s->items.as<ArrItem>() + P.n_near;
-  L.n_items = P.n_far;
-  L.near = false;
-  L.R = R;
-  ProfToken tf = prof_begin("arrival_far", st);
-  DD_HIP(launch_arrival(L, st), "arrival far-region launch");
-  prof_end(tf, st, P.far_pairs, P.far_flops);
+  if (mixed && P.n_near + P.n_far <= kOneLaunch) {
+    L.n_items = P.n_near + P.n_far;
+    prof_end(prof_begin("arrival_near", st), st, P.near_pairs, P.near_flops);
+    ProfToken tf = prof_begin("arrival_far", st);
+    DD_HIP(launch_arrival_both(L, P.n_near, RN, st), "arrival launch");
+    prof_end(tf, st, P.far_pairs, P.far_flops);
+  } else {
+    L.n_items = P.n_near;
+    L.near = true;
+    L.R = RN;
+    ProfToken tn = prof_begin("arrival_near", st);
+    DD_HIP(launch_arrival(L, st), "arrival near-band launch");
+    prof_end(tn, st, P.near_pairs, P.near_flops);
+    L.items = s->items.as<ArrItem>() + P.n_near;
+    L.n_items = P.n_far;
+    L.near = false;
+    L.R = R;
+    ProfToken tf = prof_begin("arrival_far", st);
+    DD_HIP(launch_arrival(L, st), "arrival far-region launch");
+    prof_end(tf, st, P.far_pairs, P.far_flops);
+  }
   ProfToken tq = prof_begin("reduce", st);
   DD_HIP(launch_reduce_arrival(s->partial.as<double>(), s->aux.as<int32_t>(), s->V, 0, 64 * R,
                                s->pref, 0, s->V, out_dev, fl, st),
@@ -592,7 +610,7 @@ dd_status dd::launch_range(dd_scan* s, bool mixed, const RangePlan& rp, int64_t 
     L.R = P.R;
     if (profile) prof_end(prof_begin("arrival_near", st), st, P.near_pairs, P.near_flops);
     ProfToken tf = profile ? prof_begin("arrival_far", st) : ProfToken{};
-    DD_HIP(launch_arrival_range(L, P.n_near, P.RN, st), "arrival range launch");
+    DD_HIP(launch_arrival_both(L, P.n_near, P.RN, st), "arrival range launch");
     if (profile) prof_end(tf, st, P.far_pairs, P.far_flops);
   } else {
     L.n_items = P.n_near;
