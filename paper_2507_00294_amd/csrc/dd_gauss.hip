@@ -11,9 +11,9 @@
 //   psi(v, u) = sum_{i,k} [omega_ik e^{-beta_ik (Y_v - y_i)^2}] [e^{-beta_ik (X_u - x_i)^2}]
 // over all (visit, node) pairs: one FP64 multiply-add per pixel, visit and
 // node instead of a series and an exponential.  All terms are positive and
-// the rules are good to 2e-15 of each visit's own term at every distance, so
-// the sum keeps its relative accuracy at every pixel, also where all terms
-// are tiny.
+// the rules are good to 5e-15 of each visit's own term at every distance (see
+// gauss_nodes), so the sum keeps its relative accuracy at every pixel, also
+// where all terms are tiny.
 //
 // A wave owns a tile of 16 F x 16 F pixels and a chunk of visits.  It takes 64
 // visits at a time, one per lane, drops those that are beyond the cull for the
@@ -32,9 +32,9 @@
 // waves (measured); a step is F^2 MFMAs and 2 F exponentials of 18 operations,
 // i.e. 1150 + 630 cycles at F = 4 and 72 + 160 at F = 1, which is why F is as
 // large as the call's work allows.  Measured against a per-pair series with
-// its own exponential (25 to 60 FP64 operations a pair): the final map of a
-// 256x256 scan (4.3e9 pairs) 6.4 -> 0.89 ms, 512 maps of 128x128 over a 64x64
-// scan 24.8 -> 7.3 ms, 64 maps of 32x32 of an 8x8 scan 74 -> 35 us.
+// its own exponential (25 to 60 FP64 operations a pair), random order: the final
+// map of a 256x256 scan (4.3e9 pairs) 6.4 -> 0.84 ms, 512 maps of 128x128 over a
+// 64x64 scan 28.8 -> 3.2 ms, 64 maps of 32x32 of an 8x8 scan 104 -> 53 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -140,8 +140,9 @@ __device__ __forceinline__ double gauss_log1p(double q) {
 }
 
 // Nodes for which one Gauss-Legendre rule on [0, L] has a relative error below
-// 2e-15 for every a with a (1/b0 - 1/b1) <= dx (found by comparing rules with a
-// 96-node composite one in 64-bit-mantissa arithmetic over L and dx); 0 if
+// 2.6e-15 for every a with a (1/b0 - 1/b1) <= dx (against the integral in 40
+// digits: 1e-15 to 2.4e-15 at the ends of these ranges and L small, 2.6e-15 with
+// 16 nodes at dx = 22, where the roundings of the nodes bring it to 4.5e-15); 0 if
 // more than 16 are needed or L > 0.3: panels (below).
 __device__ __forceinline__ int gauss_nodes(double L, double dx) {
   if (L > 0.3 || dx > 22.0) return 0;
@@ -460,20 +461,20 @@ __global__ void __launch_bounds__(256) k_gauss_reduce(const GaussJob* __restrict
 // or a smaller one that leaves so much less of itself empty that a node of four
 // visits takes fewer cycles for the whole map: 1780, 600 and 230 per tile for F =
 // 4, 2, 1, and 600 per row of 128 pixels, where a call has 2048 items of them, or
-// 1024 and they take half the cycles (64x1 pixels, 256x256 scan, 128 items: 314 us,
-// 142 with F = 1; 500x2 of 65536 visits, 1024 items: 380 and 231; 1x2048 of 4096 visits,
-// 1024 items: 12 and 28 a map).  64 maps of a 64x64 scan,
-// 4096x1 pixels: 7.8 ms with F = 4, 1.5 in rows; 512x8: 2.7 with F = 4, 0.95 with F = 1;
-// 8x8: 0.84 and 0.16.  (With the recent visits apart, below: 1.1, 0.65 and 0.09.)
+// 1024 and they take half the cycles (one map of a 256x256 scan: 64x1 pixels, 128
+// items, 373 us in rows, 157 with F = 1; 500x2, 1024 items, 393 and 240; 1x2048 of
+// 4096 visits, 1024 items, 12 and 28 a map).  64 maps of a 64x64 scan, 4096x1 pixels:
+// 5.9 ms with F = 4, 3.6 with F = 1, 1.0 in rows; 512x8: 0.89 with F = 4, 0.58 with
+// F = 1; 8x8: 162 and 65 us.
 // Where a call has more than 16k items of that kind (64k rows), chunks grow to
 // leave about half as many.
 // The 64 most recent visits of a map take up to a hundred nodes each, a million
 // cycles of one wave at F = 4, as much as thousands of older ones: they have chunks of
 // their own, unless the call's tiles alone are enough for every wave to have such a
-// share (256 maps of 33x33 of a 64x64 scan: 3.3 ms without, 0.59; 64 of 128x128:
-// 2.9 and 0.56; 512 of 128x128: 7.5 and 4.7; 4000 of 64x64 of an 8x8 scan: 0.87
-// without, 1.2).  Partial sums: at most 32 kB an item, 1 GiB in all, or one chunk's
-// for a call of more than 8k tiles.
+// share.  Of a 64x64 scan, together and apart: 64 maps of 8x8 141 and 64 us, 256 of
+// 33x33 660 and 485, 512 of 64x64 1170 and 1040; 4000 of 64x64 of an 8x8 scan 850
+// and 920.  Partial sums: at most 32 kB an item, 1 GiB in all, or one chunk's for a
+// call of more than 8k tiles.
 GaussShape gauss_shape(int64_t w, int64_t h, int64_t n_vis, int64_t n_t) {
   auto up64 = [](int64_t v) { return (v + 63) / 64 * 64; };
   const int64_t base0 = std::max<int64_t>(64, up64((n_vis + 127) / 128));

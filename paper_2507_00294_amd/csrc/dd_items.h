@@ -145,16 +145,17 @@ __device__ __forceinline__ float series_row32_q(float a, const RowSel<M>& row, f
 //
 // Lane l = 4 b + c owns the R visits j = J + R u + t, t < R, u = far_unit(b) + 2 c:
 // a block's columns are every other unit of R visits, and two blocks share eight
-// units (items with an edge: every unit, u = 4 b + c, see kFarSpace).  Step D takes, per t, the four earlier visits i = J + R far_unit(b) + t - D
-// - v, v < 4, of block b (the A rows) against the block's four columns c: lane
-// (b, c) gets the pairs of lags D + 2 R c + v, four consecutive lags per lane and
-// step.  The lag now differs between a block's lanes, so the fields of the lag
-// rows that the form needs pass through a ring of 128 lags in LDS, one row per
-// lane and 64 lags at a time (coalesced, prefetched), and are read back by
-// broadcast; lags outside [lo, hi), which the slant adds at both ends, get zero
-// coefficients.  Terms are summed in groups of R consecutive lags from lo in FP32,
-// then in FP64; with columns two groups apart, the parity of a group is that of
-// the step (R = 4) or of v / R (R = 2) in every lane (see far_alone).
+// units (items with an edge: every unit, u = 4 b + c, see kFarSpace).  Step D takes,
+// per t, the four earlier visits i = J + R far_unit(b) + t - D - v, v < 4, of block b
+// (the A rows) against the block's four columns c: lane (b, c) gets the pairs of
+// lags D + 2 R c + v, four consecutive lags per lane and step.  The lag differs
+// between a block's lanes, so the fields of the lag rows that the form needs pass
+// through a ring of 128 lags in LDS, one row per lane and 64 lags at a time
+// (coalesced, prefetched), and are read back by broadcast; lags outside [lo, hi),
+// which the slant adds at both ends, get zero coefficients.  Terms are summed in
+// groups of R consecutive lags from lo in FP32, then in FP64; with columns two
+// groups apart, the parity of a group is that of the step (R = 4) or of v / R
+// (R = 2) in every lane (see far_alone).
 //
 // Bound: VALU issue, in the folded form a product, the exponential (two
 // issues) and a fused multiply-add per pair, and 1/R of a conversion and an FP64

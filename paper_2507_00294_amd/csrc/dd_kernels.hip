@@ -132,9 +132,9 @@ k_arrival_both32(const float2* __restrict__ pos, const uint2* __restrict__ posh,
 
 // Far and near-band items of a mixed map call in one launch, far blocks first: a
 // small call is bound by its longest item, and an item of one kind fills the time of
-// the other's.  One 16x16 map of a 128x128 scan: 154 us far and 48 near in launches of
-// their own, 160 as mixed blocks of near and far waves, 145 so; 64 maps of 64x64 of
-// it 1.15 ms apart, 0.95 together (near blocks first: 1.18).
+// the other's.  One 16x16 map of a 128x128 scan: 264 us in launches of their own,
+// 222 with the near blocks first, 217 so; 64 maps of 64x64 of it 1.15 ms, 1.18 and
+// 0.95.
 template <int R, bool MM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_map(const uint2* __restrict__ pos, const float4* __restrict__ pos4,
