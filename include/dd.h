@@ -24,7 +24,10 @@
  *    pointer and the work is enqueued on `hip_stream` (a hipStream_t, NULL =
  *    the null stream); the call returns once the work is enqueued.  With
  *    out_on_device = 0, `out` is host memory and the call synchronizes the
- *    stream before returning.
+ *    stream before returning.  The library keeps events recorded on the
+ *    streams it was given: keep a stream while handles used on it live and
+ *    its thread makes further calls (waiting for an event whose stream is
+ *    gone fails in the HIP runtime).
  *  - Results are double precision in u/m^2 (the unit of Q0 per square metre).
  *  - Precision DD_FP64 evaluates every term in double precision;
  *    DD_MIXED evaluates the bulk of the E1 differences in single precision

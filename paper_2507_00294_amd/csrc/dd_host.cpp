@@ -86,6 +86,53 @@ dd_status ensure_device() {
   return DD_OK;
 }
 
+namespace {
+struct OwnStream {
+  hipStream_t st;
+  int dev;
+  bool free;
+};
+struct OwnStreams {
+  std::mutex mu;
+  std::vector<OwnStream> all;
+};
+OwnStreams& own_streams() {  // not destroyed: a handle may outlive this file's statics
+  static OwnStreams& s = *new OwnStreams;
+  return s;
+}
+}  // namespace
+
+hipError_t take_stream(hipStream_t* st) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  OwnStreams& S = own_streams();
+  std::lock_guard<std::mutex> lk(S.mu);
+  for (OwnStream& o : S.all)
+    if (o.free && o.dev == dev) {
+      o.free = false;
+      *st = o.st;
+      return hipSuccess;
+    }
+  try {
+    S.all.reserve(S.all.size() + 1);
+  } catch (const std::bad_alloc&) {
+    return hipErrorOutOfMemory;
+  }
+  hipStream_t s = nullptr;
+  if ((e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess) return e;
+  S.all.push_back(OwnStream{s, dev, false});
+  *st = s;
+  return hipSuccess;
+}
+
+void give_stream(hipStream_t st) {
+  OwnStreams& S = own_streams();
+  std::lock_guard<std::mutex> lk(S.mu);
+  for (OwnStream& o : S.all)
+    if (o.st == st) o.free = true;
+}
+
 // Gauss-Legendre rule on [0, 1] with n nodes by Newton iteration on P_n:
 // x[i] = (1 - z_i) / 2, w[i] = half the weight of z_i on [-1, 1].
 void gauss_legendre01(int n, double* x, double* w) {

@@ -20,6 +20,14 @@ dd_status hip_fail(hipError_t e, const char* what);
 bool host_alloc_ok(size_t bytes);
 hipError_t dev_alloc(void** p, size_t bytes);
 dd_status ensure_device();
+// A non-blocking stream of the current device for the library's own work, and its
+// return.  Events that outlive a call (a scan's, a thread's scratch) may have been
+// recorded on it last, and the runtime looks at an event's stream when the event is
+// waited for: with the stream destroyed, that wait has failed with
+// hipErrorCapturedEvent.  Such streams are therefore taken again, never destroyed;
+// there are as many per device as were in use at once.
+hipError_t take_stream(hipStream_t* st);
+void give_stream(hipStream_t st);
 const GLNodes& gl_nodes();
 void gauss_legendre01(int n, double* x, double* w);
 double row_c(double lam, double kappa, double s2);

@@ -160,10 +160,10 @@ dd_status dd_autotune(const char* cache_path) {
   dd_status rc = ensure_device();
   if (rc != DD_OK) return rc;
   hipStream_t st = nullptr;
-  if (hipStreamCreate(&st) != hipSuccess) return fail(DD_EDEVICE, "hipStreamCreate failed");
+  if (take_stream(&st) != hipSuccess) return fail(DD_EDEVICE, "stream creation failed");
   struct StreamGuard {
     hipStream_t s;
-    ~StreamGuard() { (void)hipStreamDestroy(s); }
+    ~StreamGuard() { give_stream(s); }
   } sg{st};
   const TuneParams saved = tune();
   TuneParams best = saved;

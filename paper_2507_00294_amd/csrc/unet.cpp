@@ -522,7 +522,7 @@ void dd_unet_destroy(dd_unet* u) {
   }
   u->pieces.release();
   if (u->judge_done) (void)hipEventDestroy(u->judge_done);
-  if (u->judge_stream) (void)hipStreamDestroy(u->judge_stream);
+  if (u->judge_stream) give_stream(u->judge_stream);
   delete u;
 }
 
@@ -723,7 +723,7 @@ dd_status dd_unet_predict(dd_unet* u, dd_scan* const* scans, int32_t n, double s
     UN_HIP(spot.ensure(sizeof(double) * nok * kJudge.w * kJudge.h), "device allocation");
     UN_HIP(rel.ensure(sizeof(double) * nok), "device allocation");
     if (!u->judge_stream)
-      UN_HIP(hipStreamCreateWithFlags(&u->judge_stream, hipStreamNonBlocking), "stream creation");
+      UN_HIP(take_stream(&u->judge_stream), "stream creation");
     if (!u->judge_done)
       UN_HIP(hipEventCreateWithFlags(&u->judge_done, hipEventDisableTiming), "event creation");
     // the network, enqueued on the caller's stream

@@ -2,19 +2,21 @@
 // devices whose memory is host memory, copies made at once, launches written to a
 // log instead of run, and the runtime's rules that the tests look at: an event is
 // recorded on streams of its own device only, nothing synchronizes while a
-// stream is captured, a grid has fewer than 2^32 threads in x.  Preloaded before
-// libamdhip64 (see fake_hip.py).
+// stream is captured, an event whose stream is gone cannot be waited for, a grid
+// has fewer than 2^32 threads in x.  Preloaded before libamdhip64 (see fake_hip.py).
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 
 namespace {
 struct Event {
   int dev;
+  hipStream_t on;  // recorded on last
 };
 struct Stream {
   int dev;
@@ -26,6 +28,7 @@ std::string g_log;
 std::map<const void*, std::string> g_names;
 std::map<const void*, void*> g_symbols;
 std::map<void*, size_t> g_allocs;
+std::set<hipStream_t> g_gone;
 size_t g_held = 0, g_peak = 0, g_limit = ~(size_t)0;
 dim3 g_grid, g_block;
 hipStream_t g_stream;
@@ -134,7 +137,7 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
 }
 hipError_t hipStreamCreate(hipStream_t* s) { return hipStreamCreateWithFlags(s, 0); }
 hipError_t hipStreamDestroy(hipStream_t s) {
-  delete reinterpret_cast<Stream*>(s);
+  g_gone.insert(s);  // kept, so that no other stream gets its address
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return sync_allowed(); }
@@ -143,9 +146,13 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
   *c = g_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
 }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+// What the runtime has returned for events whose stream was destroyed.
+static hipError_t event_stream(hipEvent_t e) {
+  return g_gone.count(reinterpret_cast<Event*>(e)->on) ? fail(hipErrorCapturedEvent) : hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t e, unsigned) { return event_stream(e); }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
-  *e = reinterpret_cast<hipEvent_t>(new Event{g_dev});
+  *e = reinterpret_cast<hipEvent_t>(new Event{g_dev, nullptr});
   return hipSuccess;
 }
 hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
@@ -155,9 +162,13 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   if (reinterpret_cast<Event*>(e)->dev != device_of(s)) return fail(hipErrorInvalidHandle);
+  reinterpret_cast<Event*>(e)->on = s;
   return hipSuccess;
 }
-hipError_t hipEventSynchronize(hipEvent_t) { return sync_allowed(); }
+hipError_t hipEventSynchronize(hipEvent_t e) {
+  const hipError_t r = event_stream(e);
+  return r == hipSuccess ? sync_allowed() : r;
+}
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
   *ms = 0.f;
   return hipSuccess;
